@@ -183,8 +183,8 @@ struct CnnNet {
     }
 
     void reduce(int seg, int off, hipStream_t s) {
-        hipLaunchKernelGGL(k_cnn_reduce, dim3((seg + 255) / 256), dim3(256), 0, s, wpart, nblk_w, seg,
-                           grad + off);
+        hipLaunchKernelGGL(k_cnn_reduce, dim3((seg + 63) / 64), dim3(64 * CNN_RED_W), 0, s, wpart,
+                           nblk_w, seg, grad + off);
     }
 
     // Gradients of the loss of the last training forward pass into `grad`.

@@ -105,6 +105,25 @@ def test_gradients_match_oracle():
         off += cnt
 
 
+@pytest.mark.parametrize("m,n,b", [(16, 16, 1), (32, 16, 3), (128, 256, 5)])
+def test_gradients_match_oracle_at_tile_counts(m, n, b):
+    """One tile, fewer tiles than the 512 blocks of the weight-gradient
+    kernels, and 640 tiles (some blocks take a second one, which they request
+    ahead); same BF16 bar as above."""
+    blob = make_blob(6)
+    S = samples(m, n, b, 40)
+    tr = api.CnnTrainer(m, n, b, blob)
+    loss, g = tr.step(*cols(S, 0, 1, 2, 3), update=False, grad=True)
+    tr.close()
+    lref, gref = N.loss_and_grad(blob, S)
+    assert abs(loss - lref) <= 3e-2 * lref
+    off = 0
+    for name, shape in N.layout():
+        cnt = int(np.prod(shape))
+        assert rel(g[off:off + cnt], gref[off:off + cnt]) <= 5e-2, name
+        off += cnt
+
+
 def test_adam_matches_oracle_on_gpu_gradients():
     blob = make_blob(5)
     S = samples(M, NN, B, 30)
