@@ -172,10 +172,12 @@ struct CnnNet {
         o.gscale = 2.0 / ((double)B * (double)NP);
         if (training) {
             hipLaunchKernelGGL((k_cnn_out32<true>), tg, blk, 0, s, o);
-            hipLaunchKernelGGL((k_partials_sum<256>), dim3(1), blk, 0, s, part, nblk_out, B, sums);
+            hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                               part, nblk_out, B, sums);
         } else {
             hipLaunchKernelGGL((k_cnn_out32<false>), tg, blk, 0, s, o);
-            hipLaunchKernelGGL((k_partials_sum<256>), dim3(1), blk, 0, s, part, nblk_out, B, sums);
+            hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                               part, nblk_out, B, sums);
             if (shift)
                 hipLaunchKernelGGL(k_cnn_shift, dim3((unsigned)((NP + 255) / 256), B), blk, 0, s,
                                    d_smp, NP, sums);

@@ -483,8 +483,8 @@ void vcycle_mpfc_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) {
         if (l == 0 && C->prof) prof_mark(C, 3, s);
         if (T.norm) {
             const int nb = (A.m / T.tx) * (A.n / T.ty);
-            hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, nb, C->st,
-                               C->hist, A.h * A.h, C->o.tol, C->o.max_cycles + 1, C->o.diverge);
+            launch_norm_finalize(C->part, nb, C->st, C->hist, A.h * A.h, C->o.tol,
+                                 C->o.max_cycles + 1, C->o.diverge, s);
         }
     }
 }
@@ -501,8 +501,8 @@ void resnorm(mpfc_ctx* C, hipStream_t s) {
     else
         hipLaunchKernelGGL((k_resnorm<2, NT>), dim3(nb), dim3(NT), 0, s, finest_fields(C),
                            level_op(C, lv), lv.g, C->st, C->part, nullptr, nullptr, nullptr);
-    hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)nb, C->st,
-                       C->hist, h2, C->o.tol, max_norms, C->o.diverge);
+    launch_norm_finalize(C->part, (int)nb, C->st, C->hist, h2, C->o.tol, max_norms, C->o.diverge,
+                         s);
 }
 
 // ---- mixed precision ---------------------------------------------------------------
@@ -558,8 +558,8 @@ void defect(mpfc_ctx* C, int from, int add, hipStream_t s) {
     hipLaunchKernelGGL(kern, grid, dim3(DT_X * DT_Y), 0, s, F, level_op(C, F0), F0.g, C->st,
                        C->part, FF.e[0][0], FF.e[0][1], FF.e[0][2], add, F0.u[to][0], F0.u[to][1],
                        F0.u[to][2], FF.f[0], FF.f[1], FF.f[2], FF.pb);
-    hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)nb, C->st,
-                       C->hist, F0.h * F0.h, C->o.tol, max_norms, C->o.diverge);
+    launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h, C->o.tol, max_norms,
+                         C->o.diverge, s);
 }
 
 // One outer iteration of mixed precision starting from FP64 copy `from`:
@@ -1172,13 +1172,14 @@ int compute_energies(mpfc_ctx* C, const double* phi, const double* phiprev, cons
     // b^2 and of the warm start's squared residual (acc[10], acc[11])
     hipLaunchKernelGGL((k_sum2<NT>), dim3(rb), dim3(NT), 0, s, psi, (const double*)nullptr, total,
                        C->part, C->pst);
-    hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 2, C->acc + 8);
+    hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->part, (int)rb, 2, C->acc + 8);
     if (!warm)
         hipLaunchKernelGGL((k_fill<double>), grid1(total), dim3(256), 0, s, F0.w[0], total, 0.0);
     hipLaunchKernelGGL((k_p_rhs_resid<NT>), dim3(rb), dim3(NT), 0, s, F0.g, 1.0 / (F0.h * F0.h),
                        psi, C->acc + 8, F0.pf, warm ? F0.w[0] : nullptr, C->part);
-    hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 2,
-                       C->acc + 10);
+    hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->part, (int)rb, 2, C->acc + 10);
     // the warm start may already meet the stopping test (its residual is the
     // first norm of the solve)
     if (warm)
@@ -1190,8 +1191,8 @@ int compute_energies(mpfc_ctx* C, const double* phi, const double* phiprev, cons
                            1.0 / (F0.h * F0.h), phi, phiprev, F0.pf, F0.w[0], C->part,
                            (const double*)(C->pinned ? F0.pin : nullptr),
                            (const double*)(C->pinned ? C->phihat : nullptr));
-        hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 8,
-                           C->acc);
+        hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                           C->part, (int)rb, 8, C->acc);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpyAsync(C->host_buf, C->rb, 32 * sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -1266,9 +1267,8 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
             cnn_choose(C, s);  // leaves the kept guess's sum in part[0]
         }
         if (!mixed) {
-            hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part,
-                               learned ? 1 : (int)nb, C->st, C->hist, F0.h * F0.h, C->o.tol,
-                               C->o.max_cycles + 1, C->o.diverge);
+            launch_norm_finalize(C->part, learned ? 1 : (int)nb, C->st, C->hist, F0.h * F0.h,
+                                 C->o.tol, C->o.max_cycles + 1, C->o.diverge, s);
         } else {
             const auto& FF = C->FL[0];
             if (C->p.scheme == 2)
@@ -1307,16 +1307,15 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
     }
     if (C->o.precision != MPFC_MIXED) {
         if (learned) {  // the pick left the kept guess's squared norm in part[0]
-            hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, 1, C->st,
-                               C->hist, F0.h * F0.h, C->o.tol, C->o.max_cycles + 1, C->o.diverge);
+            launch_norm_finalize(C->part, 1, C->st, C->hist, F0.h * F0.h, C->o.tol,
+                                 C->o.max_cycles + 1, C->o.diverge, s);
         } else {
             // the completed guess satisfies N^(2) = S^(2), N^(3) = S^(3): only r1 is left
             const unsigned nb = red_blocks(total);
             hipLaunchKernelGGL((k_resnorm_guess<NT>), dim3(nb), dim3(NT), 0, s, finest_fields(C),
                                level_op(C, F0), g0, C->part);
-            hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)nb,
-                               C->st, C->hist, F0.h * F0.h, C->o.tol, C->o.max_cycles + 1,
-                               C->o.diverge);
+            launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h, C->o.tol,
+                                 C->o.max_cycles + 1, C->o.diverge, s);
         }
     } else {
         const auto& FF = C->FL[0];
@@ -1364,8 +1363,8 @@ void enqueue_wrapup(mpfc_ctx* C, hipStream_t s, bool warm, int npoisson) {
     auto k1 = C->p.scheme == 1 ? k_wrap_psi_sums<1, NT> : k_wrap_psi_sums<2, NT>;
     hipLaunchKernelGGL(k1, dim3(rb), dim3(NT), 0, s, io, C->st, mixed, wf, warm ? 1 : 0, total,
                        C->p.dt, C->part, C->pst);
-    hipLaunchKernelGGL((k_wrap_partials<NT>), dim3(1), dim3(NT), 0, s, C->st, C->part, (int)rb, 2,
-                       C->acc + 8);
+    hipLaunchKernelGGL((k_wrap_partials<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->st, C->part, (int)rb, 2, C->acc + 8);
     if (!warm) {
         hipLaunchKernelGGL(k_wrap_w_zero, grid1(total), dim3(256), 0, s, C->st, F0.w[0], total);
     } else {
@@ -1385,12 +1384,12 @@ void enqueue_wrapup(mpfc_ctx* C, hipStream_t s, bool warm, int npoisson) {
     // the warm start's residual is the first norm of the Poisson solve: it
     // may already meet the test, and the cycles behind it then exit at once
     if (warm)
-        hipLaunchKernelGGL((k_wrap_partials_pnorm<NT>), dim3(1), dim3(NT), 0, s, C->st, C->part,
-                           (int)rb, C->acc, C->pst, C->phist, kPoissonRel, kPoissonStall,
-                           kPoissonMax);
+        hipLaunchKernelGGL((k_wrap_partials_pnorm<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                           C->st, C->part, (int)rb, C->acc, C->pst, C->phist, kPoissonRel,
+                           kPoissonStall, kPoissonMax);
     else
-        hipLaunchKernelGGL((k_wrap_partials<NT>), dim3(1), dim3(NT), 0, s, C->st, C->part, (int)rb,
-                           12, C->acc);
+        hipLaunchKernelGGL((k_wrap_partials<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                           C->st, C->part, (int)rb, 12, C->acc);
     for (int k = 0; k < npoisson; ++k) vcycle_poisson(C, s);
     // A warm start with no cycle behind it keeps the sums above (the host runs
     // cycles and the sums again if it fails its test): nothing to enqueue.
@@ -1406,8 +1405,8 @@ void enqueue_energy_terms(mpfc_ctx* C, hipStream_t s, bool warm) {
                        (const StepIO*)C->io, F0.g, 1.0 / (F0.h * F0.h), F0.pf, F0.w[0], C->part,
                        (const double*)(C->pinned ? F0.pin : nullptr),
                        (const double*)(C->pinned ? C->phihat : nullptr));
-    hipLaunchKernelGGL((k_wrap_terms_sum<NT>), dim3(1), dim3(NT), 0, s, C->st, C->pst,
-                       warm ? 1 : 0, C->part, (int)rb, C->acc);
+    hipLaunchKernelGGL((k_wrap_terms_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->st, C->pst, warm ? 1 : 0, C->part, (int)rb, C->acc);
 }
 
 }  // namespace

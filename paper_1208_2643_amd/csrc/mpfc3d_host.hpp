@@ -277,9 +277,8 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
     } else {
         hipLaunchKernelGGL((k3_resnorm<Op, NT>), dim3(nb), dim3(NT), 0, s, op_of(F0), F0.g, FF,
                            C->part, stop);
-        hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)nb, C->st,
-                           C->hist, F0.h * F0.h * F0.h, C->o.tol, C->o.max_cycles + 1,
-                           C->o.diverge);
+        launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h * F0.h, C->o.tol,
+                             C->o.max_cycles + 1, C->o.diverge, s);
     }
     HIP_TRY(hipGetLastError());
     return MPFC_OK;
@@ -334,7 +333,8 @@ int compute_energies3(mpfc3d_ctx* C, const double* phi, const double* phiprev, c
     const bool advance = warm && mu;
     hipLaunchKernelGGL((k_sum2<NT>), dim3(rb), dim3(NT), 0, s, psi, advance ? mu : nullptr, total,
                        C->part, C->pst);
-    hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 2, C->acc + 8);
+    hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->part, (int)rb, 2, C->acc + 8);
     if (!warm) {
         hipLaunchKernelGGL((k_fill<double>), dim3(blocks256(total)), dim3(256), 0, s, F0.w, total, 0.0);
     } else if (advance) {
@@ -347,7 +347,8 @@ int compute_energies3(mpfc3d_ctx* C, const double* phi, const double* phiprev, c
     }
     hipLaunchKernelGGL((k3_p_rhs<NT>), dim3(rb), dim3(NT), 0, s, F0.g, ih2, psi, C->acc + 8, F0.pf,
                        warm ? F0.w : nullptr, C->part);
-    hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 2, C->acc + 10);
+    hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->part, (int)rb, 2, C->acc + 10);
     if (warm)
         hipLaunchKernelGGL((k_p_finalize<NT>), dim3(1), dim3(NT), 0, s, C->acc + 11, 1, C->pst,
                            C->phist, C->acc + 10, kPoissonRel, kPoissonStall, kPoissonMax);
@@ -367,7 +368,8 @@ int compute_energies3(mpfc3d_ctx* C, const double* phi, const double* phiprev, c
     C->have_w = true;
     hipLaunchKernelGGL((k3_energy_terms<NT>), dim3(rb), dim3(NT), 0, s, F0.g, ih2, phi, phiprev,
                        F0.pf, F0.w, C->part);
-    hipLaunchKernelGGL((k_partials_sum<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, 8, C->acc);
+    hipLaunchKernelGGL((k_partials_sum<kSumThreads>), dim3(1), dim3(kSumThreads), 0, s,
+                       C->part, (int)rb, 8, C->acc);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(C->host_buf, C->acc, 8 * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -533,9 +535,8 @@ int mpfc3d_step(mpfc3d_ctx* C, const double* phi_n, const double* phi_nm1, doubl
             if (nw) hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, true>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, true>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
             else hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, false>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, false>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
         }
-        hipLaunchKernelGGL((k_norm_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)rb, C->st,
-                           C->hist, F0.h * F0.h * F0.h, C->o.tol, C->o.max_cycles + 1,
-                           C->o.diverge);
+        launch_norm_finalize(C->part, (int)rb, C->st, C->hist, F0.h * F0.h * F0.h, C->o.tol,
+                             C->o.max_cycles + 1, C->o.diverge, s);
     }
     HIP_TRY(hipGetLastError());
     // cycles: enqueue the expected number, then one or two at a time until the
