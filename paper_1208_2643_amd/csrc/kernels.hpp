@@ -54,6 +54,24 @@ __device__ __forceinline__ float recip_ge1(float x) {
     return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
 
+// The same for K values, step by step (independent chains interleaved).
+template <typename T, int K>
+__device__ __forceinline__ void recip_ge1_n(const T (&x)[K], T (&r)[K]) {
+    T e[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if constexpr (sizeof(T) == 8) r[k] = __builtin_amdgcn_rcp(x[k]);
+        else r[k] = __builtin_amdgcn_rcpf(x[k]);
+    }
+#pragma unroll
+    for (int it = 0; it < (sizeof(T) == 8 ? 2 : 1); ++it) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) e[k] = T(1) - x[k] * r[k];
+#pragma unroll
+        for (int k = 0; k < K; ++k) r[k] += r[k] * e[k];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Nonlinear term of N^(2) (App. B.1: phi^3; App. B.2: chi(phi, phi^k)(phi + phi^k)/2
 // with chi(a, b) = (a^2 + b^2)/2) and its derivative.  In DEFECT mode v is a
@@ -88,6 +106,25 @@ __device__ __forceinline__ T nl_lin(T x, T xk) {
     }
 }
 
+// Both of the above at once (non-defect second-order form: they share
+// q = (v^2 + xk^2)/4 and v + xk).
+template <typename T, int SCHEME, bool NEWTON, bool DEFECT>
+__device__ __forceinline__ void nl_both(T v, T pb, T xk, T& g, T& d) {
+    if constexpr (DEFECT) {
+        g = nl_value<T, SCHEME, DEFECT>(v, pb, xk);
+        d = nl_lin<T, SCHEME, NEWTON>(pb + v, xk);
+    } else if constexpr (SCHEME == 1) {
+        const T v2 = v * v;
+        g = v2 * v;
+        d = NEWTON ? T(3) * v2 : v2;
+    } else {
+        const T hv = T(0.5) * v, s = v + xk;
+        const T q = T(0.5) * hv * v + T(0.25) * xk * xk;
+        g = q * s;
+        d = NEWTON ? hv * s + q : q;   // (3 v^2 + 2 v xk + xk^2)/4
+    }
+}
+
 // Per-level operator constants.
 template <typename T>
 struct LevelOp {
@@ -96,6 +133,21 @@ struct LevelOp {
     T al;    // alpha (scheme 1) or alpha/2 (scheme 2)
     T e;     // 1 (scheme 1) or 1/2 (scheme 2): N^(3) = kappa - e Lap phi
     T w = T(1);  // relaxation factor of the smoother's cell update (1: App. B)
+    // formed from the above (derive): the local system of the smoother,
+    // [[1, a, 0], [-d, 1, b], [ec, 0, 1]] with d = al + d' (d' the linearised
+    // nonlinear coefficient), has determinant det0 + a d'; d + b ec = dd0 + d'
+    T k1, e1;            // c/h^2, e/h^2
+    T a, b, ec;          // 4c/h^2, 4/h^2, 4e/h^2
+    T det0, dd0;         // 1 + a (al + b ec), al + b ec
+    __host__ __device__ void derive() {
+        k1 = c * ih2;
+        e1 = e * ih2;
+        a = T(4) * k1;
+        b = T(4) * ih2;
+        ec = T(4) * e1;
+        dd0 = al + b * ec;
+        det0 = T(1) + a * dd0;
+    }
 };
 
 // Boundary conditions, per axis (App. A): periodic (eqs. per-bcs) unless the

@@ -87,11 +87,11 @@ void launch_coarse(const Op& op, const CoarseArgs<typename Op::real>& A, bool fo
                    const CycleState* stop, hipStream_t s) {
     const dim3 g1(1), blk(CP_THREADS);
     if (A.geo.bc) {
-        if (four) hipLaunchKernelGGL((k_coarse_persistent<Op, CP_THREADS, 4, true>), g1, blk, 0, s, op, A, stop);
-        else hipLaunchKernelGGL((k_coarse_persistent<Op, CP_THREADS, 8, true>), g1, blk, 0, s, op, A, stop);
+        if (four) hipLaunchKernelGGL((k_coarse_persistent<Op, 4, true>), g1, blk, 0, s, op, A, stop);
+        else hipLaunchKernelGGL((k_coarse_persistent<Op, 8, true>), g1, blk, 0, s, op, A, stop);
     } else {
-        if (four) hipLaunchKernelGGL((k_coarse_persistent<Op, CP_THREADS, 4, false>), g1, blk, 0, s, op, A, stop);
-        else hipLaunchKernelGGL((k_coarse_persistent<Op, CP_THREADS, 8, false>), g1, blk, 0, s, op, A, stop);
+        if (four) hipLaunchKernelGGL((k_coarse_persistent<Op, 4, false>), g1, blk, 0, s, op, A, stop);
+        else hipLaunchKernelGGL((k_coarse_persistent<Op, 8, false>), g1, blk, 0, s, op, A, stop);
     }
 }
 
@@ -112,9 +112,9 @@ void launch_tile_batched(bool neu, int shape, const BatchTile<Op>* args, const B
 
 template <class Op, int NC>
 void launch_coarse_batched(bool neu, int nsim, const BatchCoarse<Op>* args, hipStream_t s) {
-    if (neu) hipLaunchKernelGGL((k_coarse_persistent_batched<Op, CP_THREADS, NC, true>), dim3(nsim),
+    if (neu) hipLaunchKernelGGL((k_coarse_persistent_batched<Op, NC, true>), dim3(nsim),
                                 dim3(CP_THREADS), 0, s, args);
-    else hipLaunchKernelGGL((k_coarse_persistent_batched<Op, CP_THREADS, NC, false>), dim3(nsim),
+    else hipLaunchKernelGGL((k_coarse_persistent_batched<Op, NC, false>), dim3(nsim),
                             dim3(CP_THREADS), 0, s, args);
 }
 

@@ -190,6 +190,7 @@ LevelOp<double> level_op(const mpfc_ctx* C, const Level& lv) {
     op.al = C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha;
     op.e = C->p.scheme == 1 ? 1.0 : 0.5;
     op.w = C->o.omega;
+    op.derive();
     return op;
 }
 
@@ -364,6 +365,7 @@ Op make_op32(const mpfc_ctx* C, const Level& lv) {
     o.op.al = (float)(C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha);
     o.op.e = (float)(C->p.scheme == 1 ? 1.0 : 0.5);
     o.op.w = (float)C->o.omega;
+    o.op.derive();
     return o;
 }
 
@@ -1050,6 +1052,7 @@ LevelOp<double> params_op(const mpfc_params* p) {
     op.c = c;
     op.al = p->scheme == 1 ? alpha : 0.5 * alpha;
     op.e = p->scheme == 1 ? 1.0 : 0.5;
+    op.derive();
     return op;
 }
 

@@ -92,6 +92,7 @@ LevelOp<double> level_op3(const mpfc3d_ctx* C, const Level3& lv) {
     o.c = C->c;
     o.al = C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha;
     o.e = C->p.scheme == 1 ? 1.0 : 0.5;
+    o.derive();
     return o;
 }
 

@@ -49,31 +49,76 @@ struct MpfcOp {
     static constexpr bool PW = PIN;
     LevelOp<T> op;
 
-    __device__ __forceinline__ void apply(const T* u, const T* ns, T xk, T pb, T w, T* N) const {
-        const T lphi = (ns[0] - T(4) * u[0]) * op.ih2;
-        const T lmu = (ns[1] - T(4) * u[1]) * op.ih2;
-        const T lka = (ns[2] - T(4) * u[2]) * op.ih2;
-        const T al = PIN ? op.al + w : op.al;
-        N[0] = u[0] - op.c * lmu;
-        N[1] = u[1] - nl_value<T, SCHEME, DEFECT>(u[0], pb, xk) - al * u[0] - lka;
-        N[2] = u[2] - op.e * lphi;
+    // The functions take K cells (which do not neighbour each other where they
+    // are updated) and do every operation for all of them in turn: a wave issues
+    // in order and a dependent FP64 operation waits 8 clocks against 4 to issue,
+    // so one cell's chain after the other left the unit idle half of the time.
+
+    // r = f - N(u).
+    template <int K>
+    __device__ __forceinline__ void resid(const T (&u)[K][3], const T (&ns)[K][3],
+                                          const T (&f)[K][3], const T (&xk)[K], const T (&pb)[K],
+                                          const T (&w)[K], T (&r)[K][3]) const {
+        T g[K], lap[K][3];
+#pragma unroll
+        for (int k = 0; k < K; ++k) g[k] = nl_value<T, SCHEME, DEFECT>(u[k][0], pb[k], xk[k]);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            r[k][0] = f[k][0] - u[k][0];
+            r[k][1] = (f[k][1] - u[k][1]) + (g[k] + (PIN ? op.al + w[k] : op.al) * u[k][0]);
+            r[k][2] = f[k][2] - u[k][2];
+        }
+        residual_lap(u, ns, lap, r);
     }
-    // Collective update of one cell: J_loc delta = f - N(u) (see relax_at).
-    __device__ __forceinline__ void relax(T* u, const T* ns, const T* f, T xk, T pb, T w) const {
-        T N[3];
-        apply(u, ns, xk, pb, w, N);
-        const T r1 = f[0] - N[0], r2 = f[1] - N[1], r3 = f[2] - N[2];
-        // (the base phi pb exists only in correction form)
-        const T d = (PIN ? op.al + w : op.al) +
-                    nl_lin<T, SCHEME, NEWTON>(DEFECT ? pb + u[0] : u[0], xk);
-        const T a = T(4) * op.c * op.ih2, b = T(4) * op.ih2, ec = T(4) * op.e * op.ih2;
-        const T det = T(1) + a * d + a * b * ec;
-        const T dm = (r2 + (d + b * ec) * r1 - b * r3) * recip_ge1(det);
-        const T dx = r1 - a * dm;
-        const T dk = r3 - ec * dx;
-        u[0] += op.w * dx;
-        u[1] += op.w * dm;
-        u[2] += op.w * dk;
+    // Collective update of the cells: J_loc delta = f - N(u) (see relax_at).
+    // What does not depend on the neighbours comes first (their LDS reads are
+    // in flight meanwhile).
+    template <int K>
+    __device__ __forceinline__ void relax(T (&u)[K][3], const T (&ns)[K][3], const T (&f)[K][3],
+                                          const T (&xk)[K], const T (&pb)[K],
+                                          const T (&w)[K]) const {
+        T d[K], det[K], rec[K], r[K][3], lap[K][3];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            T g;
+            nl_both<T, SCHEME, NEWTON, DEFECT>(u[k][0], pb[k], xk[k], g, d[k]);
+            if constexpr (PIN) d[k] += w[k];
+            r[k][0] = f[k][0] - u[k][0];
+            r[k][1] = (f[k][1] - u[k][1]) + (g + (PIN ? op.al + w[k] : op.al) * u[k][0]);
+            r[k][2] = f[k][2] - u[k][2];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) det[k] = op.det0 + op.a * d[k];
+        recip_ge1_n(det, rec);
+        residual_lap(u, ns, lap, r);
+        T dm[K], dx[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) dm[k] = r[k][1] + (op.dd0 + d[k]) * r[k][0];
+#pragma unroll
+        for (int k = 0; k < K; ++k) dm[k] = (dm[k] - op.b * r[k][2]) * rec[k];
+#pragma unroll
+        for (int k = 0; k < K; ++k) dx[k] = r[k][0] - op.a * dm[k];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            u[k][1] += op.w * dm[k];
+            u[k][0] += op.w * dx[k];
+            u[k][2] += op.w * (r[k][2] - op.ec * dx[k]);
+        }
+    }
+    // r (f - N without its Laplacians) completed with them.
+    template <int K>
+    __device__ __forceinline__ void residual_lap(const T (&u)[K][3], const T (&ns)[K][3],
+                                                 T (&lap)[K][3], T (&r)[K][3]) const {
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int k = 0; k < K; ++k) lap[k][f] = ns[k][f] - T(4) * u[k][f];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            r[k][0] += op.k1 * lap[k][1];
+            r[k][2] += op.e1 * lap[k][0];
+            r[k][1] += op.ih2 * lap[k][2];
+        }
     }
 };
 
@@ -86,11 +131,18 @@ struct PoissonOp {
     static constexpr bool PB = false;
     static constexpr bool PW = false;
     T ih2, h2;
-    __device__ __forceinline__ void apply(const T* u, const T* ns, T, T, T, T* N) const {
-        N[0] = (T(4) * u[0] - ns[0]) * ih2;
+    template <int K>
+    __device__ __forceinline__ void resid(const T (&u)[K][1], const T (&ns)[K][1],
+                                          const T (&f)[K][1], const T (&)[K], const T (&)[K],
+                                          const T (&)[K], T (&r)[K][1]) const {
+#pragma unroll
+        for (int k = 0; k < K; ++k) r[k][0] = f[k][0] - (T(4) * u[k][0] - ns[k][0]) * ih2;
     }
-    __device__ __forceinline__ void relax(T* u, const T* ns, const T* f, T, T, T) const {
-        u[0] = T(0.25) * (h2 * f[0] + ns[0]);
+    template <int K>
+    __device__ __forceinline__ void relax(T (&u)[K][1], const T (&ns)[K][1], const T (&f)[K][1],
+                                          const T (&)[K], const T (&)[K], const T (&)[K]) const {
+#pragma unroll
+        for (int k = 0; k < K; ++k) u[k][0] = T(0.25) * (h2 * f[k][0] + ns[k][0]);
     }
 };
 
@@ -118,16 +170,6 @@ struct TileArgs {
     int norm;
     double* part;
 };
-
-template <typename T>
-__device__ __forceinline__ T bilinear(const T* __restrict__ uH, const T* __restrict__ vH, int I,
-                                      int J, int Is, int Js, int mc) {
-    const size_t a = (size_t)J * mc + I, b = (size_t)J * mc + Is;
-    const size_t c = (size_t)Js * mc + I, d = (size_t)Js * mc + Is;
-    return T(9.0 / 16.0) * (uH[a] - vH[a]) +
-           T(3.0 / 16.0) * ((uH[b] - vH[b]) + (uH[c] - vH[c])) +
-           T(1.0 / 16.0) * (uH[d] - vH[d]);
-}
 
 // Cell index along one axis inside the tile and coarse kernels: plain
 // wrap-around in the periodic instantiation (NEU = false), the per-axis ghost
@@ -241,6 +283,24 @@ struct TileWork {
             const T s = dy == 1 ? O.u[cid(dx, 0)][f] : S.U[f][oc][ys][bx];
             ns[f] = (e + w) + (n + s);
         }
+    }
+    // f - N(u) (ZF: -N(u)) at cells C0 and C1 of the owned block.
+    template <int C0, int C1, bool ZF>
+    static __device__ __forceinline__ void resid2(const Op& op, const Lds& S, const Own& O,
+                                                  const Geo& G, int bx, int by, const Rhs& R,
+                                                  T (&r)[2][NF]) {
+        T u[2][NF], ns[2][NF], fv[2][NF];
+        nsum_own<C0>(S, O, G, bx, by, ns[0]);
+        nsum_own<C1>(S, O, G, bx, by, ns[1]);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            u[0][f] = O.u[C0][f];
+            u[1][f] = O.u[C1][f];
+            fv[0][f] = ZF ? T(0) : R.f[0][C0][f];
+            fv[1][f] = ZF ? T(0) : R.f[0][C1][f];
+        }
+        op.resid(u, ns, fv, {R.xk[0][C0], R.xk[0][C1]}, {R.pb[0][C0], R.pb[0][C1]},
+                 {R.w[0][C0], R.w[0][C1]}, r);
     }
     // The owned block's cells from LDS into registers (after a barrier).
     static __device__ __forceinline__ void load_own(const Lds& S, const Geo& G, Own& O) {
@@ -460,22 +520,24 @@ struct TileWork {
     if (!UP && OWN && A.complete_f) {
         if (t < nblk) {
             const int by = t / LX2, bx = t - by * LX2;
-            // all four cells computed without branches (the chains
-            // interleave), kept only where the cell can be updated
-            auto cell_f = [&](auto cc_) {
-                constexpr int c = decltype(cc_)::value;
-                const int x = 2 * bx + cdx(c), y = 2 * by + cdy(c);
-                const bool in = x >= 1 && y >= 1 && x < LX - 1 && y < LY - 1;
-                T ns[NF], N[NF];
-                nsum_own<c>(S, O, G, bx, by, ns);
-                op.apply(O.u[c], ns, xkr[0][c], pbr[0][c], wr[0][c], N);
+            // all four cells computed without branches, kept only where the
+            // cell can be updated
+            auto cells_f = [&](auto c0_, auto c1_) {
+                constexpr int c0 = decltype(c0_)::value, c1 = decltype(c1_)::value;
+                T r[2][NF];
+                resid2<c0, c1, true>(op, S, O, G, bx, by, R, r);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) fr[0][c][f] = in ? fr[0][c][f] + N[f] : fr[0][c][f];
+                for (int k = 0; k < 2; ++k) {
+                    const int c = k ? c1 : c0;
+                    const int x = 2 * bx + cdx(c), y = 2 * by + cdy(c);
+                    const bool in = x >= 1 && y >= 1 && x < LX - 1 && y < LY - 1;
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        fr[0][c][f] = in ? fr[0][c][f] - r[k][f] : fr[0][c][f];
+                }
             };
-            cell_f(std::integral_constant<int, 0>{});
-            cell_f(std::integral_constant<int, 1>{});
-            cell_f(std::integral_constant<int, 2>{});
-            cell_f(std::integral_constant<int, 3>{});
+            cells_f(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+            cells_f(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
         }
         __syncthreads();
     } else if (!UP && A.complete_f) {
@@ -491,16 +553,17 @@ struct TileWork {
                 if (x < 1 || y < 1 || x >= LX - 1 || y >= LY - 1) continue;
                 const int col = (x + y) & 1, oc = col ^ 1, k = x >> 1;
                 const int ke = (x + 1) >> 1, kw = (x - 1) >> 1;
-                T u[NF], ns[NF], N[NF];
+                T u[1][NF], ns[1][NF], r[1][NF];
+                const T zero[1][NF] = {};
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    u[f] = U[f][col][y][k];
-                    ns[f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
-                            (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
+                    u[0][f] = U[f][col][y][k];
+                    ns[0][f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
+                               (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
                 }
-                op.apply(u, ns, xkr[s][c], pbr[s][c], wr[s][c], N);
+                op.resid(u, ns, zero, {xkr[s][c]}, {pbr[s][c]}, {wr[s][c]}, r);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) fr[s][c][f] += N[f];
+                for (int f = 0; f < NF; ++f) fr[s][c][f] -= r[0][f];
             }
         }
         // every N(u) above reads u as loaded: no pass may write before all
@@ -517,17 +580,21 @@ struct TileWork {
         if constexpr (OWN) {
             if (t >= nblk) return;
             const int by = t / LX2, bx = t - by * LX2;
-            // both cells of the colour are relaxed without branches (their
-            // chains interleave; they do not neighbour each other), then
-            // stored where the pass updates them
-            auto cell = [&](auto cc_, T (&u)[NF]) {
-                constexpr int c = decltype(cc_)::value;
-                T ns[NF];
-                nsum_own<c>(S, O, G, bx, by, ns);
+            // both cells of the colour are relaxed without branches, then stored
+            // where the pass updates them
+            constexpr int c0 = colour == 0 ? 0 : 2, c1 = colour == 0 ? 1 : 3;
+            T u[2][NF], ns[2][NF], f2[2][NF];
+            nsum_own<c0>(S, O, G, bx, by, ns[0]);
+            nsum_own<c1>(S, O, G, bx, by, ns[1]);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) u[f] = O.u[c][f];
-                op.relax(u, ns, fr[0][c], xkr[0][c], pbr[0][c], wr[0][c]);
-            };
+            for (int f = 0; f < NF; ++f) {
+                u[0][f] = O.u[c0][f];
+                u[1][f] = O.u[c1][f];
+                f2[0][f] = fr[0][c0][f];
+                f2[1][f] = fr[0][c1][f];
+            }
+            op.relax(u, ns, f2, {xkr[0][c0], xkr[0][c1]}, {pbr[0][c0], pbr[0][c1]},
+                     {wr[0][c0], wr[0][c1]});
             // (a cell the pass does not update gets its own value back: only
             // its owner writes it, so the store is branch-free)
             auto put = [&](auto cc_, const T (&u)[NF]) {
@@ -541,12 +608,8 @@ struct TileWork {
                     O.u[c][f] = v;
                 }
             };
-            constexpr int c0 = colour == 0 ? 0 : 2, c1 = colour == 0 ? 1 : 3;
-            T u0[NF], u1[NF];
-            cell(std::integral_constant<int, c0>{}, u0);
-            cell(std::integral_constant<int, c1>{}, u1);
-            put(std::integral_constant<int, c0>{}, u0);
-            put(std::integral_constant<int, c1>{}, u1);
+            put(std::integral_constant<int, c0>{}, u[0]);
+            put(std::integral_constant<int, c1>{}, u[1]);
             return;
         }
 #pragma unroll
@@ -561,16 +624,17 @@ struct TileWork {
                 const int x = 2 * bx + dx, y = 2 * by + dy;
                 if (x < p || y < p || x >= LX - p || y >= LY - p) continue;
                 const int k = x >> 1, ke = (x + 1) >> 1, kw = (x - 1) >> 1;
-                T u[NF], ns[NF];
+                T u[1][NF], ns[1][NF], f1[1][NF];
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    u[f] = U[f][colour][y][k];
-                    ns[f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
-                            (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
+                    u[0][f] = U[f][colour][y][k];
+                    ns[0][f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
+                               (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
+                    f1[0][f] = fr[s][c][f];
                 }
-                op.relax(u, ns, fr[s][c], xkr[s][c], pbr[s][c], wr[s][c]);
+                op.relax(u, ns, f1, {xkr[s][c]}, {pbr[s][c]}, {wr[s][c]});
 #pragma unroll
-                for (int f = 0; f < NF; ++f) U[f][colour][y][k] = u[f];
+                for (int f = 0; f < NF; ++f) U[f][colour][y][k] = u[0][f];
             }
         }
     };
@@ -644,24 +708,22 @@ struct TileWork {
         T su[NF], sr[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) { su[f] = T(0); sr[f] = T(0); }
-        auto res_own = [&](auto cc_) {
-            constexpr int c = decltype(cc_)::value;
-            T ns[NF], N[NF];
-            nsum_own<c>(S, O, G, bx, by, ns);
-            op.apply(O.u[c], ns, xkr[0][c], pbr[0][c], wr[0][c], N);
+        auto res_own = [&](auto c0_, auto c1_) {
+            constexpr int c0 = decltype(c0_)::value, c1 = decltype(c1_)::value;
+            T r[2][NF];
+            resid2<c0, c1, false>(op, S, O, G, bx, by, R, r);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const T r = fr[0][c][f] - N[f];
-                su[f] += O.u[c][f];
-                sr[f] += r;
-                acc += (double)r * (double)r;
-            }
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    su[f] += O.u[k ? c1 : c0][f];
+                    sr[f] += r[k][f];
+                    acc += (double)r[k][f] * (double)r[k][f];
+                }
         };
         if constexpr (OWN) {
-            res_own(std::integral_constant<int, 0>{});
-            res_own(std::integral_constant<int, 1>{});
-            res_own(std::integral_constant<int, 2>{});
-            res_own(std::integral_constant<int, 3>{});
+            res_own(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+            res_own(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -669,20 +731,20 @@ struct TileWork {
                 const int x = 2 * bx + dx, y = 2 * by + dy;
                 const int col = (x + y) & 1, oc = col ^ 1, k = x >> 1;
                 const int ke = (x + 1) >> 1, kw = (x - 1) >> 1;
-                T u[NF], ns[NF], N[NF];
+                T u[1][NF], ns[1][NF], f1[1][NF], r[1][NF];
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    u[f] = U[f][col][y][k];
-                    ns[f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
-                            (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
+                    u[0][f] = U[f][col][y][k];
+                    ns[0][f] = (U[f][oc][y][ke] + U[f][oc][y][kw]) +
+                               (U[f][oc][y + 1][k] + U[f][oc][y - 1][k]);
+                    f1[0][f] = fr[s][c][f];
                 }
-                op.apply(u, ns, xkr[s][c], pbr[s][c], wr[s][c], N);
+                op.resid(u, ns, f1, {xkr[s][c]}, {pbr[s][c]}, {wr[s][c]}, r);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    const T r = fr[s][c][f] - N[f];
-                    su[f] += u[f];
-                    sr[f] += r;
-                    acc += (double)r * (double)r;
+                    su[f] += u[0][f];
+                    sr[f] += r[0][f];
+                    acc += (double)r[0][f] * (double)r[0][f];
                 }
             }
         }
@@ -799,11 +861,11 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_batched(const BatchTile<O
 // ---------------------------------------------------------------------------
 // Persistent kernel: every level of at most CP_CELLS cells, in LDS, one
 // workgroup.  Same V(nu1, nu2) cycle as the tiled levels; the coarsest grid is
-// solved directly (CoarseSolve).
+// solved directly.
 constexpr int CP_CELLS = 1024;  // largest level handled here (32 x 32)
 constexpr int CP_TOTAL = 1368;  // cells of all its levels (1024 + 256 + 64 + 16 + 4, padded)
 constexpr int CP_MAXLEV = 12;
-constexpr int CP_THREADS = 512;  // threads of the persistent workgroup
+constexpr int CP_THREADS = CP_CELLS / 2;  // one thread per red-black pair of the largest level
 
 struct CoarseGeom {
     int bc;               // boundary conditions (BC_NEUMANN_X | BC_NEUMANN_Y bits)
@@ -836,12 +898,11 @@ struct CoarseArgs {
 // indexed with compile-time indices only (row swaps are selects), so that it
 // lives in registers.
 template <class Op, int NC>
-__device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::real* phi,
-                                                  typename Op::real* mu, typename Op::real* ka,
-                                                  const typename Op::real (&f)[3 * NC],
-                                                  const typename Op::real* xk,
-                                                  const typename Op::real* pb,
-                                                  const typename Op::real* pw, int m, int lm,
+__device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::real (&u)[3][NC],
+                                                  const typename Op::real (&f)[3][NC],
+                                                  const typename Op::real (&xk)[NC],
+                                                  const typename Op::real (&pb)[NC],
+                                                  const typename Op::real (&pw)[NC], int m, int lm,
                                                   int n, int bc, int maxit, typename Op::real tol) {
     using T = typename Op::real;
     const T c = op.op.c, e = op.op.e, al = op.op.al;
@@ -874,7 +935,7 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
     };
     T f1[NC], f2[NC], f3[NC], t1[NC], t2[NC], rhs[NC];
 #pragma unroll
-    for (int a = 0; a < NC; ++a) { f1[a] = f[a]; f2[a] = f[NC + a]; f3[a] = f[2 * NC + a]; }
+    for (int a = 0; a < NC; ++a) { f1[a] = f[0][a]; f2[a] = f[1][a]; f3[a] = f[2][a]; }
     // rhs = f1 + c Lap(f2 + Lap f3)
     lap(f3, t1);
 #pragma unroll
@@ -897,7 +958,7 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
     T x[NC], xkv[NC], pbv[NC], alv[NC];
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
-        x[a] = phi[a];
+        x[a] = u[0][a];
         xkv[a] = Op::XK ? xk[a] : T(0);
         pbv[a] = Op::PB ? pb[a] : T(0);
         alv[a] = Op::PW ? al + pw[a] : al;  // pinning: W added to the phi coefficient
@@ -959,7 +1020,10 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
             smax = fmax(smax, fabs(t1[a]));
             xmax = fmax(xmax, fabs(x[a]));
         }
-        if (smax <= tol * (T(1) + xmax)) break;
+        // Newton's method converges quadratically: in FP64 a step below the root of
+        // the tolerance leaves an error below the tolerance
+        const T xs = T(1) + xmax;
+        if (smax <= tol * xs || (sizeof(T) == 8 && smax * smax <= tol * xs * xs)) break;
     }
     // recover kappa and mu
     lap(x, t1);
@@ -968,40 +1032,547 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
     lap(t1, t2);
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
-        ka[a] = t1[a];
-        mu[a] = f2[a] + nl_value<T, (Op::XK ? 2 : 1), Op::PB>(x[a], pbv[a], xkv[a]) + alv[a] * x[a] + t2[a];
-        phi[a] = x[a];
+        u[2][a] = t1[a];
+        u[1][a] = f2[a] + nl_value<T, (Op::XK ? 2 : 1), Op::PB>(x[a], pbv[a], xkv[a]) + alv[a] * x[a] + t2[a];
+        u[0][a] = x[a];
     }
 }
 
-// Coarsest grid, Poisson: w = G f + mean(v) (the mean of w is free; keep the
-// correction mean-free).  One thread per cell.
-template <typename T>
-__device__ void coarse_solve_poisson(T* w, const T* f, const T* v, const double* G, int ncell) {
-    const int t = threadIdx.x;
-    __shared__ T mv;
-    if (t == 0) {
-        T s = 0;
-        for (int k = 0; k < ncell; ++k) s += v[k];
-        mv = s / T(ncell);
-    }
-    __syncthreads();
-    if (t < ncell) {
-        T s = 0;
-        for (int k = 0; k < ncell; ++k) s += (T)G[t * ncell + k] * f[k];
-        w[t] = s + mv;
-    }
+// The same problem in the Laplacian's eigenvectors, for the grids whose
+// eigenvectors are the sign patterns w_k(a) = (-1)^popcount(k & a) (cell a =
+// i + j m): every 2 x 2 grid, and 4 x 2 or 2 x 4 with a periodic 4-cell axis.
+// With K = -Lap = diag(lam) in that basis, coefficients z of phi, and mode k's
+// equation divided by c lam_k, the Newton system is
+//   (1/(c lam) + e lam^2) delta + (W^T D W) delta = residual   (k > 0),
+// symmetric positive definite (D = g' + al + W >= 0), its matrix's entry (i, j)
+// the transform of D at i xor j: L D L^T without pivoting.  The mean (k = 0)
+// does not change in the iteration.  One thread: 1.6 us where the elimination
+// above takes 3 us (2 x 2); on 4 x 2 the elimination was about 15 us of a 34 us
+// coarse launch.
+template <int NC, typename T>
+__device__ __forceinline__ void walsh(const T (&x)[NC], T (&out)[NC], T scale) {
+#pragma unroll
+    for (int a = 0; a < NC; ++a) out[a] = scale * x[a];
+#pragma unroll
+    for (int h = 1; h < NC; h *= 2)
+#pragma unroll
+        for (int a = 0; a < NC; ++a)
+            if (!(a & h)) {
+                const T p = out[a], q = out[a + h];
+                out[a] = p + q;
+                out[a + h] = p - q;
+            }
 }
 
-template <class Op, int NTP, int NC, bool NEU>
-__device__ __forceinline__ void coarse_body(const Op& op_top,
-                                            const CoarseArgs<typename Op::real>& A,
-                                            const CycleState* stop);
+template <class Op, int NC>
+__device__ __forceinline__ void coarse_solve_walsh(const Op& op, typename Op::real (&u)[3][NC],
+                                                   const typename Op::real (&f)[3][NC],
+                                                   const typename Op::real (&xk)[NC],
+                                                   const typename Op::real (&pb)[NC],
+                                                   const typename Op::real (&pw)[NC], int m, int n,
+                                                   int bc, int maxit, typename Op::real tol) {
+    using T = typename Op::real;
+    constexpr int SCH = Op::XK ? 2 : 1;
+    constexpr T SC = T(1) / T(NC), TINY = sizeof(T) == 8 ? T(1e-280) : T(1e-30);
+    const T c = op.op.c, e = op.op.e, al = op.op.al, ih2 = op.op.ih2;
+    T lam[NC], icl[NC], s[NC], rho[NC], z[NC], fh[3][NC], x[NC], G[NC], D[NC], Gh[NC], Dh[NC];
+    // eigenvalue of an axis' sign pattern: 2 cells, (1, -1): 4/h^2 periodic, 2/h^2
+    // Neumann; 4 cells, patterns alternating in bit 0, bit 1, both: 4, 2, 2 / h^2
+    auto axis = [&](int k, int len, bool neu) {
+        if (len == 2) return k ? (neu ? T(2) : T(4)) : T(0);
+        return k == 0 ? T(0) : (k == 1 ? T(4) : T(2));
+    };
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        const int kx = k & (m - 1), ky = m == 2 ? k >> 1 : k >> 2;
+        lam[k] = ih2 * (axis(kx, m, bc & BC_NEUMANN_X) + axis(ky, n, bc & BC_NEUMANN_Y));
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) walsh<NC>(f[i], fh[i], SC);
+    walsh<NC>(u[0], z, SC);
+    {
+        T cl[NC];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const T t = c * lam[k];
+            rho[k] = fh[0][k] - t * (fh[1][k] - lam[k] * fh[2][k]);
+            cl[k] = k ? fmax(t, TINY) : T(1);
+        }
+        recip_ge1_n(cl, icl);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) s[k] = icl[k] + e * lam[k] * lam[k];
+    }
+    z[0] = rho[0];
+    for (int it = 0; it < maxit; ++it) {
+        walsh<NC>(z, x, T(1));
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            const T ala = Op::PW ? al + pw[a] : al;
+            nl_both<T, SCH, true, Op::PB>(x[a], pb[a], xk[a], G[a], D[a]);
+            G[a] += ala * x[a];
+            D[a] += ala;
+        }
+        walsh<NC>(G, Gh, SC);
+        walsh<NC>(D, Dh, SC);
+        // L D L^T of the modes 1 ... NC - 1, the right-hand side carried along
+        T M[NC][NC], b[NC];
+#pragma unroll
+        for (int i = 1; i < NC; ++i) {
+#pragma unroll
+            for (int j = 1; j <= i; ++j) M[i][j] = Dh[i ^ j] + (i == j ? s[i] : T(0));
+            b[i] = (rho[i] - z[i]) * icl[i] - e * lam[i] * lam[i] * z[i] - Gh[i];
+        }
+        T ip[NC];
+#pragma unroll
+        for (int k = 1; k < NC; ++k) {
+            const T pv[1] = {M[k][k]};
+            T rc[1];
+            recip_ge1_n(pv, rc);
+            ip[k] = rc[0];
+#pragma unroll
+            for (int i = k + 1; i < NC; ++i) {
+                const T l = M[i][k] * ip[k];
+#pragma unroll
+                for (int j = k + 1; j <= i; ++j) M[i][j] -= l * M[j][k];
+                b[i] -= l * b[k];
+            }
+        }
+        T smax = 0, xmax = fabs(z[0]);
+#pragma unroll
+        for (int k = NC - 1; k >= 1; --k) {
+            T t = b[k];
+#pragma unroll
+            for (int i = k + 1; i < NC; ++i) t -= M[i][k] * b[i];
+            b[k] = t * ip[k];
+            z[k] += b[k];
+            smax += fabs(b[k]);
+            xmax += fabs(z[k]);
+        }
+        // quadratic convergence: as in coarse_solve_mpfc
+        const T xs = T(1) + xmax;
+        if (smax <= tol * xs || (sizeof(T) == 8 && smax * smax <= tol * xs * xs)) break;
+    }
+    // kappa = f3 + e Lap phi, mu = f2 + g(phi) + al phi + Lap kappa
+    walsh<NC>(z, u[0], T(1));
+#pragma unroll
+    for (int a = 0; a < NC; ++a)
+        G[a] = nl_value<T, SCH, Op::PB>(u[0][a], pb[a], xk[a]) + (Op::PW ? al + pw[a] : al) * u[0][a];
+    walsh<NC>(G, Gh, SC);
+    T kh[NC], mh[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        kh[k] = fh[2][k] - e * lam[k] * z[k];
+        mh[k] = fh[1][k] + Gh[k] - lam[k] * kh[k];
+    }
+    walsh<NC>(kh, u[2], T(1));
+    walsh<NC>(mh, u[1], T(1));
+}
 
-template <class Op, int NTP, int NC, bool NEU>
-__global__ void __launch_bounds__(NTP) k_coarse_persistent(Op op_top, CoarseArgs<typename Op::real> A,
-                                                           const CycleState* stop) {
-    coarse_body<Op, NTP, NC, NEU>(op_top, A, stop);
+// The persistent workgroup.  A thread owns one row of a 2x2 block of every
+// level it works on: a red and a black cell, beside each other, with unknowns,
+// right-hand side and coefficients in registers while the level is relaxed.
+// Threads 2b and 2b + 1 hold the rows dy = 0, 1 of block b, so that a block's sums
+// (the restriction) are one lane exchange.  The unknowns are in LDS as a red and
+// a black array with one entry per thread: a cell's inner x neighbour is the
+// owner's other cell, its other three neighbours are of the other array.
+// Levels of at most 64 threads (8 x 8 cells and below) run in the first wave
+// alone: LDS instructions of one wave complete in order, so its half-sweeps
+// need no workgroup barrier.
+//
+// Bound by latency: a chain of dependent phases (about 46 for V(2,2) from
+// 32 x 32), each an LDS round trip (64 clocks and up) and the local solve, some
+// 40 FP64 operations that a wave issues in order, 8 clocks each when dependent.
+// V(2,2) in FP64 from 32 x 32, in the V-cycle graph of a 1024^2 grid: one cell
+// per thread and half-sweep, everything re-read from LDS, 24.7 us; a whole block
+// per thread (half the waves, twice the instructions in each) 23.1; this one
+// 18.4.
+template <class Op, int NC, bool NEU>
+struct CoarseWork {
+    using T = typename Op::real;
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    static constexpr int NF = Op::NF;
+    static constexpr int CPH = CP_TOTAL / 2;   // cells of one colour, all levels
+    struct Lds {
+        T u[2][NF][CPH], f[2][NF][CPH], v[2][NF][CPH];   // [colour][field][thread of a level]
+        T xk[2][Op::XK ? CPH : 1], pb[2][Op::PB ? CPH : 1], pw[2][Op::PW ? CPH : 1];
+        T E[NF][CP_CELLS / 4];  // u_H - v_H of the level below, row-major
+    };
+    struct Lev {
+        int m, n, lm, off, l;   // sides, log2 m, first LDS entry, level number
+        __device__ __forceinline__ Lev coarser() const {
+            return {m >> 1, n >> 1, lm - 1, off + ((m * n) >> 1), l + 1};
+        }
+        __device__ __forceinline__ Lev finer() const {
+            return {m << 1, n << 1, lm + 1, off - 2 * m * n, l - 1};
+        }
+        __device__ __forceinline__ bool coarsest() const { return m == 2 || n == 2; }
+        __device__ __forceinline__ bool one_wave() const { return m * n <= 128; }
+    };
+    // A thread's cells of a level: LDS entries of the neighbours outside its own
+    // row of the block (h: x neighbour of the red and of the black cell, vi and vo:
+    // y neighbour inside and outside the block), and the E entries it reads.  At
+    // a Neumann edge the neighbour index is the block itself (the ghost of the
+    // correction), and gh, gv say that a cell's own value is its ghost.
+    struct Pos {
+        bool on, gh[2], gv;
+        int dy, bx, by, q, h[2], vi, vo;
+        int e, ew, ee, eo, eow, eoe;
+    };
+    struct Own {
+        T u[2][NF], f[2][NF], xk[2], pb[2], pw[2];
+    };
+
+    static __device__ __forceinline__ Pos pos(const Lev& L, int bc) {
+        const int bw = L.m >> 1, bh = L.n >> 1, nt = 2 * bw * bh;
+        const bool nx = NEU && (bc & BC_NEUMANN_X), ny = NEU && (bc & BC_NEUMANN_Y);
+        Pos P;
+        P.on = (int)threadIdx.x < nt;
+        const int t = threadIdx.x & (nt - 1), b = t >> 1, dy = t & 1;
+        P.dy = dy;
+        P.bx = b & (bw - 1);
+        P.by = b >> (L.lm - 1);
+        const bool ge = nx && P.bx == bw - 1, gw = nx && P.bx == 0;
+        const bool go = ny && P.by == (dy ? bh - 1 : 0);
+        const int xe = ge ? P.bx : (P.bx + 1) & (bw - 1);
+        const int xw = gw ? P.bx : (P.bx - 1) & (bw - 1);
+        const int r = P.by * bw;
+        const int ro = (go ? P.by : (P.by + (dy ? 1 : -1)) & (bh - 1)) * bw;
+        P.gh[0] = dy ? ge : gw;
+        P.gh[1] = dy ? gw : ge;
+        P.gv = go;
+        P.q = L.off + t;
+        P.h[0] = L.off + 2 * (r + (dy ? xe : xw)) + dy;
+        P.h[1] = L.off + 2 * (r + (dy ? xw : xe)) + dy;
+        P.vi = L.off + (t ^ 1);
+        P.vo = L.off + 2 * (ro + P.bx) + (dy ^ 1);
+        P.e = r + P.bx; P.ew = r + xw; P.ee = r + xe;
+        P.eo = ro + P.bx; P.eow = ro + xw; P.eoe = ro + xe;
+        return P;
+    }
+    // LDS writes of the workgroup (WG) or of this wave before, reads after.
+    template <bool WG>
+    static __device__ __forceinline__ void sync() {
+        if constexpr (WG) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+    // Value of the thread that holds the block's other row.
+    static __device__ __forceinline__ int swap1(int x) {
+        return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2
+    }
+    static __device__ __forceinline__ T other_row(T x) {
+        if constexpr (sizeof(T) == 8)
+            return __hiloint2double(swap1(__double2hiint(x)), swap1(__double2loint(x)));
+        else
+            return __int_as_float(swap1(__float_as_int(x)));
+    }
+    // level l has spacing 2^l h_top: scale 1/h^2 (and h^2) by exact powers of two
+    static __device__ __forceinline__ Op opl(const Op& top, int l) {
+        Op o = top;
+        if constexpr (NF == 3) { o.op.ih2 = ldexp(top.op.ih2, -2 * l); o.op.derive(); }
+        else { o.ih2 = ldexp(top.ih2, -2 * l); o.h2 = ldexp(top.h2, 2 * l); }
+        return o;
+    }
+    static __device__ __forceinline__ void load_own(const Lds& S, const Pos& P, Own& O) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) { O.u[c][f] = S.u[c][f][P.q]; O.f[c][f] = S.f[c][f][P.q]; }
+            O.xk[c] = Op::XK ? S.xk[c][P.q] : T(0);
+            O.pb[c] = Op::PB ? S.pb[c][P.q] : T(0);
+            O.pw[c] = Op::PW ? S.pw[c][P.q] : T(0);
+        }
+    }
+    // Neighbour sums of the cell of colour C, every field: x neighbours first.
+    template <int C>
+    static __device__ __forceinline__ void nsum(const Lds& S, const Pos& P, const Own& O,
+                                                T (&ns)[NF]) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            T h = S.u[C ^ 1][f][P.h[C]], vo = S.u[C ^ 1][f][P.vo];
+            const T vi = S.u[C ^ 1][f][P.vi];
+            if constexpr (NEU) {
+                h = P.gh[C] ? O.u[C][f] : h;
+                vo = P.gv ? O.u[C][f] : vo;
+            }
+            ns[f] = (h + O.u[C ^ 1][f]) + (vi + vo);
+        }
+    }
+    // f - N(u) (ZF: -N(u)) at both cells.
+    template <bool ZF>
+    static __device__ __forceinline__ void resid(const Op& o, const Lds& S, const Pos& P,
+                                                 const Own& O, T (&r)[2][NF]) {
+        T ns[2][NF];
+        const T zero[2][NF] = {};
+        nsum<0>(S, P, O, ns[0]);
+        nsum<1>(S, P, O, ns[1]);
+        o.resid(O.u, ns, ZF ? zero : O.f, O.xk, O.pb, O.pw, r);
+    }
+    // f = R r + N(u).
+    static __device__ __forceinline__ void complete(const Op& o, const Lds& S, const Pos& P, Own& O) {
+        T r[2][NF];
+        resid<true>(o, S, P, O, r);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) O.f[c][f] -= r[c][f];
+    }
+    // Half-sweep of one colour, into registers and LDS.
+    template <int C>
+    static __device__ __forceinline__ void pass(const Op& o, Lds& S, const Pos& P, Own& O) {
+        T u[1][NF], ns[1][NF], f1[1][NF];
+        nsum<C>(S, P, O, ns[0]);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) { u[0][f] = O.u[C][f]; f1[0][f] = O.f[C][f]; }
+        o.relax(u, ns, f1, {O.xk[C]}, {O.pb[C]}, {O.pw[C]});
+#pragma unroll
+        for (int f = 0; f < NF; ++f) S.u[C][f][P.q] = O.u[C][f] = u[0][f];
+    }
+    template <bool WG>
+    static __device__ __forceinline__ void sweeps(const Op& o, Lds& S, const Pos& P, Own& O,
+                                                  int nsw) {
+#pragma unroll 1
+        for (int p = 0; p < nsw; p += 2) {
+            if (P.on) pass<0>(o, S, P, O);
+            sync<WG>();
+            if (P.on) pass<1>(o, S, P, O);
+            sync<WG>();
+        }
+    }
+    // Down part of one level: completed right-hand side, sweeps, residual and
+    // its restriction (with u and the coefficients) onto the next level.
+    template <bool WG>
+    static __device__ __forceinline__ void down(const Op& top, Lds& S, const Lev& L, int bc,
+                                                int nsw, bool compl_f) {
+        const Op o = opl(top, L.l);
+        const Pos P = pos(L, bc);
+        Own O;
+        if (P.on) {
+            load_own(S, P, O);
+            if (compl_f) complete(o, S, P, O);
+        }
+        if (WG && compl_f) __syncthreads();  // every N(u) reads u as loaded
+        if (P.on) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    S.v[c][f][P.q] = O.u[c][f];
+                    S.f[c][f][P.q] = O.f[c][f];
+                }
+        }
+        sweeps<WG>(o, S, P, O, nsw);
+        if (P.on) {
+            T r[2][NF];
+            resid<false>(o, S, P, O, r);
+            // coarse cell (bx, by): the block's averages, the u part stored by the
+            // first of its two threads, the residual by the second
+            const Lev C = L.coarser();
+            const int q = C.off + 2 * ((P.by >> 1) * (C.m >> 1) + (P.bx >> 1)) + (P.by & 1);
+            const int col = (P.bx ^ P.by) & 1;
+            T* d = P.dy ? &S.f[0][0][0] : &S.u[0][0][0];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const T su = O.u[0][f] + O.u[1][f], sr = r[0][f] + r[1][f];
+                const T au = T(0.25) * (su + other_row(su)), ar = T(0.25) * (sr + other_row(sr));
+                d[(col * NF + f) * CPH + q] = P.dy ? ar : au;
+            }
+            auto avg = [&](const T (&x)[2]) {
+                const T sx = x[0] + x[1];
+                return T(0.25) * (sx + other_row(sx));
+            };
+            if constexpr (Op::XK) S.xk[col][q] = avg(O.xk);
+            if constexpr (Op::PB) S.pb[col][q] = avg(O.pb);
+            if constexpr (Op::PW) S.pw[col][q] = avg(O.pw);
+        }
+        sync<WG>();
+    }
+    // Up part: the correction E prolonged onto u, sweeps, and this level's own
+    // correction u - v for the level above (on the top level S.u is the result).
+    template <bool WG>
+    static __device__ __forceinline__ void up(const Op& top, Lds& S, const Lev& L, int bc, int nsw) {
+        const Op o = opl(top, L.l);
+        const Pos P = pos(L, bc);
+        Own O;
+        if (P.on) {
+            load_own(S, P, O);
+            const int cw = P.dy;  // colour of the row's west cell
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                // bilinear, one axis after the other: the west and east cell's
+                // column in the block's own coarse row and in the outer one
+                const T* E = S.E[f];
+                const T c0 = T(0.75) * E[P.e], c1 = T(0.75) * E[P.eo];
+                const T w = T(0.75) * (c0 + T(0.25) * E[P.ew]) + T(0.25) * (c1 + T(0.25) * E[P.eow]);
+                const T e = T(0.75) * (c0 + T(0.25) * E[P.ee]) + T(0.25) * (c1 + T(0.25) * E[P.eoe]);
+                O.u[0][f] += cw ? e : w;
+                O.u[1][f] += cw ? w : e;
+                S.u[0][f][P.q] = O.u[0][f];
+                S.u[1][f][P.q] = O.u[1][f];
+            }
+        }
+        sync<WG>();
+        sweeps<WG>(o, S, P, O, nsw);
+        if (P.on && L.l > 0) {
+            const int row = (2 * P.by + P.dy) << L.lm;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    S.E[f][row + 2 * P.bx + (c ^ P.dy)] = O.u[c][f] - S.v[c][f][P.q];
+        }
+        sync<WG>();
+    }
+    // Coarsest grid: the direct solve, and E = u - v for the level above.
+    static __device__ __forceinline__ void solve(const Op& top, const CoarseArgs<T>& A, Lds& S,
+                                                 const Lev& L, int bc, bool compl_f) {
+        const Op o = opl(top, L.l);
+        const int t = threadIdx.x;
+        if (compl_f) {
+            const Pos P = pos(L, bc);
+            if (P.on) {
+                Own O;
+                load_own(S, P, O);
+                complete(o, S, P, O);
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) S.f[c][f][P.q] = O.f[c][f];
+            }
+            sync<false>();
+        }
+        // colour and LDS entry of grid cell a = j m + i
+        auto at = [&](int a, int& col) {
+            const int i = a & (L.m - 1), j = a >> L.lm;
+            col = (i ^ j) & 1;
+            return L.off + 2 * ((j >> 1) * (L.m >> 1) + (i >> 1)) + (j & 1);
+        };
+        int col;
+        if constexpr (NF == 3) {
+            // the host launches the instantiation whose NC equals the coarsest cell count
+            if (t == 0 && L.m * L.n == NC) {
+                T u[3][NC], f[3][NC], xk[NC], pb[NC], pw[NC];
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    const int q = at(a, col);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) { u[k][a] = S.u[col][k][q]; f[k][a] = S.f[col][k][q]; }
+                    xk[a] = Op::XK ? S.xk[col][q] : T(0);
+                    pb[a] = Op::PB ? S.pb[col][q] : T(0);
+                    pw[a] = Op::PW ? S.pw[col][q] : T(0);
+                }
+                const bool cosines = NEU && NC == 8 &&
+                                     (bc & (L.m == 4 ? BC_NEUMANN_X : BC_NEUMANN_Y));
+                if (NEU && NC == 8 && cosines)
+                    coarse_solve_mpfc<Op, NC>(o, u, f, xk, pb, pw, L.m, L.lm, L.n, bc,
+                                              A.newton_maxit, A.newton_tol);
+                else
+                    coarse_solve_walsh<Op, NC>(o, u, f, xk, pb, pw, L.m, L.n, NEU ? bc : 0,
+                                               A.newton_maxit, A.newton_tol);
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    const int q = at(a, col);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        S.E[k][a] = u[k][a] - S.u[col][k][q];
+                        S.u[col][k][q] = u[k][a];
+                    }
+                }
+            }
+        } else {
+            // Poisson: w = G f + mean(v) (the mean of w is free; the correction
+            // stays mean-free); u holds v
+            const int nc = L.m * L.n;
+            if (t < nc) {
+                T mv = T(0), w = T(0);
+                for (int k = 0; k < nc; ++k) {
+                    const int q = at(k, col);
+                    mv += S.u[col][0][q];
+                    w += (T)A.G[t * nc + k] * S.f[col][0][q];
+                }
+                w += mv / T(nc);
+                const int q = at(t, col);
+                S.E[0][t] = w - S.u[col][0][q];
+                S.u[col][0][q] = w;
+            }
+        }
+        sync<false>();
+    }
+    // Every level from L down to the coarsest and back, in one wave.
+    static __device__ __forceinline__ void cycle_wave(const Op& top, const CoarseArgs<T>& A, Lds& S,
+                                                      Lev L, int bc) {
+        const int l0 = L.l;
+#pragma unroll 1
+        for (; !L.coarsest(); L = L.coarser())
+            down<false>(top, S, L, bc, A.nsw1, L.l > 0 || A.complete_top);
+        solve(top, A, S, L, bc, L.l > 0 || A.complete_top);
+#pragma unroll 1
+        while (L.l > l0) {
+            L = L.finer();
+            up<false>(top, S, L, bc, A.nsw2);
+        }
+    }
+
+    static __device__ __forceinline__ void run(const Op& top, const CoarseArgs<T>& A, Lds& S,
+                                               const CycleState* stop) {
+        Lev L = {A.geo.m[0], A.geo.n[0], A.geo.lm[0], 0, 0};
+        const int bc = A.geo.bc;
+        const Pos P = pos(L, bc);
+        const size_t g0 = ((size_t)(2 * P.by + P.dy) << L.lm) + 2 * P.bx;  // the west cell
+        const bool done = stopped(stop);  // looked at behind the loads, in flight with them
+        if (P.on) {
+            constexpr int NV = 2 * NF + (Op::XK ? 1 : 0) + (Op::PB ? 1 : 0) + (Op::PW ? 1 : 0);
+            const T* src[NV];
+            T *red[NV], *black[NV];
+            int k = 0;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                src[k] = A.u[f]; red[k] = S.u[0][f]; black[k++] = S.u[1][f];
+                src[k] = A.rr[f]; red[k] = S.f[0][f]; black[k++] = S.f[1][f];
+            }
+            if constexpr (Op::XK) { src[k] = A.xk; red[k] = S.xk[0]; black[k++] = S.xk[1]; }
+            if constexpr (Op::PB) { src[k] = A.pb; red[k] = S.pb[0]; black[k++] = S.pb[1]; }
+            if constexpr (Op::PW) { src[k] = A.pin; red[k] = S.pw[0]; black[k++] = S.pw[1]; }
+            T2 v[NV];
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[i] = *(const T2*)(src[i] + g0);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                red[i][P.q] = P.dy ? v[i].y : v[i].x;
+                black[i][P.q] = P.dy ? v[i].x : v[i].y;
+            }
+        }
+        if (done) return;
+        __syncthreads();
+#pragma unroll 1
+        for (; !L.one_wave(); L = L.coarser())
+            down<true>(top, S, L, bc, A.nsw1, L.l > 0 || A.complete_top);
+        if (threadIdx.x < 64) cycle_wave(top, A, S, L, bc);
+        __syncthreads();
+#pragma unroll 1
+        while (L.l > 0) {
+            L = L.finer();
+            up<true>(top, S, L, bc, A.nsw2);
+        }
+        if (P.on) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const T r = S.u[0][f][P.q], b = S.u[1][f][P.q];
+                *(T2*)(A.u[f] + g0) = P.dy ? T2{b, r} : T2{r, b};
+            }
+        }
+    }
+};
+
+template <class Op, int NC, bool NEU>
+__global__ void __launch_bounds__(CP_THREADS) k_coarse_persistent(
+    Op op_top, CoarseArgs<typename Op::real> A, const CycleState* stop) {
+    __shared__ typename CoarseWork<Op, NC, NEU>::Lds S;
+    CoarseWork<Op, NC, NEU>::run(op_top, A, S, stop);
 }
 
 // Batched: workgroup b runs the coarse levels of grid b.
@@ -1012,218 +1583,12 @@ struct BatchCoarse {
     const CycleState* stop;
 };
 
-template <class Op, int NTP, int NC, bool NEU>
-__global__ void __launch_bounds__(NTP) k_coarse_persistent_batched(
+template <class Op, int NC, bool NEU>
+__global__ void __launch_bounds__(CP_THREADS) k_coarse_persistent_batched(
     const BatchCoarse<Op>* __restrict__ args) {
+    __shared__ typename CoarseWork<Op, NC, NEU>::Lds S;
     const BatchCoarse<Op>& B = args[blockIdx.x];
-    coarse_body<Op, NTP, NC, NEU>(B.op, B.A, B.stop);
-}
-
-template <class Op, int NTP, int NC, bool NEU>
-__device__ __forceinline__ void coarse_body(const Op& op_top,
-                                            const CoarseArgs<typename Op::real>& A,
-                                            const CycleState* stop) {
-    using T = typename Op::real;
-    constexpr int NF = Op::NF;
-    __shared__ T Su[NF][CP_TOTAL];
-    __shared__ T Sf[NF][CP_TOTAL];
-    __shared__ T Sv[NF][CP_TOTAL];
-    __shared__ T Sxk[Op::XK ? CP_TOTAL : 1];
-    __shared__ T Spb[Op::PB ? CP_TOTAL : 1];
-    __shared__ T Spw[Op::PW ? CP_TOTAL : 1];
-    if (stopped(stop)) return;
-    const int t = threadIdx.x;
-    const CoarseGeom& G = A.geo;
-    const int N0 = G.m[0] * G.n[0];
-    // load the top level: every stride's loads are issued before the LDS
-    // stores (indices clamped to the last cell, which is then stored twice
-    // with the same value)
-    {
-        constexpr int NQ = (CP_CELLS + NTP - 1) / NTP;
-        constexpr int NV = 2 * NF + (Op::XK ? 1 : 0) + (Op::PB ? 1 : 0) + (Op::PW ? 1 : 0);
-        T v[NQ][NV];
-        int qs[NQ];
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const int q = min(t + j * NTP, N0 - 1);
-            qs[j] = q;
-            int k = 0;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                v[j][k++] = A.u[f][q];
-                v[j][k++] = A.rr[f][q];
-            }
-            if constexpr (Op::XK) v[j][k++] = A.xk[q];
-            if constexpr (Op::PB) v[j][k++] = A.pb[q];
-            if constexpr (Op::PW) v[j][k++] = A.pin[q];
-        }
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const int q = qs[j];
-            int k = 0;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                Su[f][q] = v[j][k++];
-                Sf[f][q] = v[j][k++];
-            }
-            if constexpr (Op::XK) Sxk[q] = v[j][k++];
-            if constexpr (Op::PB) Spb[q] = v[j][k++];
-            if constexpr (Op::PW) Spw[q] = v[j][k++];
-        }
-    }
-    __syncthreads();
-    // coefficient pyramids (2x2 averages)
-    if constexpr (Op::XK || Op::PB || Op::PW) {
-        for (int l = 1; l < G.nlev; ++l) {
-            const int mf = G.m[l - 1], lmc = G.lm[l], mcv = G.m[l];
-            for (int q = t; q < mcv * G.n[l]; q += NTP) {
-                const int I = q & (mcv - 1), J = q >> lmc;
-                const int a = G.off[l - 1] + 2 * J * mf + 2 * I;
-                if constexpr (Op::XK)
-                    Sxk[G.off[l] + q] = T(0.25) * ((Sxk[a] + Sxk[a + 1]) + (Sxk[a + mf] + Sxk[a + mf + 1]));
-                if constexpr (Op::PB)
-                    Spb[G.off[l] + q] = T(0.25) * ((Spb[a] + Spb[a + 1]) + (Spb[a + mf] + Spb[a + mf + 1]));
-                if constexpr (Op::PW)
-                    Spw[G.off[l] + q] = T(0.25) * ((Spw[a] + Spw[a + 1]) + (Spw[a + mf] + Spw[a + mf + 1]));
-            }
-            __syncthreads();
-        }
-    }
-    // level l has spacing 2^l h_top: scale 1/h^2 (and h^2) by exact powers of two
-    auto opl = [&](int l) {
-        Op o = op_top;
-        if constexpr (NF == 3) o.op.ih2 = ldexp(op_top.op.ih2, -2 * l);
-        else { o.ih2 = ldexp(op_top.ih2, -2 * l); o.h2 = ldexp(op_top.h2, 2 * l); }
-        return o;
-    };
-    // sum of the four neighbours (ghost rule of each axis) of cell (i, j) of
-    // an m x n level
-    const bool nbx = G.bc & BC_NEUMANN_X, nby = G.bc & BC_NEUMANN_Y;
-    auto nsum_l = [&](const T* a, int i, int j, int m, int lm, int n) {
-        const int r = j << lm;
-        return (a[bidx<NEU>(i + 1, m, nbx) + r] + a[bidx<NEU>(i - 1, m, nbx) + r]) +
-               (a[i + (bidx<NEU>(j + 1, n, nby) << lm)] + a[i + (bidx<NEU>(j - 1, n, nby) << lm)]);
-    };
-    auto complete_rhs = [&](int l) {
-        const Op o = opl(l);
-        const int m = G.m[l], lm = G.lm[l], n = G.n[l], off = G.off[l];
-        for (int q = t; q < m * n; q += NTP) {
-            const int i = q & (m - 1), j = q >> lm;
-            T u[NF], ns[NF], N[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) { u[f] = Su[f][off + q]; ns[f] = nsum_l(&Su[f][off], i, j, m, lm, n); }
-            o.apply(u, ns, Op::XK ? Sxk[off + q] : T(0), Op::PB ? Spb[off + q] : T(0),
-                    Op::PW ? Spw[off + q] : T(0), N);
-#pragma unroll
-            for (int f = 0; f < NF; ++f) Sf[f][off + q] += N[f];
-        }
-        __syncthreads();
-    };
-    auto sweeps = [&](int l, int nsw) {
-        const Op o = opl(l);
-        const int m = G.m[l], lm = G.lm[l], n = G.n[l], off = G.off[l];
-        for (int p = 0; p < nsw; ++p) {
-            const int colour = p & 1;
-            for (int q2 = t; q2 < (m * n) >> 1; q2 += NTP) {
-                const int j = q2 >> (lm - 1), k = q2 & ((m >> 1) - 1);
-                const int i = 2 * k + ((j + colour) & 1);
-                const int q = (j << lm) + i;
-                T u[NF], ns[NF], fv[NF];
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    u[f] = Su[f][off + q];
-                    ns[f] = nsum_l(&Su[f][off], i, j, m, lm, n);
-                    fv[f] = Sf[f][off + q];
-                }
-                o.relax(u, ns, fv, Op::XK ? Sxk[off + q] : T(0), Op::PB ? Spb[off + q] : T(0),
-                        Op::PW ? Spw[off + q] : T(0));
-#pragma unroll
-                for (int f = 0; f < NF; ++f) Su[f][off + q] = u[f];
-            }
-            __syncthreads();
-        }
-    };
-    const int L = G.nlev;
-    // down
-    if (A.complete_top) complete_rhs(0);
-    for (int l = 0; l < L - 1; ++l) {
-        sweeps(l, A.nsw1);
-        const Op o = opl(l);
-        const int m = G.m[l], lm = G.lm[l], n = G.n[l], off = G.off[l];
-        const int mc = G.m[l + 1], lmc = G.lm[l + 1], nc = G.n[l + 1], offc = G.off[l + 1];
-        for (int Q = t; Q < mc * nc; Q += NTP) {
-            const int I = Q & (mc - 1), J = Q >> lmc;
-            T su[NF], sr[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) { su[f] = T(0); sr[f] = T(0); }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int i = 2 * I + (c & 1), j = 2 * J + (c >> 1);
-                const int q = (j << lm) + i;
-                T u[NF], ns[NF], N[NF];
-#pragma unroll
-                for (int f = 0; f < NF; ++f) { u[f] = Su[f][off + q]; ns[f] = nsum_l(&Su[f][off], i, j, m, lm, n); }
-                o.apply(u, ns, Op::XK ? Sxk[off + q] : T(0), Op::PB ? Spb[off + q] : T(0),
-                    Op::PW ? Spw[off + q] : T(0), N);
-#pragma unroll
-                for (int f = 0; f < NF; ++f) { su[f] += u[f]; sr[f] += Sf[f][off + q] - N[f]; }
-            }
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                Su[f][offc + Q] = T(0.25) * su[f];
-                Sv[f][offc + Q] = T(0.25) * su[f];
-                Sf[f][offc + Q] = T(0.25) * sr[f];
-            }
-        }
-        __syncthreads();
-        complete_rhs(l + 1);
-    }
-    // coarsest
-    {
-        const int l = L - 1, off = G.off[l], nc = G.m[l] * G.n[l];
-        if constexpr (NF == 3) {
-            // the host launches the instantiation whose NC equals the coarsest cell count
-            if (t == 0 && nc == NC) {
-                const Op o = opl(l);
-                T fbuf[3 * NC];
-#pragma unroll
-                for (int q = 0; q < NC; ++q) {
-                    fbuf[q] = Sf[0][off + q];
-                    fbuf[NC + q] = Sf[1][off + q];
-                    fbuf[2 * NC + q] = Sf[2][off + q];
-                }
-                T* xkp = Op::XK ? &Sxk[off] : nullptr;
-                T* pbp = Op::PB ? &Spb[off] : nullptr;
-                T* pwp = Op::PW ? &Spw[off] : nullptr;
-                coarse_solve_mpfc<Op, NC>(o, &Su[0][off], &Su[1][off], &Su[2][off], fbuf, xkp, pbp, pwp,
-                                          G.m[l], G.lm[l], G.n[l], NEU ? G.bc : 0,
-                                          A.newton_maxit, A.newton_tol);
-            }
-        } else {
-            coarse_solve_poisson<T>(&Su[0][off], &Sf[0][off], &Sv[0][off], A.G, nc);
-        }
-        __syncthreads();
-    }
-    // up
-    for (int l = L - 2; l >= 0; --l) {
-        const int m = G.m[l], lm = G.lm[l], n = G.n[l], off = G.off[l];
-        const int mc = G.m[l + 1], nc = G.n[l + 1], offc = G.off[l + 1];
-        for (int q = t; q < m * n; q += NTP) {
-            const int i = q & (m - 1), j = q >> lm, I = i >> 1, J = j >> 1;
-            const int Is = bidx<NEU>((i & 1) ? I + 1 : I - 1, mc, nbx);
-            const int Js = bidx<NEU>((j & 1) ? J + 1 : J - 1, nc, nby);
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-                Su[f][off + q] += bilinear<T>(&Su[f][offc], &Sv[f][offc], I, J, Is, Js, mc);
-        }
-        __syncthreads();
-        sweeps(l, A.nsw2);
-    }
-    // top level back to global memory
-    for (int q = t; q < N0; q += NTP) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) A.u[f][q] = Su[f][q];
-    }
+    CoarseWork<Op, NC, NEU>::run(B.op, B.A, S, B.stop);
 }
 
 // ---------------------------------------------------------------------------
@@ -1289,17 +1654,18 @@ __global__ void __launch_bounds__(CG_THREADS) k_coarsest_sweeps(Op op,
             if constexpr (Op::XK) xkr[c][s] = A.xk[q];
             if constexpr (Op::PB) pbr[c][s] = A.pb[q];
             if constexpr (Op::PW) wr[c][s] = A.pin[q];
-            T u[NF], ns[NF], Nu[NF];
+            T u[1][NF], ns[1][NF], r[1][NF];
+            const T zero[1][NF] = {};
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                u[f] = Su[f][q];
-                ns[f] = nsum(Su[f], i, j);
+                u[0][f] = Su[f][q];
+                ns[0][f] = nsum(Su[f], i, j);
                 fr[c][s][f] = A.rr[f][q];
             }
             if (A.complete_top) {
-                op.apply(u, ns, xkr[c][s], pbr[c][s], wr[c][s], Nu);
+                op.resid(u, ns, zero, {xkr[c][s]}, {pbr[c][s]}, {wr[c][s]}, r);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) fr[c][s][f] += Nu[f];
+                for (int f = 0; f < NF; ++f) fr[c][s][f] -= r[0][f];
             }
         }
     }
@@ -1311,15 +1677,16 @@ __global__ void __launch_bounds__(CG_THREADS) k_coarsest_sweeps(Op op,
             int i = 0, j = 0;
             const int q = cell(c, s, i, j);
             if (q < 0) continue;
-            T u[NF], ns[NF];
+            T u[1][NF], ns[1][NF], f1[1][NF];
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                u[f] = Su[f][q];
-                ns[f] = nsum(Su[f], i, j);
+                u[0][f] = Su[f][q];
+                ns[0][f] = nsum(Su[f], i, j);
+                f1[0][f] = fr[c][s][f];
             }
-            op.relax(u, ns, fr[c][s], xkr[c][s], pbr[c][s], wr[c][s]);
+            op.relax(u, ns, f1, {xkr[c][s]}, {pbr[c][s]}, {wr[c][s]});
 #pragma unroll
-            for (int f = 0; f < NF; ++f) Su[f][q] = u[f];
+            for (int f = 0; f < NF; ++f) Su[f][q] = u[0][f];
         }
     };
     for (int p = 0; p < A.nsw2; ++p) {
@@ -1371,11 +1738,12 @@ __global__ void __launch_bounds__(CG_THREADS) k_coarsest_poisson(PoissonOp<T> op
         const int js = j > 0 ? j - 1 : (nby ? 0 : n - 1);
         T f = A.rr[0][q];
         if (A.complete_top) {
-            const T u[1] = {S0[q]};
-            const T ns[1] = {(S0[ie + j * m] + S0[iw + j * m]) + (S0[i + jn * m] + S0[i + js * m])};
-            T Nu[1];
-            op.apply(u, ns, T(0), T(0), T(0), Nu);
-            f += Nu[0];
+            const T u[1][1] = {{S0[q]}}, zero[1][1] = {};
+            const T ns[1][1] = {
+                {(S0[ie + j * m] + S0[iw + j * m]) + (S0[i + jn * m] + S0[i + js * m])}};
+            T r[1][1];
+            op.resid(u, ns, zero, {T(0)}, {T(0)}, {T(0)}, r);
+            f -= r[0][0];
         }
         S1[q] = f;
     }
