@@ -247,13 +247,23 @@ __global__ void __launch_bounds__(256) k_guess(Grid g, int mode, const StepIO* _
     phi[q] = guess_value(mode, io->phi_n[q], io->phi_nm1[q]);
 }
 
+// kappa = S3 + e Lap phi of one cell from its value and neighbour sum, with the
+// rounding fixed by an explicit fma: S3 is a product in some callers and a
+// loaded value in others, and either sum of two products may be contracted
+// (the learned guess's choice between two candidates, completed by different
+// kernels, has to see the same bits for the same guess).
+__device__ __forceinline__ double kappa_value(double s3, double e, double ns, double x,
+                                              double ih2) {
+    return fma(e * (ns - 4.0 * x), ih2, s3);
+}
+
 // Consistent completion of the guess: kappa = S3 + e Lap phi (so N^(3) = S^(3)).
 __device__ __forceinline__ void complete_kappa_cell(const Grid& g, double ih2, double e,
                                                     const double* __restrict__ phi,
                                                     const double* __restrict__ S3, double* ka,
                                                     int i, int j) {
     const size_t q = at(i, j, g);
-    ka[q] = S3[q] + e * (nsum(phi, i, j, g) - 4.0 * phi[q]) * ih2;
+    ka[q] = kappa_value(S3[q], e, nsum(phi, i, j, g), phi[q], ih2);
 }
 
 __global__ void k_set_io(StepIO* io, const double* phi_n, const double* phi_nm1, double* psi,
@@ -300,7 +310,7 @@ __global__ void __launch_bounds__(256) k_setup(Grid g, double ih2, double d, dou
     const int ip = wrapx(i + 1, g), im = wrapx(i - 1, g);
     const int jp = wrapy(j + 1, g), jm = wrapy(j - 1, g);
     const double ns = (gv(at(ip, j, g)) + gv(at(im, j, g))) + (gv(at(i, jp, g)) + gv(at(i, jm, g)));
-    ka[q] = S3[q] + e * (ns - 4.0 * x) * ih2;
+    ka[q] = kappa_value(S3[q], e, ns, x, ih2);
 }
 
 // The step's whole set-up on a 32 x 8 tile per workgroup: the source S, the
@@ -364,7 +374,7 @@ __global__ void __launch_bounds__(SU_X * SU_Y) k_setup_tile(
         const int ly = 1 + c / (LX - 2), lx = 1 + c % (LX - 2);
         const double lk = (ns(PK, lx, ly) - 4.0 * PK[ly][lx]) * ih2;
         const double s3 = SCHEME == 1 ? 0.0 : 0.5 * lk;
-        K[ly][lx] = s3 + op.e * (ns(G0, lx, ly) - 4.0 * G0[ly][lx]) * ih2;
+        K[ly][lx] = kappa_value(s3, op.e, ns(G0, lx, ly), G0[ly][lx], ih2);
     }
     __syncthreads();
     // S2 of a cell (source_cell's arithmetic)

@@ -161,6 +161,19 @@ def crystal_run(stepper, steps, seed=5, N_=64):
 PARAMS = dict(eps=0.025, beta=0.9, M=1.0, h=math.pi / 4, dt=0.05, scheme=2)
 
 
+@pytest.mark.parametrize("N_", [64, 128])
+def test_zero_network_always_falls_back(N_):
+    """The two candidates of a zero network are the same guess, completed by
+    different kernels: their residual sums must be equal bits in every step, so
+    that each one falls back."""
+    st = api.Stepper(N_, N_, api.Params(**PARAMS), energy=0, guess=L.MPFC_GUESS_CNN)
+    st.load_cnn(N.init_blob(7, zero_last=True))
+    for seed in (1, 2):
+        crystal_run(st, 12, seed=seed, N_=N_)
+    assert st.cnn_counts() == (0, 24)
+    st.close()
+
+
 def test_fallback_is_exact():
     """A network whose output is zero reproduces extrapolation and counts
     every step as a fallback; a NaN network too; the states are bitwise those
