@@ -328,8 +328,8 @@ __device__ __forceinline__ double parts_sum(const double* __restrict__ part, int
 // cycle limit.  No atomics and no device-wide fences are involved, and the
 // norm is deterministic.  Bound by launch and memory latency, so the partial
 // sums and the cycle state are requested together, before the stop flag is
-// looked at.  Per launch: 4.4 us with 1024 partial sums (4.5 with one dependent
-// load chain per thread), 5.4 us with 16384, the defect pass at 2048^2 (20.5).
+// looked at: with 1024 threads and 16384 sums (the defect pass at 2048^2) 5.4 us
+// a launch where one dependent load chain per thread took 20.5.
 template <int NT>
 __device__ __forceinline__ void norm_finalize_body(const double* __restrict__ part, int nparts,
                                                    CycleState* st, double* hist, double h2,
@@ -353,6 +353,18 @@ __device__ __forceinline__ void norm_finalize_body(const double* __restrict__ pa
     }
 }
 
+// A norm whose partial sums are written but whose stopping test has not run:
+// the finest down launch behind it takes the test along in a workgroup of its
+// own (k_tile), nparts = 0: none.
+struct PendingNorm {
+    const double* part;
+    int nparts;
+    CycleState* st;
+    double* hist;
+    double h2, tol, diverge;
+    int max_norms;
+};
+
 template <int NT>
 __global__ void __launch_bounds__(NT) k_norm_finalize(const double* __restrict__ part, int nparts,
                                                       CycleState* st, double* hist, double h2,
@@ -360,17 +372,13 @@ __global__ void __launch_bounds__(NT) k_norm_finalize(const double* __restrict__
     norm_finalize_body<NT>(part, nparts, st, hist, h2, tol, max_norms, diverge);
 }
 
-// One round of eight loads per thread covers 2048 partial sums with 256
-// threads; more of them take 1024 threads.
-inline void launch_norm_finalize(const double* part, int nparts, CycleState* st, double* hist,
-                                 double h2, double tol, int max_norms, double diverge,
-                                 hipStream_t s) {
-    if (nparts <= 2048)
-        hipLaunchKernelGGL((k_norm_finalize<256>), dim3(1), dim3(256), 0, s, part, nparts, st, hist,
-                           h2, tol, max_norms, diverge);
-    else
-        hipLaunchKernelGGL((k_norm_finalize<1024>), dim3(1), dim3(1024), 0, s, part, nparts, st,
-                           hist, h2, tol, max_norms, diverge);
+// Threads of every block that runs the test, alone or beside a launch's tiles:
+// the order of the sum, and with it the norm's last bit, must not depend on
+// which of the two it was.
+constexpr int kNormThreads = 512;
+inline void launch_norm_finalize(const PendingNorm& P, hipStream_t s) {
+    hipLaunchKernelGGL((k_norm_finalize<kNormThreads>), dim3(1), dim3(kNormThreads), 0, s, P.part,
+                       P.nparts, P.st, P.hist, P.h2, P.tol, P.max_norms, P.diverge);
 }
 
 }  // namespace mpfc

@@ -19,11 +19,12 @@ constexpr TileShape kShapes[] = {{64, 32, 6},  {32, 32, 6},  {32, 16, 6}, {16, 1
 constexpr int kNumShapes = 7;
 constexpr bool gen_shape(int k) { return k == 0 || k == 2; }
 
-// One tiled level: grid (m / tx, n / ty) workgroups of tile shape `shape`;
+// One tiled level: (m / tx) (n / ty) workgroups of tile shape `shape`;
 // the periodic, Neumann or general-index instantiation by A.g.
+// `pend` (down launches): a norm whose stopping test rides along.
 template <class Op, bool UP>
 void launch_tile(const Op& op, const TileArgs<typename Op::real>& A, int shape,
-                 const CycleState* stop, hipStream_t s);
+                 const CycleState* stop, hipStream_t s, const PendingNorm& pend = PendingNorm{});
 
 // Every level from the first untiled one down, one workgroup; `four`: the
 // coarsest grid has 4 cells (2 x 2), else 8 (2 x 4 or 4 x 2).

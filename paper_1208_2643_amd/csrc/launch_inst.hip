@@ -15,39 +15,40 @@ bool general_index(const Grid& g) { return g.lm < 0 || g.ln < 0; }
 #endif
 
 template <class Op, bool UP, bool NEU, int K>
-void tile_k(const Op& op, const TileArgs<typename Op::real>& A, const CycleState* stop,
-            hipStream_t s, bool gen) {
+void tile_k(const Op& op, TileArgs<typename Op::real> A, const CycleState* stop, hipStream_t s,
+            bool gen, const PendingNorm& P) {
     constexpr TileShape S = kShapes[K];
-    const dim3 grid(A.g.m / A.tx, A.g.n / A.ty), blk(kTileThreads);
+    A.ntx = A.g.m / A.tx;
+    const dim3 grid(A.ntx * (A.g.n / A.ty) + (P.nparts ? 1 : 0)), blk(kTileThreads);
     if constexpr (std::is_same<typename Op::real, double>::value && gen_shape(K)) {
         if (gen) {
             hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU, true>), grid, blk, 0, s, op,
-                               A, stop);
+                               A, stop, P);
             return;
         }
     }
     // the shape's own tile and halo (the larger levels): compile-time extents
     if (MPFC_TILE_EXACT && A.tx == S.tx && A.ty == S.ty && A.H == S.hmax) {
         hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU, false, true>), grid, blk, 0, s,
-                           op, A, stop);
+                           op, A, stop, P);
         return;
     }
-    hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU>), grid, blk, 0, s, op, A, stop);
+    hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU>), grid, blk, 0, s, op, A, stop, P);
 }
 
 template <class Op, bool UP, bool NEU>
 void tile_bc(const Op& op, const TileArgs<typename Op::real>& A, int shape,
-             const CycleState* stop, hipStream_t s) {
+             const CycleState* stop, hipStream_t s, const PendingNorm& P) {
     const bool gen = general_index(A.g);
     if (gen) shape = shape == 2 ? 2 : 0;  // general-index kernels: shapes 0 and 2
     switch (shape) {
-        case 0: tile_k<Op, UP, NEU, 0>(op, A, stop, s, gen); break;
-        case 1: tile_k<Op, UP, NEU, 1>(op, A, stop, s, gen); break;
-        case 2: tile_k<Op, UP, NEU, 2>(op, A, stop, s, gen); break;
-        case 3: tile_k<Op, UP, NEU, 3>(op, A, stop, s, gen); break;
-        case 4: tile_k<Op, UP, NEU, 4>(op, A, stop, s, gen); break;
-        case 5: tile_k<Op, UP, NEU, 5>(op, A, stop, s, gen); break;
-        default: tile_k<Op, UP, NEU, 6>(op, A, stop, s, gen); break;
+        case 0: tile_k<Op, UP, NEU, 0>(op, A, stop, s, gen, P); break;
+        case 1: tile_k<Op, UP, NEU, 1>(op, A, stop, s, gen, P); break;
+        case 2: tile_k<Op, UP, NEU, 2>(op, A, stop, s, gen, P); break;
+        case 3: tile_k<Op, UP, NEU, 3>(op, A, stop, s, gen, P); break;
+        case 4: tile_k<Op, UP, NEU, 4>(op, A, stop, s, gen, P); break;
+        case 5: tile_k<Op, UP, NEU, 5>(op, A, stop, s, gen, P); break;
+        default: tile_k<Op, UP, NEU, 6>(op, A, stop, s, gen, P); break;
     }
 }
 
@@ -77,9 +78,9 @@ void tile_batched_bc(int shape, const BatchTile<Op>* args, const BatchItem* item
 // Periodic grids run the instantiation without the Neumann ghost handling.
 template <class Op, bool UP>
 void launch_tile(const Op& op, const TileArgs<typename Op::real>& A, int shape,
-                 const CycleState* stop, hipStream_t s) {
-    if (A.g.bc) tile_bc<Op, UP, true>(op, A, shape, stop, s);
-    else tile_bc<Op, UP, false>(op, A, shape, stop, s);
+                 const CycleState* stop, hipStream_t s, const PendingNorm& pend) {
+    if (A.g.bc) tile_bc<Op, UP, true>(op, A, shape, stop, s, pend);
+    else tile_bc<Op, UP, false>(op, A, shape, stop, s, pend);
 }
 
 template <class Op>
@@ -120,9 +121,10 @@ void launch_coarse_batched(bool neu, int nsim, const BatchCoarse<Op>* args, hipS
 
 #define MPFC_INST_TILE(OP)                                                                   \
     template void launch_tile<OP, false>(const OP&, const TileArgs<OP::real>&, int,          \
-                                         const CycleState*, hipStream_t);                    \
+                                         const CycleState*, hipStream_t,                     \
+                                         const PendingNorm&);                                \
     template void launch_tile<OP, true>(const OP&, const TileArgs<OP::real>&, int,           \
-                                        const CycleState*, hipStream_t);                     \
+                                        const CycleState*, hipStream_t, const PendingNorm&); \
     template void launch_coarse<OP>(const OP&, const CoarseArgs<OP::real>&, bool,            \
                                     const CycleState*, hipStream_t);
 #define MPFC_INST_GEN(OP)                                                                    \

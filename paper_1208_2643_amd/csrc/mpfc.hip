@@ -7,10 +7,10 @@
 // side, direct solve on the coarsest grid, bilinear prolongation of the
 // coarse-grid correction.  Levels above 32x32 cells take two fused tile
 // launches per cycle (tiles.hpp); all smaller levels take one persistent
-// launch.  One V-cycle is captured once into a hipGraph and replayed.  The
-// stopping test runs on the device (the finest up-launch records the
-// residual norm and raises a stop flag that every later kernel checks), so
-// the host only reads back a small status record per cycle.  Afterwards psi
+// launch.  Runs of V-cycles are captured into hipGraphs and replayed.  The
+// stopping test runs on the device (on the finest up launch's sums, beside the
+// next cycle's first launch; it raises a stop flag that every later kernel
+// checks), so the host only reads back a small status record per step.  Afterwards psi
 // is updated (eqs. discrete_1_b / discrete_2_b) and the energies of Sec. 3
 // are computed, the -1 norm with the same multigrid on the Poisson problem.
 #include <hip/hip_runtime.h>
@@ -152,7 +152,7 @@ struct mpfc_ctx {
     double* rb = nullptr;
     size_t rb_count = 0;            // doubles of one full readback
     StepIO* io = nullptr;           // the caller's arrays of the current step
-    // captured graphs (set-up, runs of cycles, Poisson cycle, wrap-up)
+    // captured graphs (runs of cycles, Poisson cycle, wrap-ups with Poisson cycles)
     bool use_graph = true;
     std::vector<std::pair<int, hipGraphExec_t>> graphs;
     hipStream_t cap_stream = nullptr;  // capture only (the caller's stream may be the null stream)
@@ -447,12 +447,29 @@ bool coarsest_is_4(const mpfc_ctx* C) {
     return cl.m * cl.n == 4;
 }
 
-// One FAS V-cycle of the MPFC system on all levels.  With `only` >= 0 just
+// The stopping test of the norm whose `nparts` partial sums are in C->part.
+PendingNorm pending_norm(const mpfc_ctx* C, int nparts) {
+    const Level& F0 = C->L[0];
+    return PendingNorm{C->part, nparts, C->st, C->hist, F0.h * F0.h, C->o.tol, C->o.diverge,
+                       C->o.max_cycles + 1};
+}
+
+// Whether a norm's stopping test may be left to the next cycle's finest down
+// launch: there is one, and no host look at the state comes in between (the
+// live timing waits for every cycle).
+bool may_pend(const mpfc_ctx* C) { return C->Lp > 0 && !C->prof; }
+
+// One FAS V-cycle of the MPFC system on all levels.  `pend`: the previous
+// norm's stopping test, run by the finest down launch; `close`: launch this
+// cycle's own test (else it is left to the next cycle).  Returns the number
+// of this cycle's partial sums.  With `only` >= 0 just
 // the down (only_up = 0) or up (1) launch of that level is issued, without
 // the stop flag or the norm (used by the tile autotuner).
 template <class Op>
-void vcycle_mpfc_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) {
+int vcycle_mpfc_t(mpfc_ctx* C, hipStream_t s, int pend = 0, bool close = true, int only = -1,
+                  int only_up = 0) {
     const int nl = (int)C->L.size(), Lp = C->Lp;
+    int nparts = 0;
     const CycleState* stop = only >= 0 ? nullptr : C->st;
     for (int l = 0; l < Lp; ++l) {
         if (only >= 0 && (l != only || only_up)) continue;
@@ -461,7 +478,8 @@ void vcycle_mpfc_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) {
         const int shape = level_shape(A, SH_DN, T.H);
         tile_dims(A, shape, T.tx, T.ty);
         if (l == 0 && C->prof) prof_mark(C, 0, s);
-        launch_tile<Op, false>(make_op<Op>(C, A), T, shape, stop, s);
+        launch_tile<Op, false>(make_op<Op>(C, A), T, shape, stop, s,
+                               pending_norm(C, l == 0 ? pend : 0));
         if (l == 0 && C->prof) prof_mark(C, 1, s);
     }
     if (Lp < nl && only < 0) {
@@ -484,18 +502,16 @@ void vcycle_mpfc_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) {
         launch_tile<Op, true>(make_op<Op>(C, A), T, shape, stop, s);
         if (l == 0 && C->prof) prof_mark(C, 3, s);
         if (T.norm) {
-            const int nb = (A.m / T.tx) * (A.n / T.ty);
-            launch_norm_finalize(C->part, nb, C->st, C->hist, A.h * A.h, C->o.tol,
-                                 C->o.max_cycles + 1, C->o.diverge, s);
+            nparts = (A.m / T.tx) * (A.n / T.ty);
+            if (close) launch_norm_finalize(pending_norm(C, nparts), s);
         }
     }
+    return nparts;
 }
 
 void resnorm(mpfc_ctx* C, hipStream_t s) {
     const Level& lv = C->L[0];
     const size_t total = (size_t)lv.m * lv.n;
-    const double h2 = lv.h * lv.h;
-    const int max_norms = C->o.max_cycles + 1;
     const unsigned nb = red_blocks(total);
     if (C->p.scheme == 1)
         hipLaunchKernelGGL((k_resnorm<1, NT>), dim3(nb), dim3(NT), 0, s, finest_fields(C),
@@ -503,16 +519,15 @@ void resnorm(mpfc_ctx* C, hipStream_t s) {
     else
         hipLaunchKernelGGL((k_resnorm<2, NT>), dim3(nb), dim3(NT), 0, s, finest_fields(C),
                            level_op(C, lv), lv.g, C->st, C->part, nullptr, nullptr, nullptr);
-    launch_norm_finalize(C->part, (int)nb, C->st, C->hist, h2, C->o.tol, max_norms, C->o.diverge,
-                         s);
+    launch_norm_finalize(pending_norm(C, (int)nb), s);
 }
 
 // ---- mixed precision ---------------------------------------------------------------
 // One FP32 FAS V-cycle on the correction equation N(u + e) - N(u) = r (DEFECT
 // operators: the base phi of every level is a coefficient field).
 template <class Op>
-void vcycle_inner_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0,
-                    bool first = false) {
+void vcycle_inner_t(mpfc_ctx* C, hipStream_t s, int pend = 0, bool first = false, int only = -1,
+                    int only_up = 0) {
     const int nl = (int)C->L.size(), Lp = C->Lp;
     const CycleState* stop = only >= 0 ? nullptr : C->st;
     for (int l = 0; l < Lp; ++l) {
@@ -522,7 +537,8 @@ void vcycle_inner_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0,
         Tg.zero_in = first && l == 0;  // the outer iteration's correction starts at zero
         const int shape = level_shape(A, SH_DN32, Tg.H);
         tile_dims(A, shape, Tg.tx, Tg.ty);
-        launch_tile<Op, false>(make_op32<Op>(C, A), Tg, shape, stop, s);
+        launch_tile<Op, false>(make_op32<Op>(C, A), Tg, shape, stop, s,
+                               pending_norm(C, l == 0 ? pend : 0));
     }
     if (Lp < nl && only < 0) {
         const CoarseArgs<float> A = coarse_args32(C);
@@ -540,8 +556,10 @@ void vcycle_inner_t(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0,
 }
 
 // FP64 defect step on the finest grid: u[to] = u[from] + e (add) or u[from],
-// r = S - N(u[to]) with its norm (stopping test), r and base phi to FP32.
-void defect(mpfc_ctx* C, int from, int add, hipStream_t s) {
+// r = S - N(u[to]) with its norm, r and base phi to FP32.  `close`: launch the
+// norm's stopping test (else it is left to the next outer iteration's first
+// launch).  Returns the number of partial sums.
+int defect(mpfc_ctx* C, int from, int add, bool close, hipStream_t s) {
     const Level& F0 = C->L[0];
     const auto& FF = C->FL[0];
     const size_t total = (size_t)F0.m * F0.n;
@@ -551,7 +569,6 @@ void defect(mpfc_ctx* C, int from, int add, hipStream_t s) {
     F.phik = C->p.scheme == 2 ? C->phik : nullptr;
     F.base = nullptr;
     const int to = from ^ 1;
-    const int max_norms = C->o.max_cycles + 1;
     // one 32 x 8 tile per workgroup (the partial sums hold one value per 256
     // cells), its values and their ring staged in LDS
     auto kern = C->p.scheme == 1 ? k_defect_tile<1> : k_defect_tile<2>;
@@ -560,14 +577,14 @@ void defect(mpfc_ctx* C, int from, int add, hipStream_t s) {
     hipLaunchKernelGGL(kern, grid, dim3(DT_X * DT_Y), 0, s, F, level_op(C, F0), F0.g, C->st,
                        C->part, FF.e[0][0], FF.e[0][1], FF.e[0][2], add, F0.u[to][0], F0.u[to][1],
                        F0.u[to][2], FF.f[0], FF.f[1], FF.f[2], FF.pb);
-    launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h, C->o.tol, max_norms,
-                         C->o.diverge, s);
+    if (close) launch_norm_finalize(pending_norm(C, (int)nb), s);
+    return (int)nb;
 }
 
 // One outer iteration of mixed precision starting from FP64 copy `from`:
 // `ncyc` FP32 V-cycles on the correction (from e = 0), then the FP64 defect
-// step into the other copy.
-void outer_mixed(mpfc_ctx* C, int from, int ncyc, hipStream_t s) {
+// step into the other copy.  `pend`, `close` and the result as in vcycle_mpfc_t.
+int outer_mixed(mpfc_ctx* C, int from, int ncyc, int pend, bool close, hipStream_t s) {
     const auto& FF = C->FL[0];
     const size_t total = (size_t)C->m * C->n;
     // The first inner cycle's finest down launch starts from e = 0 and its down
@@ -579,29 +596,32 @@ void outer_mixed(mpfc_ctx* C, int from, int ncyc, hipStream_t s) {
     const bool nw = C->o.linearization == MPFC_NEWTON;
     for (int k = 0; k < ncyc; ++k) {
         const bool first = k == 0;
+        const int pk = first ? pend : 0;
         if (C->p.scheme == 1) {
-            if (nw) vcycle_inner_t<MpfcOp<float, 1, true, true>>(C, s, -1, 0, first);
-            else vcycle_inner_t<MpfcOp<float, 1, false, true>>(C, s, -1, 0, first);
+            if (nw) vcycle_inner_t<MpfcOp<float, 1, true, true>>(C, s, pk, first);
+            else vcycle_inner_t<MpfcOp<float, 1, false, true>>(C, s, pk, first);
         } else {
-            if (nw) vcycle_inner_t<MpfcOp<float, 2, true, true>>(C, s, -1, 0, first);
-            else vcycle_inner_t<MpfcOp<float, 2, false, true>>(C, s, -1, 0, first);
+            if (nw) vcycle_inner_t<MpfcOp<float, 2, true, true>>(C, s, pk, first);
+            else vcycle_inner_t<MpfcOp<float, 2, false, true>>(C, s, pk, first);
         }
     }
-    defect(C, from, 1, s);
+    return defect(C, from, 1, close, s);
 }
 
-void vcycle_mpfc(mpfc_ctx* C, hipStream_t s) {
+int vcycle_mpfc(mpfc_ctx* C, hipStream_t s, int pend, bool close) {
     const bool nw = C->o.linearization == MPFC_NEWTON;
+    int np = 0;
     if (C->p.scheme == 1) {
-        if (nw) vcycle_mpfc_t<MpfcOp<double, 1, true, false>>(C, s);
-        else vcycle_mpfc_t<MpfcOp<double, 1, false, false>>(C, s);
+        if (nw) np = vcycle_mpfc_t<MpfcOp<double, 1, true, false>>(C, s, pend, close);
+        else np = vcycle_mpfc_t<MpfcOp<double, 1, false, false>>(C, s, pend, close);
     } else if (C->pinned) {  // Sec. 4.6 pinning: scheme 2, Newton (checked when set)
-        vcycle_mpfc_t<MpfcOp<double, 2, true, false, true>>(C, s);
+        np = vcycle_mpfc_t<MpfcOp<double, 2, true, false, true>>(C, s, pend, close);
     } else {
-        if (nw) vcycle_mpfc_t<MpfcOp<double, 2, true, false>>(C, s);
-        else vcycle_mpfc_t<MpfcOp<double, 2, false, false>>(C, s);
+        if (nw) np = vcycle_mpfc_t<MpfcOp<double, 2, true, false>>(C, s, pend, close);
+        else np = vcycle_mpfc_t<MpfcOp<double, 2, false, false>>(C, s, pend, close);
     }
     if (C->Lp == 0) resnorm(C, s);
+    return np;
 }
 
 // Stopping test of the Poisson solve of the -1 norm: ||r|| <= 1e-11 ||b||, or
@@ -679,19 +699,14 @@ void vcycle_poisson(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) 
     }
 }
 
-// What one replayable unit of work is.
-enum CycleKind { CYC_MPFC = 0, CYC_POISSON = 1 };
-
-void enqueue(mpfc_ctx* C, int kind, hipStream_t s) {
-    if (kind == CYC_MPFC) vcycle_mpfc(C, s);
-    else vcycle_poisson(C, s);
-}
-
-// Unit `unit` (0, 1, ...) of a mixed-precision step: an outer iteration from
-// FP64 copy 1 (even units; the set-up writes copy 1) or 0, with the first
-// unit's FP32 cycle count or the later ones'.
-void enqueue_outer(mpfc_ctx* C, int unit, hipStream_t s) {
-    outer_mixed(C, 1 ^ (unit & 1), unit == 0 ? C->inner_cycles : C->inner_next, s);
+// Unit `unit` (0, 1, ...) of a step: a V-cycle, or with mixed precision an
+// outer iteration from FP64 copy 1 (even units; the set-up writes copy 1) or 0,
+// with the first unit's FP32 cycle count or the later ones'.  `pend`, `close` and
+// the result as in vcycle_mpfc_t.
+int enqueue_unit(mpfc_ctx* C, int unit, int pend, bool close, hipStream_t s) {
+    if (C->o.precision != MPFC_MIXED) return vcycle_mpfc(C, s, pend, close);
+    return outer_mixed(C, 1 ^ (unit & 1), unit == 0 ? C->inner_cycles : C->inner_next, pend, close,
+                       s);
 }
 
 // FP32 cycles that `nouter` outer iterations ran.
@@ -699,11 +714,22 @@ int inner_cycles_run(const mpfc_ctx* C, int nouter) {
     return nouter > 0 ? C->inner_cycles + (nouter - 1) * C->inner_next : 0;
 }
 
-// Captured graphs of a context, keyed by what they hold (graph_key): the
-// step's set-up, runs of 1..kMaxRun V-cycles (or mixed-precision outer
-// iterations, by the parity of the first one), one Poisson V-cycle, and the
-// wrap-up variants.
-enum GraphKind { GK_PROLOGUE = 1, GK_CYCLES = 2, GK_MIXED = 3, GK_POISSON = 4, GK_WRAPUP = 5 };
+// Captured graphs of a context, keyed by what they hold (graph_key): runs of
+// 1..kMaxRun V-cycles (or mixed-precision outer iterations, by the parity of
+// the first one) with or without the run's last stopping test, one Poisson
+// V-cycle, and the wrap-ups with Poisson cycles.
+//
+// A replayed graph costs 1.6 us per small kernel where a launch costs the host
+// 2.9 to 4.2 us, but it starts only some 25 us after its launch.  So a step
+// begins with plain launches (the set-up and the first unit: 35 us of work on a
+// 64^2 grid, more on larger ones), its other units are replayed behind them,
+// their start hidden, and the wrap-up's five kernels are plain launches again,
+// queued while the cycles run.  With set-up, cycles and wrap-up each a graph the
+// GPU waited 25 to 30 us before the first two.  A readback is a one-workgroup
+// kernel that writes pinned host memory (a device-to-host copy came 8 us after
+// the last kernel and took 4).  Ten steps on
+// 64^2 (156 cycles): 6.81 -> 6.60 ms; on 512^2 without energies: 4.05 -> 3.93 ms.
+enum GraphKind { GK_CYCLES = 2, GK_MIXED = 3, GK_POISSON = 4, GK_WRAPUP = 5 };
 constexpr int kMaxRun = 8;
 int graph_key(int kind, int a = 0, int b = 0) { return (kind * 16 + a) * 64 + b; }
 
@@ -752,27 +778,74 @@ int run_unit(mpfc_ctx* C, int key, Fn&& fn) {
 
 // One V-cycle of the Poisson problem of the -1 norm.
 int run_poisson_cycle(mpfc_ctx* C) {
-    return run_unit(C, graph_key(GK_POISSON), [&](hipStream_t s) { enqueue(C, CYC_POISSON, s); });
+    return run_unit(C, graph_key(GK_POISSON), [&](hipStream_t s) { vcycle_poisson(C, s); });
+}
+
+// Partial sums of the set-up's norm (step_prologue).
+int setup_parts(const mpfc_ctx* C) {
+    const size_t total = (size_t)C->m * C->n;
+    if (C->o.precision == MPFC_MIXED) return ((C->m + DT_X - 1) / DT_X) * ((C->n + DT_Y - 1) / DT_Y);
+    if (C->o.guess == MPFC_GUESS_CNN) return 1;
+    if (C->m % SU_X == 0 && C->n % SU_Y == 0) return (C->m / SU_X) * (C->n / SU_Y);
+    return (int)red_blocks(total);
+}
+
+// Partial sums of a unit's norm: one per tile of the finest up launch, or of the
+// defect pass.
+int unit_parts(const mpfc_ctx* C) {
+    if (C->o.precision == MPFC_MIXED) return setup_parts(C);
+    const Level& A = C->L[0];
+    int tx, ty;
+    tile_dims(A, level_shape(A, SH_UP, up_args64(C, 0, true).H), tx, ty);
+    return (A.m / tx) * (A.n / ty);
+}
+
+// Launch the work `fn` enqueues.
+template <class Fn>
+int run_direct(mpfc_ctx* C, Fn&& fn) {
+    fn(C->stream);
+    HIP_TRY(hipGetLastError());
+    return MPFC_OK;
 }
 
 // `count` units of the step's solve (V-cycles, or mixed-precision outer
-// iterations, the first being the step's unit number `first`), in runs of at
-// most kMaxRun replayed from one graph each.  A mixed run's graph depends on
-// the parity of its first unit and on whether it holds unit 0.
+// iterations, the first being the step's unit number `first`).  Unit 0 takes the
+// set-up's norm along (may_pend) and is launched directly, and so is a single
+// later unit (the host asks for those one by one); the others are replayed in
+// runs of at most kMaxRun.  Every unit's stopping test is left to the next
+// unit, the last one's is a launch of its own.  A run's graph depends on its
+// length, on whether it ends the units and, with mixed precision, on the parity
+// of its first unit.
 int run_cycles(mpfc_ctx* C, int first, int count) {
     const bool mixed = C->o.precision == MPFC_MIXED;
+    const bool pends = may_pend(C);
+    int pend = first == 0 && pends ? setup_parts(C) : 0;
+    if (first == 0 || count == 1) {
+        const bool close = count == 1 || !pends;
+        int np = 0;
+        int rc = run_direct(C, [&](hipStream_t s) { np = enqueue_unit(C, first, pend, close, s); });
+        if (rc) return rc;
+        pend = close ? 0 : np;
+        ++first;
+        --count;
+    }
     while (count > 0) {
         const int k = count < kMaxRun ? count : kMaxRun;
-        const int f0 = first;
-        const int key = mixed ? graph_key(GK_MIXED, (f0 & 1) + (f0 == 0 ? 2 : 0), k)
-                              : graph_key(GK_CYCLES, 0, k);
+        const bool last = k == count || !pends;
+        const int f0 = first, p0 = pend;
+        const int key = graph_key(mixed ? GK_MIXED : GK_CYCLES,
+                                  (mixed ? f0 & 1 : 0) + (last ? 2 : 0) + (p0 ? 4 : 0), k);
         int rc = run_unit(C, key, [&](hipStream_t s) {
+            int p = p0;
             for (int j = 0; j < k; ++j) {
-                if (mixed) enqueue_outer(C, f0 + j, s);
-                else enqueue(C, CYC_MPFC, s);
+                const bool close = !pends || (last && j == k - 1);
+                const int np = enqueue_unit(C, f0 + j, p, close, s);
+                p = close ? 0 : np;
             }
         });
         if (rc) return rc;
+        // the partial sums of a unit are as many in every unit
+        pend = last ? 0 : unit_parts(C);
         first += k;
         count -= k;
     }
@@ -887,20 +960,20 @@ int autotune(mpfc_ctx* C) {
     // correction cycle and of the Poisson cycle
     auto f64 = [&](hipStream_t s, int lev, int up) {
         if (C->p.scheme == 1) {
-            if (nw) vcycle_mpfc_t<MpfcOp<double, 1, true, false>>(C, s, lev, up);
-            else vcycle_mpfc_t<MpfcOp<double, 1, false, false>>(C, s, lev, up);
+            if (nw) vcycle_mpfc_t<MpfcOp<double, 1, true, false>>(C, s, 0, true, lev, up);
+            else vcycle_mpfc_t<MpfcOp<double, 1, false, false>>(C, s, 0, true, lev, up);
         } else {
-            if (nw) vcycle_mpfc_t<MpfcOp<double, 2, true, false>>(C, s, lev, up);
-            else vcycle_mpfc_t<MpfcOp<double, 2, false, false>>(C, s, lev, up);
+            if (nw) vcycle_mpfc_t<MpfcOp<double, 2, true, false>>(C, s, 0, true, lev, up);
+            else vcycle_mpfc_t<MpfcOp<double, 2, false, false>>(C, s, 0, true, lev, up);
         }
     };
     auto f32 = [&](hipStream_t s, int lev, int up) {
         if (C->p.scheme == 1) {
-            if (nw) vcycle_inner_t<MpfcOp<float, 1, true, true>>(C, s, lev, up);
-            else vcycle_inner_t<MpfcOp<float, 1, false, true>>(C, s, lev, up);
+            if (nw) vcycle_inner_t<MpfcOp<float, 1, true, true>>(C, s, 0, false, lev, up);
+            else vcycle_inner_t<MpfcOp<float, 1, false, true>>(C, s, 0, false, lev, up);
         } else {
-            if (nw) vcycle_inner_t<MpfcOp<float, 2, true, true>>(C, s, lev, up);
-            else vcycle_inner_t<MpfcOp<float, 2, false, true>>(C, s, lev, up);
+            if (nw) vcycle_inner_t<MpfcOp<float, 2, true, true>>(C, s, 0, false, lev, up);
+            else vcycle_inner_t<MpfcOp<float, 2, false, true>>(C, s, 0, false, lev, up);
         }
     };
     // Levels in order, down before up: the kernel that writes a candidate's
@@ -1233,7 +1306,7 @@ void cnn_choose(mpfc_ctx* C, hipStream_t s);
 // the first residual norm (FP64), or for mixed precision phi^k in FP32 and the
 // first FP64 defect (copy 0 -> 1).  The coarse levels' phi^k (scheme 2) is
 // averaged by each cycle's down launches.  The caller's arrays are read from
-// C->io (k_set_io), so the set-up is captured once and replayed.
+// C->io (k_set_io).
 int step_prologue(mpfc_ctx* C, hipStream_t s) {
     Level& F0 = C->L[0];
     const Grid g0 = F0.g;
@@ -1242,6 +1315,7 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
     const double e = C->p.scheme == 1 ? 1.0 : 0.5;
     const double al = C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha;
     const bool learned = C->o.guess == MPFC_GUESS_CNN;
+    const bool close = !may_pend(C);  // the norm's test: here, or with the first cycle
     const int gmode = C->o.guess == MPFC_GUESS_PREV ? 0 : 1;
     const double* pin = C->pinned ? F0.pin : nullptr;
     const double* phihat = C->pinned ? C->phihat : nullptr;
@@ -1254,7 +1328,6 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
     // without it bit for bit).
     if (F0.m % SU_X == 0 && F0.n % SU_Y == 0) {
         const dim3 grid(F0.m / SU_X, F0.n / SU_Y);
-        const unsigned nb = grid.x * grid.y;
         const bool mixed = C->o.precision == MPFC_MIXED;
         const bool norm = !mixed && !learned;
         const int ce = learned ? 1 : 0;
@@ -1270,20 +1343,18 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
             cnn_choose(C, s);  // leaves the kept guess's sum in part[0]
         }
         if (!mixed) {
-            launch_norm_finalize(C->part, learned ? 1 : (int)nb, C->st, C->hist, F0.h * F0.h,
-                                 C->o.tol, C->o.max_cycles + 1, C->o.diverge, s);
+            if (close) launch_norm_finalize(pending_norm(C, setup_parts(C)), s);
         } else {
             const auto& FF = C->FL[0];
             if (C->p.scheme == 2)
                 hipLaunchKernelGGL((k_convert<double, float>), grid1(total), dim3(256), 0, s,
                                    C->phik, FF.xk, total);
-            defect(C, 0, 0, s);
+            defect(C, 0, 0, close, s);
         }
         HIP_TRY(hipGetLastError());
         return MPFC_OK;
     }
-    // Source, guess and kappa in one pass (the caller's arrays from C->io: this
-    // part is captured once and replayed); with the learned guess the
+    // Source, guess and kappa in one pass; with the learned guess the
     // extrapolated candidate goes to copy 1 and the network's to copy 0.
     const int ce = learned ? 1 : 0;
     if (C->p.scheme == 1)
@@ -1309,24 +1380,19 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
         cnn_choose(C, s);
     }
     if (C->o.precision != MPFC_MIXED) {
-        if (learned) {  // the pick left the kept guess's squared norm in part[0]
-            launch_norm_finalize(C->part, 1, C->st, C->hist, F0.h * F0.h, C->o.tol,
-                                 C->o.max_cycles + 1, C->o.diverge, s);
-        } else {
-            // the completed guess satisfies N^(2) = S^(2), N^(3) = S^(3): only r1 is left
-            const unsigned nb = red_blocks(total);
-            hipLaunchKernelGGL((k_resnorm_guess<NT>), dim3(nb), dim3(NT), 0, s, finest_fields(C),
-                               level_op(C, F0), g0, C->part);
-            launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h, C->o.tol,
-                                 C->o.max_cycles + 1, C->o.diverge, s);
-        }
+        // the learned guess's pick left the kept guess's squared norm in part[0];
+        // else the completed guess satisfies N^(2) = S^(2), N^(3) = S^(3): only r1 is left
+        if (!learned)
+            hipLaunchKernelGGL((k_resnorm_guess<NT>), dim3(red_blocks(total)), dim3(NT), 0, s,
+                               finest_fields(C), level_op(C, F0), g0, C->part);
+        if (close) launch_norm_finalize(pending_norm(C, setup_parts(C)), s);
     } else {
         const auto& FF = C->FL[0];
         // the coarse levels' phi^k is averaged by the down launches of each cycle
         if (C->p.scheme == 2)
             hipLaunchKernelGGL((k_convert<double, float>), grid1(total), dim3(256), 0, s, C->phik,
                                FF.xk, total);
-        defect(C, 0, 0, s);
+        defect(C, 0, 0, close, s);
     }
     HIP_TRY(hipGetLastError());
     return MPFC_OK;
@@ -1683,25 +1749,25 @@ int mpfc_step(mpfc_ctx* C, const double* phi_n, const double* phi_nm1, double* p
     const size_t total = (size_t)C->m * C->n;
     const bool mixed = C->o.precision == MPFC_MIXED;
     const bool learned = C->o.guess == MPFC_GUESS_CNN;
-    // The caller's arrays, for the captured set-up and wrap-up.
+    // The caller's arrays, for the set-up and the wrap-up.
     hipLaunchKernelGGL(k_set_io, dim3(1), dim3(64), 0, s, C->io, phi_n, phi_nm1, psi, phi_np1,
                        mu_out, ka_out);
-    int rc = run_unit(C, graph_key(GK_PROLOGUE), [&](hipStream_t cs) {
-        (void)step_prologue(C, cs);
-    });
+    int rc = step_prologue(C, s);
     if (rc) return rc;
     const CycleState* hst = (const CycleState*)C->host_buf;
     const CycleState* hpst = (const CycleState*)(C->host_buf + 8);
     auto readback = [&](size_t count) -> int {
-        HIP_TRY(hipMemcpyAsync(C->host_buf, C->rb, count * sizeof(double), hipMemcpyDeviceToHost, s));
+        hipLaunchKernelGGL(k_readback, dim3(1), dim3(256), 0, s, C->rb, (int)count, C->host_buf);
+        HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(s));
         return MPFC_OK;
     };
     const bool warm = C->have_w != 0;
     const int npoisson = C->poisson_cycles;
     auto wrapup = [&]() {
-        return run_unit(C, graph_key(GK_WRAPUP, warm ? 1 : 0, npoisson),
-                        [&](hipStream_t cs) { enqueue_wrapup(C, cs, warm, npoisson); });
+        auto fn = [&](hipStream_t cs) { enqueue_wrapup(C, cs, warm, npoisson); };
+        if (!C->o.energy || npoisson == 0) return run_direct(C, fn);
+        return run_unit(C, graph_key(GK_WRAPUP, warm ? 1 : 0, npoisson), fn);
     };
     // Cycles (or mixed-precision outer iterations) are enqueued without
     // waiting for the set-up: as many as the previous step needed, then the
@@ -1798,7 +1864,7 @@ int mpfc_set_pinning(mpfc_ctx* C, const double* weight, const double* phihat) {
         return fail(MPFC_EINVAL,
                     "pinning needs the second-order scheme, FP64 and Newton linearisation");
     hipStream_t s = C->stream;
-    // the captured set-up, cycles and wrap-up change (other operator
+    // the captured cycles and wrap-ups change (other operator
     // instantiation, pinning terms): capture again
     HIP_TRY(hipStreamSynchronize(s));
     destroy_graphs(C);

@@ -278,8 +278,8 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
     } else {
         hipLaunchKernelGGL((k3_resnorm<Op, NT>), dim3(nb), dim3(NT), 0, s, op_of(F0), F0.g, FF,
                            C->part, stop);
-        launch_norm_finalize(C->part, (int)nb, C->st, C->hist, F0.h * F0.h * F0.h, C->o.tol,
-                             C->o.max_cycles + 1, C->o.diverge, s);
+        launch_norm_finalize(PendingNorm{C->part, (int)nb, C->st, C->hist, F0.h * F0.h * F0.h,
+                                         C->o.tol, C->o.diverge, C->o.max_cycles + 1}, s);
     }
     HIP_TRY(hipGetLastError());
     return MPFC_OK;
@@ -536,8 +536,8 @@ int mpfc3d_step(mpfc3d_ctx* C, const double* phi_n, const double* phi_nm1, doubl
             if (nw) hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, true>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, true>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
             else hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, false>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, false>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
         }
-        launch_norm_finalize(C->part, (int)rb, C->st, C->hist, F0.h * F0.h * F0.h, C->o.tol,
-                             C->o.max_cycles + 1, C->o.diverge, s);
+        launch_norm_finalize(PendingNorm{C->part, (int)rb, C->st, C->hist, F0.h * F0.h * F0.h,
+                                         C->o.tol, C->o.diverge, C->o.max_cycles + 1}, s);
     }
     HIP_TRY(hipGetLastError());
     // cycles: enqueue the expected number, then one or two at a time until the

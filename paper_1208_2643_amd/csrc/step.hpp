@@ -192,9 +192,9 @@ __device__ __forceinline__ void source_cell(const Grid& g, double ih2, double d,
     }
 }
 
-// Caller arrays of one step.  The step's set-up and wrap-up run as captured
-// graphs, so these pointers, which change from step to step, are read from a
-// small device table that k_set_io fills before each step.
+// Caller arrays of one step.  A wrap-up with Poisson cycles is a captured graph,
+// so these pointers, which change from step to step, are read from a small
+// device table that k_set_io fills before each step.
 struct StepIO {
     const double* phi_n;    // phi^k
     const double* phi_nm1;  // phi^{k-1}
@@ -264,6 +264,13 @@ __device__ __forceinline__ void complete_kappa_cell(const Grid& g, double ih2, d
                                                     int i, int j) {
     const size_t q = at(i, j, g);
     ka[q] = kappa_value(S3[q], e, nsum(phi, i, j, g), phi[q], ih2);
+}
+
+// The first `count` doubles of the readback block into pinned host memory (one
+// workgroup; visible to the host when the stream has been waited for).
+__global__ void __launch_bounds__(256) k_readback(const double* __restrict__ rb, int count,
+                                                  double* host) {
+    for (int k = threadIdx.x; k < count; k += 256) host[k] = rb[k];
 }
 
 __global__ void k_set_io(StepIO* io, const double* phi_n, const double* phi_nm1, double* psi,

@@ -169,6 +169,7 @@ struct TileArgs {
     // residual norm (finest up): per-block FP64 sums of r^2 into part[]
     int norm;
     double* part;
+    int ntx;                // tiles in x (set by the launch)
 };
 
 // Cell index along one axis inside the tile and coarse kernels: plain
@@ -200,6 +201,7 @@ __device__ __forceinline__ int xcd_item(int b, int nt) {
 #endif
 // Threads of a tile workgroup.
 constexpr int kTileThreads = MPFC_TILE_THREADS;
+static_assert(kTileThreads == kNormThreads, "a tile launch runs a pending stopping test");
 
 // One tile of a tiled level, in phases:
 //   load_direct  u (tile + halo) and, for up launches, u_H - v_H over the
@@ -818,15 +820,32 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
     W::compute(op, A, G, S, R, pslot);
 }
 
-// One level of one grid.  Grid: (m / tx, n / ty) workgroups of kTileThreads
-// threads (tx, ty divide m, n).
+// One level of one grid: (m / tx) (n / ty) workgroups of kTileThreads threads
+// (tx, ty divide m, n), and with a pending norm one more, the first, which runs
+// its stopping test.  The test used to be a launch of its own between the up
+// launch that wrote the sums and the next cycle's finest down launch: 4.4 us and
+// a launch gap of every cycle.  Beside the tiles it costs nothing: when it stops
+// the cycles, the tiles of this launch that did not see the flag yet have only
+// written what is rewritten before it is read again (the other copy of u, the
+// next level's arrays), and every launch behind this one returns at once.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
-                                                       const CycleState* stop) {
-    const int nt = gridDim.x * gridDim.y;
-    const int tl = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, nt);
-    const int tby = tl / gridDim.x, tbx = tl - tby * gridDim.x;
+                                                       const CycleState* stop, PendingNorm P) {
+    int b = blockIdx.x, nt = gridDim.x;
+    if constexpr (!UP) {
+        if (P.nparts) {
+            if (b == 0) {
+                norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
+                                                 P.max_norms, P.diverge);
+                return;
+            }
+            --b;
+            --nt;
+        }
+    }
+    const int tl = xcd_item(b, nt);
+    const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
     tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, stop, tbx, tby, tl);
 }
 

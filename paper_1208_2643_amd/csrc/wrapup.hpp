@@ -1,10 +1,10 @@
-// Kernels of the captured set-up and wrap-up of one time step.
+// Kernels of the wrap-up of one time step.
 //
-// A step's set-up (source, guess, completion, first norm) and wrap-up (psi
-// update, eqs. discrete_1_b / discrete_2_b, and the energies of Sec. 3) are
-// replayed from captured graphs.  The caller's arrays change from step to
-// step, so those kernels read them from a small device table (StepIO) that a
-// one-thread kernel fills before the step.
+// The wrap-up (psi update, eqs. discrete_1_b / discrete_2_b, and the energies of
+// Sec. 3) is launched kernel by kernel, or replayed from a captured graph when
+// it holds Poisson cycles.  The caller's arrays change from step to step, so its
+// kernels, and those of the set-up, read them from a small device table (StepIO)
+// that a one-thread kernel fills before the step.
 //
 // The wrap-up is enqueued right behind the predicted number of V-cycles,
 // before the host knows whether they were enough: each of its kernels first
