@@ -40,7 +40,7 @@ template <class Op, bool UP, bool NEU>
 void tile_bc(const Op& op, const TileArgs<typename Op::real>& A, int shape,
              const CycleState* stop, hipStream_t s, const PendingNorm& P) {
     const bool gen = general_index(A.g);
-    if (gen) shape = shape == 2 ? 2 : 0;  // general-index kernels: shapes 0 and 2
+    if (gen && !gen_shape(shape)) shape = 0;  // general-index kernels
     switch (shape) {
         case 0: tile_k<Op, UP, NEU, 0>(op, A, stop, s, gen, P); break;
         case 1: tile_k<Op, UP, NEU, 1>(op, A, stop, s, gen, P); break;

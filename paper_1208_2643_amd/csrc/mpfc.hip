@@ -893,6 +893,10 @@ int time_in_graph(hipStream_t& cap, hipStream_t s, int reps, Fn&& launch, float&
 }
 
 constexpr int kTuneReps = 8;
+// Cells of the largest general-grid level that tries 16 x 16 tiles: a down launch
+// takes 5.7 us against 6.2 with 32 x 16 tiles on 128 x 100, 8.1 against 6.6 on
+// 256 x 200.
+constexpr int kGenSmall = 16384;
 
 // For every level with tile launches and every launch kind, time each tile
 // shape whose halo allowance fits and keep the fastest (first within 5 %).
@@ -947,7 +951,7 @@ int autotune(mpfc_ctx* C) {
     if (forced && forced[0]) {
         const int k = std::atoi(forced);
         if (k < 0 || k >= kNumShapes) return fail(MPFC_EINVAL, "MPFC_TILE_SHAPE out of range");
-        if (C->gen && !gen_shape(k))
+        if (C->gen && k != 0 && k != 2)
             return fail(MPFC_EINVAL, "MPFC_TILE_SHAPE: grids with a side that is not a power of two "
                                      "take shape 0 or 2");
         for (auto& lv : C->L)

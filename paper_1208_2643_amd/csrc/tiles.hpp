@@ -812,7 +812,7 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
         // covers its latency
         W::load_direct(A, G, S, [] {});
         __syncthreads();
-        W::fetch_rhs(A, G, R);
+        if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
         W::load_direct(A, G, S, [&] { W::fetch_rhs(A, G, R); });
         __syncthreads();
