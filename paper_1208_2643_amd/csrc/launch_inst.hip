@@ -14,6 +14,14 @@ bool general_index(const Grid& g) { return g.lm < 0 || g.ln < 0; }
 #define MPFC_TILE_EXACT 1
 #endif
 
+// The halo of up launches of two passes without a residual (every coarse one of
+// V(2,2), every FP32 one), and of down and finest up launches of one pass.  As a
+// compile-time halo it leaves no extent to run time, and a tile holds 1.1 to 1.25
+// times fewer cells in LDS than with the shape's allowance of 6.  Ten steps of
+// V(1,1) on 256 x 128 (Neumann): 8.36 -> 7.97 ms; five of 2048^2 in mixed
+// precision: 10.3 -> 10.04 ms.  (Shapes 5 and 6 would repeat 2 and 3.)
+constexpr int kHaloSmall = 4;
+
 template <class Op, bool UP, bool NEU, int K>
 void tile_k(const Op& op, TileArgs<typename Op::real> A, const CycleState* stop, hipStream_t s,
             bool gen, const PendingNorm& P) {
@@ -32,6 +40,13 @@ void tile_k(const Op& op, TileArgs<typename Op::real> A, const CycleState* stop,
         hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU, false, true>), grid, blk, 0, s,
                            op, A, stop, P);
         return;
+    }
+    if constexpr (K <= 4) {
+        if (MPFC_TILE_EXACT && A.tx == S.tx && A.ty == S.ty && A.H == kHaloSmall) {
+            hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, kHaloSmall, UP, NEU, false, true>), grid, blk,
+                               0, s, op, A, stop, P);
+            return;
+        }
     }
     hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU>), grid, blk, 0, s, op, A, stop, P);
 }
