@@ -4,8 +4,8 @@
 //
 // Every batched launch walks a work list of BatchItem {arg, tile}: `arg`
 // selects the simulation's argument record in a device table, `tile` the
-// piece of its grid this workgroup handles.  The cell kernels here take
-// chunks of BCHUNK cells of the finest grid; the V-cycle tiles and the
+// piece of its grid this workgroup handles.  The kernels here take 32 x 8 tiles of
+// the finest grid (the wrap-up chunks of BCHUNK cells); the V-cycle tiles and the
 // persistent coarse levels are the batched forms of the single-grid kernels
 // (k_tile_batched, k_coarse_persistent_batched).  Each simulation keeps its
 // own stop flag: once it has converged its items return at once, while the
@@ -18,15 +18,14 @@
 
 namespace mpfc {
 
-constexpr int BCHUNK = 1024;  // cells per item of the cell kernels (256 threads x 4)
+constexpr int BCHUNK = 1024;  // cells per item of the wrap-up (256 threads x 4)
 
 // Per-simulation record of the cell kernels.  Pointers are into the
 // simulation's own device arena (finest level).
 struct BSim {
     Grid g;
-    double ih2, h2;
+    double h2;
     double d, alpha;            // source: weight of psi^k, alpha = 1 - eps
-    double al, e;               // N^(2) linear weight, N^(3) Laplacian weight
     double dt;
     LevelOp<double> op;
     double* S[3];               // source
@@ -39,7 +38,8 @@ struct BSim {
     CycleState* st;
     double* hist;
     double* part;               // per-item partial sums of r^2
-    int nchunks;                // m n / BCHUNK: partials of the cell kernels
+    int ntx;                    // 32 x 8 tiles in x
+    int nparts;                 // partials of the set-up and defect kernels (their item count)
     int ntiles_up;              // partials of the finest up launch (its tile count)
 };
 
@@ -52,52 +52,11 @@ struct BIo {
 };
 
 // Cells of item `chunk`: q = chunk * BCHUNK + k * 256 + t, k < 4 (coalesced).
-#define BATCH_CELLS(S, chunk, ...)                                                    \
+#define BATCH_CELLS(chunk, ...)                                                       \
     for (int k_ = 0; k_ < BCHUNK / 256; ++k_) {                                       \
         const size_t q = (size_t)(chunk) * BCHUNK + (size_t)k_ * 256 + threadIdx.x;   \
-        const int i = (int)(q & (size_t)((S).g.m - 1));                               \
-        const int j = (int)(q >> (S).g.lm);                                           \
-        (void)i; (void)j;                                                             \
         __VA_ARGS__                                                                   \
     }
-
-// Step set-up, part 1: source S, copy of phi^k, guess phi^(0).
-template <int SCHEME>
-__global__ void __launch_bounds__(256) k_b_setup(const BSim* __restrict__ sims,
-                                                 const BIo* __restrict__ io,
-                                                 const BatchItem* __restrict__ items, int mode) {
-    const BatchItem it = items[blockIdx.x];
-    const BSim& S = sims[it.arg];
-    const BIo& O = io[it.arg];
-    BATCH_CELLS(S, it.tile, {
-        source_cell<SCHEME>(S.g, S.ih2, S.d, S.alpha, O.phin, O.phinm1, O.psi, S.S[0], S.S[1],
-                            S.S[2], S.phik, i, j);
-        S.u[0][0][q] = guess_value(mode, O.phin[q], O.phinm1[q]);
-    })
-}
-
-// Part 2: kappa completion.
-__global__ void __launch_bounds__(256) k_b_kappa(const BSim* __restrict__ sims,
-                                                 const BatchItem* __restrict__ items) {
-    const BatchItem it = items[blockIdx.x];
-    const BSim& S = sims[it.arg];
-    BATCH_CELLS(S, it.tile, {
-        complete_kappa_cell(S.g, S.ih2, S.e, S.u[0][0], S.S[2], S.u[0][2], i, j);
-    })
-}
-
-// Part 3: mu completion; with mixed precision (scheme 2) also phi^k in FP32.
-template <int SCHEME, bool MIXED>
-__global__ void __launch_bounds__(256) k_b_mu(const BSim* __restrict__ sims,
-                                              const BatchItem* __restrict__ items) {
-    const BatchItem it = items[blockIdx.x];
-    const BSim& S = sims[it.arg];
-    BATCH_CELLS(S, it.tile, {
-        complete_mu_cell<SCHEME>(S.g, S.ih2, S.al, S.u[0][0], S.phik, S.u[0][2], S.S[1],
-                                 S.u[0][1], i, j);
-        if constexpr (MIXED && SCHEME == 2) S.fxk[q] = (float)S.phik[q];
-    })
-}
 
 // Reset every simulation's cycle state.
 __global__ void __launch_bounds__(64) k_b_state_reset(const BSim* __restrict__ sims, int nsim) {
@@ -108,72 +67,53 @@ __global__ void __launch_bounds__(64) k_b_state_reset(const BSim* __restrict__ s
     st->status = ST_RUNNING; st->done = 0; st->pad0 = st->pad1 = 0;
 }
 
-// FP64 residual of the iterate u[0]: per-item sum of r^2 into part[chunk].
-template <int SCHEME>
-__global__ void __launch_bounds__(256) k_b_resnorm(const BSim* __restrict__ sims,
-                                                   const BatchItem* __restrict__ items) {
-    const BatchItem it = items[blockIdx.x];
+// Set-up and, with mixed precision, the FP64 defect step u[from] (+ e) ->
+// u[from ^ 1] (FP32 residual, base phi, sums of r^2), one 32 x 8 tile of a finest
+// grid per item: the bodies of k_setup_tile and k_defect_tile.  (A member has more
+// than 1024 cells and an aspect ratio of at most 2, so its sides are multiples of
+// 32.)  Bound by memory: a cell's set-up moves 84 bytes, its defect 108.  On
+// 24.7e6 cells in mixed precision: set-up 782 us as three passes of one cell per
+// thread -> 434 us, defect 658 -> 508 us (5.25 TB/s, the rate of a large copy).
+template <int SCHEME, bool NORM>
+__global__ void __launch_bounds__(SU_X * SU_Y) k_b_setup_tile(const BSim* __restrict__ sims,
+                                                              const BIo* __restrict__ io,
+                                                              const BatchItem* __restrict__ items,
+                                                              int nitems, int mode) {
+    const BatchItem it = items[xcd_item(blockIdx.x, nitems)];
     const BSim& S = sims[it.arg];
-    if (stopped(S.st)) return;
-    __shared__ double red[4];
-    Fields<double> F;
-    F.phi = S.u[0][0]; F.mu = S.u[0][1]; F.ka = S.u[0][2];
-    F.f1 = S.S[0]; F.f2 = S.S[1]; F.f3 = S.S[2];
-    F.phik = S.phik; F.base = nullptr;
-    double acc = 0.0;
-    BATCH_CELLS(S, it.tile, {
-        double a, b, c;
-        residual_at<double, SCHEME, false>(F, S.op, S.g, i, j, a, b, c);
-        acc += a * a + b * b + c * c;
-    })
-    const double bs = block_sum<256>(acc, red);
-    if (threadIdx.x == 0) S.part[it.tile] = bs;
+    const BIo& O = io[it.arg];
+    const int tby = it.tile / S.ntx, tbx = it.tile - tby * S.ntx;
+    setup_tile<SCHEME, NORM>(S.g, S.op, S.d, S.alpha, mode, O.phin, O.phinm1, O.psi, S.S[0], S.S[1],
+                             S.S[2], S.phik, S.fxk, nullptr, nullptr, S.u[0][0], S.u[0][2],
+                             S.u[0][1], S.part, it.tile, tbx, tby);
 }
 
-// Mixed precision: FP64 defect step u[from] (+ e) -> u[from ^ 1], FP32 residual
-// and base phi, per-item sum of r^2.
 template <int SCHEME>
-__global__ void __launch_bounds__(256) k_b_defect(const BSim* __restrict__ sims,
-                                                  const BatchItem* __restrict__ items, int from,
-                                                  int add) {
-    const BatchItem it = items[blockIdx.x];
+__global__ void __launch_bounds__(DT_X * DT_Y) k_b_defect_tile(const BSim* __restrict__ sims,
+                                                               const BatchItem* __restrict__ items,
+                                                               int nitems, int from, int add) {
+    const BatchItem it = items[xcd_item(blockIdx.x, nitems)];
     const BSim& S = sims[it.arg];
     if (stopped(S.st)) return;
-    __shared__ double red[4];
     const int to = from ^ 1;
+    const int tby = it.tile / S.ntx, tbx = it.tile - tby * S.ntx;
     Fields<double> F;
     F.phi = S.u[from][0]; F.mu = S.u[from][1]; F.ka = S.u[from][2];
     F.f1 = S.S[0]; F.f2 = S.S[1]; F.f3 = S.S[2];
     F.phik = S.phik; F.base = nullptr;
-    double acc = 0.0;
-    BATCH_CELLS(S, it.tile, {
-        acc += defect_cell<SCHEME>(F, S.op, S.g, S.fe[0], S.fe[1], S.fe[2], add, S.u[to][0],
-                                   S.u[to][1], S.u[to][2], S.fr[0], S.fr[1], S.fr[2], S.fpb, i, j);
-    })
-    const double bs = block_sum<256>(acc, red);
-    if (threadIdx.x == 0) S.part[it.tile] = bs;
-}
-
-// Mixed precision: clear the FP32 correction before an outer iteration.
-__global__ void __launch_bounds__(256) k_b_clear_e(const BSim* __restrict__ sims,
-                                                   const BatchItem* __restrict__ items) {
-    const BatchItem it = items[blockIdx.x];
-    const BSim& S = sims[it.arg];
-    if (stopped(S.st)) return;
-    BATCH_CELLS(S, it.tile, {
-        S.fe[0][q] = 0.f; S.fe[1][q] = 0.f; S.fe[2][q] = 0.f;
-    })
+    defect_tile<SCHEME>(F, S.op, S.g, S.part, it.tile, S.fe[0], S.fe[1], S.fe[2], add, S.u[to][0],
+                        S.u[to][1], S.u[to][2], S.fr[0], S.fr[1], S.fr[2], S.fpb, tbx, tby);
 }
 
 // Norm, history and stop decision of every simulation: workgroup s sums
 // simulation s's partials.
-// `tiles` = 1: the partials come from the finest up launch, else from a cell kernel.
+// `tiles` = 1: the partials come from the finest up launch, else from set-up or defect.
 template <int NT>
 __global__ void __launch_bounds__(NT) k_b_finalize(const BSim* __restrict__ sims, int tiles,
                                                    double tol, int max_norms, double diverge) {
     const BSim& S = sims[blockIdx.x];
     if (stopped(S.st)) return;
-    norm_finalize_body<NT>(S.part, tiles ? S.ntiles_up : S.nchunks, S.st, S.hist, S.h2, tol,
+    norm_finalize_body<NT>(S.part, tiles ? S.ntiles_up : S.nparts, S.st, S.hist, S.h2, tol,
                            max_norms, diverge);
 }
 
@@ -190,7 +130,7 @@ __global__ void __launch_bounds__(256) k_b_psi(const BSim* __restrict__ sims,
     int cur = 0;
     if constexpr (MIXED) cur = 1 ^ ((S.st->count - 1) & 1);
     const double* phi = S.u[cur][0];
-    BATCH_CELLS(S, it.tile, { psi_cell<SCHEME>(S.dt, phi, O.phin, O.psi, O.phinp1, q); })
+    BATCH_CELLS(it.tile, { psi_cell<SCHEME>(S.dt, phi, O.phin, O.psi, O.phinp1, q); })
 }
 
 #undef BATCH_CELLS

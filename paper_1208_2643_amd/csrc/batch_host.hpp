@@ -3,8 +3,8 @@
 //
 // A batch is a set of independent simulations, each an internal single-grid
 // context (own arena, levels and parameters), advanced by shared launches:
-//  - cell phases (set-up, completion, residual/defect, psi update): one launch
-//    over the chunks of every simulation's finest grid;
+//  - cell phases (set-up, defect, psi update): one launch over the 32 x 8 tiles or
+//    chunks of every simulation's finest grid;
 //  - tile phases: the tiled levels of all simulations, grouped by level size
 //    (a group holds every simulation's level of that size); down phases run
 //    from the largest size to the smallest, up phases the other way, so each
@@ -33,6 +33,7 @@ struct KindTable {
     BatchItem* d_items = nullptr;
     int nitems = 0;
     int cap_items = 0;
+    int exact_h = 0;      // the halo of every member, if they agree and the tile is the shape's
 };
 
 struct PhaseKey {
@@ -70,6 +71,8 @@ struct mpfc_batch {
     CycleState* h_st = nullptr;          // pinned readback
     BatchItem* d_cells = nullptr;
     int ncells = 0;
+    BatchItem* d_tiles = nullptr;        // 32 x 8 tiles of every finest grid
+    int ntiles = 0;
     std::vector<PhaseKey> phases;        // tile phases, largest size first
     BatchBase* impl = nullptr;
     hipGraphExec_t gx_pro = nullptr, gx_cyc = nullptr, gx_epi = nullptr, gx_out[3] = {};  // outer iterations from copy 0, 1; the step's first
@@ -126,6 +129,8 @@ struct BatchImpl : BatchBase {
         std::vector<BatchTile<Op>> args;
         std::vector<BatchItem> items;
         const auto& ph = B->phases[p];
+        kt.exact_h = 0;
+        bool exact = true;
         for (int k = 0; k < (int)ph.members.size(); ++k) {
             const int s = ph.members[k].first, l = ph.members[k].second;
             const mpfc_ctx* C = B->C[s];
@@ -137,8 +142,12 @@ struct BatchImpl : BatchBase {
             } else {
                 bt.op = make_op32<Op>(C, lv);
                 bt.A = UP ? up_args32(C, l) : dn_args32(C, l);
+                bt.A.zero_in = !UP && l == 0;  // read in an outer iteration's first cycle
             }
             tile_dims(lv, shape, bt.A.tx, bt.A.ty);
+            if (k == 0) kt.exact_h = bt.A.H;
+            exact = exact && bt.A.H == kt.exact_h && bt.A.tx == kShapes[shape].tx &&
+                    bt.A.ty == kShapes[shape].ty;
             bt.stop = with_stop ? C->st : nullptr;
             bt.part_off = 0;
             bt.ntx = lv.m / bt.A.tx;
@@ -147,6 +156,7 @@ struct BatchImpl : BatchBase {
             if (F64 && UP && l == 0) B->hsims[s].ntiles_up = nt;
             args.push_back(bt);
         }
+        if (!exact) kt.exact_h = 0;
         if (!kt.d_args) {
             int rc = B->dalloc(&kt.d_args, args.size());
             if (rc) return rc;
@@ -170,9 +180,13 @@ struct BatchImpl : BatchBase {
         return MPFC_OK;
     }
 
+    // `first`: the first FP32 cycle of an outer iteration, whose finest down
+    // launches start from a zero correction instead of reading a cleared one.
     template <class Op, bool UP>
-    void launch(const KindTable<Op>& kt, hipStream_t s) {
-        if (kt.nitems > 0) launch_tile_batched<Op, UP>(B->neu, kt.shape, kt.d_args, kt.d_items, kt.nitems, s);
+    void launch(const KindTable<Op>& kt, hipStream_t s, bool first = false) {
+        if (kt.nitems > 0)
+            launch_tile_batched<Op, UP>(B->neu, kt.shape, kt.exact_h, kt.d_args, kt.d_items,
+                                        kt.nitems, first, s);
     }
 
     int build() override {
@@ -264,20 +278,21 @@ struct BatchImpl : BatchBase {
                            B->o.tol, B->o.max_cycles + 1, B->o.diverge);
     }
 
+    // FP64 defect step of mixed precision from copy `from`.
+    void defect(int from, int add, hipStream_t s) {
+        hipLaunchKernelGGL((k_b_defect_tile<S>), dim3(B->ntiles), dim3(DT_X * DT_Y), 0, s,
+                           B->d_sims, B->d_tiles, B->ntiles, from, add);
+    }
+
     void prologue(hipStream_t s) override {
         hipLaunchKernelGGL(k_b_state_reset, dim3((B->nsim + 63) / 64), dim3(64), 0, s, B->d_sims,
                            B->nsim);
-        const dim3 gc(B->ncells), blk(256);
         const int mode = B->o.guess == MPFC_GUESS_EXTRAP ? 1 : 0;
-        hipLaunchKernelGGL((k_b_setup<S>), gc, blk, 0, s, B->d_sims, B->d_io, B->d_cells, mode);
-        hipLaunchKernelGGL(k_b_kappa, gc, blk, 0, s, B->d_sims, B->d_cells);
-        if (B->mixed) {
-            hipLaunchKernelGGL((k_b_mu<S, true>), gc, blk, 0, s, B->d_sims, B->d_cells);
-            hipLaunchKernelGGL((k_b_defect<S>), gc, blk, 0, s, B->d_sims, B->d_cells, 0, 0);
-        } else {
-            hipLaunchKernelGGL((k_b_mu<S, false>), gc, blk, 0, s, B->d_sims, B->d_cells);
-            hipLaunchKernelGGL((k_b_resnorm<S>), gc, blk, 0, s, B->d_sims, B->d_cells);
-        }
+        // in FP64 with the first norm's sums
+        auto kern = B->mixed ? k_b_setup_tile<S, false> : k_b_setup_tile<S, true>;
+        hipLaunchKernelGGL(kern, dim3(B->ntiles), dim3(SU_X * SU_Y), 0, s, B->d_sims, B->d_io,
+                           B->d_tiles, B->ntiles, mode);
+        if (B->mixed) defect(0, 0, s);
         finalize(0, s);
     }
 
@@ -295,15 +310,13 @@ struct BatchImpl : BatchBase {
     // `ncyc` FP32 cycles.
     void outer(int from, int ncyc, hipStream_t s) override {
         const int np = (int)B->phases.size();
-        hipLaunchKernelGGL(k_b_clear_e, dim3(B->ncells), dim3(256), 0, s, B->d_sims, B->d_cells);
         for (int k = 0; k < ncyc; ++k) {
-            for (int p = 0; p < np; ++p) launch<Op32, false>(t32[0][p], s);
+            for (int p = 0; p < np; ++p) launch<Op32, false>(t32[0][p], s, k == 0);
             if (nc[0]) launch_coarse_batched<Op32, 4>(B->neu, nc[0], d_c32[0], s);
             if (nc[1]) launch_coarse_batched<Op32, 8>(B->neu, nc[1], d_c32[1], s);
             for (int p = np - 1; p >= 0; --p) launch<Op32, true>(t32[1][p], s);
         }
-        hipLaunchKernelGGL((k_b_defect<S>), dim3(B->ncells), dim3(256), 0, s, B->d_sims,
-                           B->d_cells, from, 1);
+        defect(from, 1, s);
         finalize(0, s);
     }
 
@@ -444,18 +457,15 @@ int mpfc_batch_create(mpfc_batch** out, int nsim, const mpfc_sim_desc* sims, con
         hipHostMalloc((void**)&B->h_io, nsim * sizeof(BIo), hipHostMallocDefault) != hipSuccess)
         return bail(fail(MPFC_ENOMEM, "hipHostMalloc"));
     // per-simulation records and the cell work list
-    std::vector<BatchItem> cells;
+    std::vector<BatchItem> cells, tiles;
     for (int s = 0; s < nsim; ++s) {
         const mpfc_ctx* C = B->C[s];
         const Level& F0 = C->L[0];
         BSim S{};
         S.g = F0.g;
-        S.ih2 = 1.0 / (F0.h * F0.h);
         S.h2 = F0.h * F0.h;
         S.d = C->d;
         S.alpha = C->alpha;
-        S.al = C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha;
-        S.e = C->p.scheme == 1 ? 1.0 : 0.5;
         S.dt = C->p.dt;
         S.op = level_op(C, F0);
         for (int f = 0; f < 3; ++f) {
@@ -475,11 +485,19 @@ int mpfc_batch_create(mpfc_batch** out, int nsim, const mpfc_sim_desc* sims, con
         S.st = C->st;
         S.hist = C->hist;
         S.part = C->part;
-        S.nchunks = (int)((size_t)F0.m * F0.n / BCHUNK);
+        const int nchunks = (int)((size_t)F0.m * F0.n / BCHUNK);
+        if (F0.m % SU_X || F0.n % SU_Y) return bail(fail(MPFC_EINVAL, "internal: narrow batch member"));
+        S.ntx = F0.m / SU_X;
+        S.nparts = S.ntx * (F0.n / SU_Y);
         S.ntiles_up = 0;
         B->hsims.push_back(S);
-        for (int c = 0; c < S.nchunks; ++c) cells.push_back(BatchItem{s, c});
+        for (int c = 0; c < nchunks; ++c) cells.push_back(BatchItem{s, c});
+        for (int c = 0; c < S.nparts; ++c) tiles.push_back(BatchItem{s, c});
     }
+    B->ntiles = (int)tiles.size();
+    if ((rc = B->dalloc(&B->d_tiles, tiles.size()))) return bail(rc);
+    if (hipMemcpy(B->d_tiles, tiles.data(), tiles.size() * sizeof(BatchItem), hipMemcpyHostToDevice) != hipSuccess)
+        return bail(fail(MPFC_EHIP, "hipMemcpy"));
     B->ncells = (int)cells.size();
     if ((rc = B->dalloc(&B->d_cells, cells.size()))) return bail(rc);
     if (hipMemcpy(B->d_cells, cells.data(), cells.size() * sizeof(BatchItem), hipMemcpyHostToDevice) != hipSuccess)

@@ -42,11 +42,13 @@ void launch_coarsest_gen(const Op& op, const CoarseArgs<typename Op::real>& A,
 void launch_coarsest_poisson(const PoissonOp<double>& op, const CoarseArgs<double>& A,
                              const CycleState* stop, hipStream_t s);
 
-// Batched: one tiled level size of many grids (work list `items`), and the
+// Batched: one tiled level size of many grids (work list `items`; `exact_h` the
+// halo of all of them where it is one and the tile is the shape's, else 0;
+// `first`: members with zero_in start from zero), and the
 // persistent coarse levels with one workgroup per grid (coarsest NC cells).
 template <class Op, bool UP>
-void launch_tile_batched(bool neu, int shape, const BatchTile<Op>* args, const BatchItem* items,
-                         int n, hipStream_t s);
+void launch_tile_batched(bool neu, int shape, int exact_h, const BatchTile<Op>* args,
+                         const BatchItem* items, int n, bool first, hipStream_t s);
 template <class Op, int NC>
 void launch_coarse_batched(bool neu, int nsim, const BatchCoarse<Op>* args, hipStream_t s);
 

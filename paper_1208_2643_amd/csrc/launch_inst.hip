@@ -68,23 +68,38 @@ void tile_bc(const Op& op, const TileArgs<typename Op::real>& A, int shape,
 }
 
 template <class Op, bool UP, bool NEU, int K>
-void tile_batched_k(const BatchTile<Op>* args, const BatchItem* items, int n, hipStream_t s) {
+void tile_batched_k(int exact_h, const BatchTile<Op>* args, const BatchItem* items, int n,
+                    bool first, hipStream_t s) {
     constexpr TileShape S = kShapes[K];
-    hipLaunchKernelGGL((k_tile_batched<Op, S.tx, S.ty, S.hmax, UP, NEU>), dim3(n), dim3(kTileThreads), 0, s,
-                       args, items, n);
+    const dim3 grid(n), blk(kTileThreads);
+    const int f = first;
+    if constexpr (K <= 3) {
+        if (exact_h == S.hmax) {
+            hipLaunchKernelGGL((k_tile_batched<Op, S.tx, S.ty, S.hmax, UP, NEU, true>), grid, blk,
+                               0, s, args, items, n, f);
+            return;
+        }
+        if (exact_h == kHaloSmall) {
+            hipLaunchKernelGGL((k_tile_batched<Op, S.tx, S.ty, kHaloSmall, UP, NEU, true>), grid,
+                               blk, 0, s, args, items, n, f);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_tile_batched<Op, S.tx, S.ty, S.hmax, UP, NEU, false>), grid, blk, 0, s,
+                       args, items, n, f);
 }
 
 template <class Op, bool UP, bool NEU>
-void tile_batched_bc(int shape, const BatchTile<Op>* args, const BatchItem* items, int n,
-                     hipStream_t s) {
+void tile_batched_bc(int shape, int h, const BatchTile<Op>* args, const BatchItem* items, int n,
+                     bool first, hipStream_t s) {
     switch (shape) {
-        case 0: tile_batched_k<Op, UP, NEU, 0>(args, items, n, s); break;
-        case 1: tile_batched_k<Op, UP, NEU, 1>(args, items, n, s); break;
-        case 2: tile_batched_k<Op, UP, NEU, 2>(args, items, n, s); break;
-        case 3: tile_batched_k<Op, UP, NEU, 3>(args, items, n, s); break;
-        case 4: tile_batched_k<Op, UP, NEU, 4>(args, items, n, s); break;
-        case 5: tile_batched_k<Op, UP, NEU, 5>(args, items, n, s); break;
-        default: tile_batched_k<Op, UP, NEU, 6>(args, items, n, s); break;
+        case 0: tile_batched_k<Op, UP, NEU, 0>(h, args, items, n, first, s); break;
+        case 1: tile_batched_k<Op, UP, NEU, 1>(h, args, items, n, first, s); break;
+        case 2: tile_batched_k<Op, UP, NEU, 2>(h, args, items, n, first, s); break;
+        case 3: tile_batched_k<Op, UP, NEU, 3>(h, args, items, n, first, s); break;
+        case 4: tile_batched_k<Op, UP, NEU, 4>(h, args, items, n, first, s); break;
+        case 5: tile_batched_k<Op, UP, NEU, 5>(h, args, items, n, first, s); break;
+        default: tile_batched_k<Op, UP, NEU, 6>(h, args, items, n, first, s); break;
     }
 }
 
@@ -120,10 +135,10 @@ void launch_coarsest_gen(const Op& op, const CoarseArgs<typename Op::real>& A,
 }
 
 template <class Op, bool UP>
-void launch_tile_batched(bool neu, int shape, const BatchTile<Op>* args, const BatchItem* items,
-                         int n, hipStream_t s) {
-    if (neu) tile_batched_bc<Op, UP, true>(shape, args, items, n, s);
-    else tile_batched_bc<Op, UP, false>(shape, args, items, n, s);
+void launch_tile_batched(bool neu, int shape, int exact_h, const BatchTile<Op>* args,
+                         const BatchItem* items, int n, bool first, hipStream_t s) {
+    if (neu) tile_batched_bc<Op, UP, true>(shape, exact_h, args, items, n, first, s);
+    else tile_batched_bc<Op, UP, false>(shape, exact_h, args, items, n, first, s);
 }
 
 template <class Op, int NC>
@@ -146,10 +161,10 @@ void launch_coarse_batched(bool neu, int nsim, const BatchCoarse<Op>* args, hipS
     template void launch_coarsest_gen<OP>(const OP&, const CoarseArgs<OP::real>&,            \
                                           const CycleState*, hipStream_t);
 #define MPFC_INST_BATCH(OP)                                                                  \
-    template void launch_tile_batched<OP, false>(bool, int, const BatchTile<OP>*,            \
-                                                 const BatchItem*, int, hipStream_t);        \
-    template void launch_tile_batched<OP, true>(bool, int, const BatchTile<OP>*,             \
-                                                const BatchItem*, int, hipStream_t);         \
+    template void launch_tile_batched<OP, false>(bool, int, int, const BatchTile<OP>*,       \
+                                                 const BatchItem*, int, bool, hipStream_t);  \
+    template void launch_tile_batched<OP, true>(bool, int, int, const BatchTile<OP>*,        \
+                                                const BatchItem*, int, bool, hipStream_t);   \
     template void launch_coarse_batched<OP, 4>(bool, int, const BatchCoarse<OP>*, hipStream_t); \
     template void launch_coarse_batched<OP, 8>(bool, int, const BatchCoarse<OP>*, hipStream_t);
 

@@ -1344,8 +1344,8 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
                                      : (norm ? k_setup_tile<2, true> : k_setup_tile<2, false>);
         hipLaunchKernelGGL(kern, grid, dim3(SU_X * SU_Y), 0, s, g0, level_op(C, F0), C->d,
                            C->alpha, gmode, (const StepIO*)C->io, F0.f[0], F0.f[1], F0.f[2],
-                           C->phik, pin, phihat, F0.u[ce][0], F0.u[ce][2], F0.u[ce][1], C->st,
-                           C->part);
+                           C->phik, mixed && C->p.scheme == 2 ? C->FL[0].xk : (float*)nullptr, pin,
+                           phihat, F0.u[ce][0], F0.u[ce][2], F0.u[ce][1], C->st, C->part);
         if (learned) {
             int rc = cnn_candidate(C, (const StepIO*)C->io, s);  // into copy 0, completed
             if (rc) return rc;
@@ -1354,10 +1354,6 @@ int step_prologue(mpfc_ctx* C, hipStream_t s) {
         if (!mixed) {
             if (close) launch_norm_finalize(pending_norm(C, setup_parts(C)), s);
         } else {
-            const auto& FF = C->FL[0];
-            if (C->p.scheme == 2)
-                hipLaunchKernelGGL((k_convert<double, float>), grid1(total), dim3(256), 0, s,
-                                   C->phik, FF.xk, total);
             defect(C, 0, 0, close, s);
         }
         HIP_TRY(hipGetLastError());

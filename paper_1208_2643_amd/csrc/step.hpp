@@ -31,70 +31,30 @@ __global__ void __launch_bounds__(NT) k_resnorm(Fields<double> F, LevelOp<double
     if (threadIdx.x == 0) part[blockIdx.x] = bs;  // summed by k_norm_finalize
 }
 
-// Mixed precision, outer FP64 defect-correction step on the finest grid, one
-// cell: u_new = u + e (the FP32 correction; `add` = 0 keeps u, for the first
-// residual of a step), r = S - N(u_new) in FP64, and the inputs of the next
-// FP32 correction solve: r rounded to FP32 and the base phi rounded to FP32.
-// The neighbours' u + e are recomputed here, so no other thread's write is
-// read.  Returns the cell's sum of squared residuals (the stopping test).
-template <int SCHEME>
-__device__ __forceinline__ double defect_cell(const Fields<double>& F, const LevelOp<double>& op,
-                                              const Grid& g, const float* __restrict__ e0,
-                                              const float* __restrict__ e1,
-                                              const float* __restrict__ e2, int add, double* un0,
-                                              double* un1, double* un2, float* r0, float* r1,
-                                              float* r2, float* pbase, int i, int j) {
-    const size_t q = at(i, j, g);
-    const size_t nb[4] = {at(wrapx(i + 1, g), j, g), at(wrapx(i - 1, g), j, g),
-                          at(i, wrapy(j + 1, g), g), at(i, wrapy(j - 1, g), g)};
-    auto val = [&](const double* u, const float* e, size_t k) {
-        return add ? u[k] + (double)e[k] : u[k];
-    };
-    const double x = val(F.phi, e0, q), y = val(F.mu, e1, q), z = val(F.ka, e2, q);
-    double sx = 0, sy = 0, sz = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        sx += val(F.phi, e0, nb[k]);
-        sy += val(F.mu, e1, nb[k]);
-        sz += val(F.ka, e2, nb[k]);
-    }
-    const double xk = SCHEME == 2 ? F.phik[q] : 0.0;
-    const double lphi = (sx - 4.0 * x) * op.ih2;
-    const double lmu = (sy - 4.0 * y) * op.ih2;
-    const double lka = (sz - 4.0 * z) * op.ih2;
-    const double a = F.f1[q] - (x - op.c * lmu);
-    const double b = F.f2[q] - (y - nl_value<double, SCHEME, false>(x, 0.0, xk) - op.al * x - lka);
-    const double c = F.f3[q] - (z - op.e * lphi);
-    un0[q] = x; un1[q] = y; un2[q] = z;
-    r0[q] = (float)a; r1[q] = (float)b; r2[q] = (float)c;
-    pbase[q] = (float)x;
-    return a * a + b * b + c * c;
-}
-
-// The same on a 32 x 8 tile per workgroup (one cell per thread): u + e of the
-// tile and a ring of one cell (the neighbour rule of wrapx / wrapy) is formed
-// once into LDS, so each cell's value is loaded from memory once instead of
-// by its five stencils.  Same arithmetic and order per cell as defect_cell;
-// per-block sums of r^2 into part[] (blockIdx.y * gridDim.x + blockIdx.x),
-// summed by k_norm_finalize.  The correction e is cleared by the next outer
-// iteration, not here (other workgroups still read it for their ring).
+// Mixed precision, outer FP64 defect-correction step on the finest grid:
+// u_new = u + e (the FP32 correction; `add` = 0 keeps u, for the first residual
+// of a step), r = S - N(u_new) in FP64, and the inputs of the next FP32
+// correction solve: r rounded to FP32 and the base phi rounded to FP32.  A
+// 32 x 8 tile per workgroup (one cell per thread): u + e of the tile and a ring
+// of one cell (the neighbour rule of wrapx / wrapy) is formed once into LDS, so
+// each cell's value is loaded from memory once instead of by its five stencils.
+// The tile's sum of r^2 goes into part[pslot], summed by the stopping test.  The
+// correction e is cleared by the next outer iteration, not here (other
+// workgroups still read it for their ring).
 constexpr int DT_X = 32, DT_Y = 8;
 template <int SCHEME>
-__global__ void __launch_bounds__(DT_X * DT_Y) k_defect_tile(Fields<double> F, LevelOp<double> op,
-                                                            Grid g, const CycleState* st,
-                                                            double* part,
-                                                            const float* __restrict__ e0,
-                                                            const float* __restrict__ e1,
-                                                            const float* __restrict__ e2, int add,
-                                                            double* un0, double* un1, double* un2,
-                                                            float* r0, float* r1, float* r2,
-                                                            float* pbase) {
+__device__ __forceinline__ void defect_tile(const Fields<double>& F, const LevelOp<double>& op,
+                                            const Grid& g, double* part, int pslot,
+                                            const float* __restrict__ e0,
+                                            const float* __restrict__ e1,
+                                            const float* __restrict__ e2, int add, double* un0,
+                                            double* un1, double* un2, float* r0, float* r1,
+                                            float* r2, float* pbase, int tbx, int tby) {
     constexpr int NT = DT_X * DT_Y, LX = DT_X + 2, LY = DT_Y + 2, NL = LX * LY;
-    if (stopped(st)) return;
     __shared__ double U[3][LY][LX];
     __shared__ double red[NT / 64];
     const int t = threadIdx.x;
-    const int x0 = blockIdx.x * DT_X, y0 = blockIdx.y * DT_Y;
+    const int x0 = tbx * DT_X, y0 = tby * DT_Y;
     // tile + ring: every load issued before the LDS stores (indices clamped)
     constexpr int NR = (NL + NT - 1) / NT;
     double v[NR][3];
@@ -127,7 +87,7 @@ __global__ void __launch_bounds__(DT_X * DT_Y) k_defect_tile(Fields<double> F, L
         const size_t q = at(i, j, g);
         const int lx = tx + 1, ly = ty + 1;
         const double x = U[0][ly][lx], y = U[1][ly][lx], z = U[2][ly][lx];
-        // neighbours in defect_cell's order: east, west, north, south
+        // neighbours: east, west, north, south
         const double sx = ((U[0][ly][lx + 1] + U[0][ly][lx - 1]) + U[0][ly + 1][lx]) + U[0][ly - 1][lx];
         const double sy = ((U[1][ly][lx + 1] + U[1][ly][lx - 1]) + U[1][ly + 1][lx]) + U[1][ly - 1][lx];
         const double sz = ((U[2][ly][lx + 1] + U[2][ly][lx - 1]) + U[2][ly + 1][lx]) + U[2][ly - 1][lx];
@@ -144,9 +104,23 @@ __global__ void __launch_bounds__(DT_X * DT_Y) k_defect_tile(Fields<double> F, L
         acc = a * a + b * b + c * c;
     }
     const double bs = block_sum<NT>(acc, red);
-    if (t == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = bs;
+    if (t == 0) part[pslot] = bs;
 }
 
+template <int SCHEME>
+__global__ void __launch_bounds__(DT_X * DT_Y) k_defect_tile(Fields<double> F, LevelOp<double> op,
+                                                            Grid g, const CycleState* st,
+                                                            double* part,
+                                                            const float* __restrict__ e0,
+                                                            const float* __restrict__ e1,
+                                                            const float* __restrict__ e2, int add,
+                                                            double* un0, double* un1, double* un2,
+                                                            float* r0, float* r1, float* r2,
+                                                            float* pbase) {
+    if (stopped(st)) return;
+    defect_tile<SCHEME>(F, op, g, part, blockIdx.y * gridDim.x + blockIdx.x, e0, e1, e2, add, un0,
+                        un1, un2, r0, r1, r2, pbase, blockIdx.x, blockIdx.y);
+}
 
 template <typename TI, typename TO>
 __global__ void __launch_bounds__(256) k_convert(const TI* __restrict__ a, TO* b, size_t n) {
@@ -329,25 +303,23 @@ __global__ void __launch_bounds__(256) k_setup(Grid g, double ih2, double d, dou
 // LDS; the guess is formed on all of it, kappa on the tile and two rings, mu
 // on the tile and one ring.  Same arithmetic and order per cell as those
 // kernels.  Sides must be multiples of 32 (x) and 8 (y), at least 32 x 8.
-// Workgroup (0, 0) also resets the cycle state.
 constexpr int SU_X = 32, SU_Y = 8, SU_H = 3;
 template <int SCHEME, bool NORM>
-__global__ void __launch_bounds__(SU_X * SU_Y) k_setup_tile(
-    Grid g, LevelOp<double> op, double d, double alpha, int mode, const StepIO* __restrict__ io,
-    double* S1, double* S2, double* S3, double* phik_copy, const double* __restrict__ pin,
-    const double* __restrict__ phihat, double* phi0, double* ka, double* mu, CycleState* st,
-    double* part) {
+__device__ __forceinline__ void setup_tile(const Grid& g, const LevelOp<double>& op, double d,
+                                           double alpha, int mode,
+                                           const double* __restrict__ phik,
+                                           const double* __restrict__ phikm1,
+                                           const double* __restrict__ psik, double* S1, double* S2,
+                                           double* S3, double* phik_copy, float* phik32,
+                                           const double* __restrict__ pin,
+                                           const double* __restrict__ phihat, double* phi0,
+                                           double* ka, double* mu, double* part, int pslot,
+                                           int tbx, int tby) {
     constexpr int NT = SU_X * SU_Y, LX = SU_X + 2 * SU_H, LY = SU_Y + 2 * SU_H;
     __shared__ double PK[LY][LX], PM[LY][LX], G0[LY][LX], K[LY][LX], MU[LY][LX];
     __shared__ double red[NT / 64];
     const int t = threadIdx.x;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) {
-        st->acc = 0.0; st->blocks = 0u; st->count = 0;
-        st->status = ST_RUNNING; st->done = 0; st->pad0 = st->pad1 = 0;
-    }
-    const int xb = blockIdx.x * SU_X - SU_H, yb = blockIdx.y * SU_Y - SU_H;
-    const double* __restrict__ phik = io->phi_n;
-    const double* __restrict__ phikm1 = io->phi_nm1;
+    const int xb = tbx * SU_X - SU_H, yb = tby * SU_Y - SU_H;
     const double ih2 = op.ih2;
     // phi^k, phi^{k-1} and the guess on the tile and three rings
     {
@@ -410,13 +382,14 @@ __global__ void __launch_bounds__(SU_X * SU_Y) k_setup_tile(
     __syncthreads();
     // the tile: S, phi^k copy, guess, kappa, mu and the first residual component
     const int tx = t % SU_X, ty = t / SU_X, lx = tx + SU_H, ly = ty + SU_H;
-    const size_t q = at(blockIdx.x * SU_X + tx, blockIdx.y * SU_Y + ty, g);
+    const size_t q = at(tbx * SU_X + tx, tby * SU_Y + ty, g);
     const double pk = PK[ly][lx];
-    const double s1 = pk + d * io->psi[q];
+    const double s1 = pk + d * psik[q];
     S1[q] = s1;
     S2[q] = s2_at(lx, ly, q);
     S3[q] = SCHEME == 1 ? 0.0 : 0.5 * ((ns(PK, lx, ly) - 4.0 * pk) * ih2);
     if (phik_copy) phik_copy[q] = pk;
+    if (phik32) phik32[q] = (float)pk;
     phi0[q] = G0[ly][lx];
     ka[q] = K[ly][lx];
     mu[q] = MU[ly][lx];
@@ -424,8 +397,24 @@ __global__ void __launch_bounds__(SU_X * SU_Y) k_setup_tile(
         const double lmu = (ns(MU, lx, ly) - 4.0 * MU[ly][lx]) * ih2;
         const double r1 = s1 - (G0[ly][lx] - op.c * lmu);
         const double bs = block_sum<NT>(r1 * r1, red);
-        if (t == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = bs;
+        if (t == 0) part[pslot] = bs;
     }
+}
+
+// (workgroup (0, 0) also resets the cycle state)
+template <int SCHEME, bool NORM>
+__global__ void __launch_bounds__(SU_X * SU_Y) k_setup_tile(
+    Grid g, LevelOp<double> op, double d, double alpha, int mode, const StepIO* __restrict__ io,
+    double* S1, double* S2, double* S3, double* phik_copy, float* phik32,
+    const double* __restrict__ pin, const double* __restrict__ phihat, double* phi0, double* ka,
+    double* mu, CycleState* st, double* part) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        st->acc = 0.0; st->blocks = 0u; st->count = 0;
+        st->status = ST_RUNNING; st->done = 0; st->pad0 = st->pad1 = 0;
+    }
+    setup_tile<SCHEME, NORM>(g, op, d, alpha, mode, io->phi_n, io->phi_nm1, io->psi, S1, S2, S3,
+                             phik_copy, phik32, pin, phihat, phi0, ka, mu, part,
+                             blockIdx.y * gridDim.x + blockIdx.x, blockIdx.x, blockIdx.y);
 }
 
 // Residual norm of a guess completed by k_setup and k_complete_mu: N^(2) = S^(2)

@@ -162,7 +162,8 @@ struct TileArgs {
     const T* pin;           // pinning weight on this level (Op::PW)
     const T* cuH[3]; const T* cvH[3];      // up: coarse u after and before its solve
     int complete_f;         // down on a coarse level
-    int zero_in;            // u before the launch is zero (uin is not read)
+    int zero_in;            // u before the launch is zero (uin is not read); in a batch: in
+                            // launches marked `first`
     int nsweep;             // red-black half-sweeps (2 nu)
     int H;                  // halo (even)
     int tx, ty;             // interior tile (even, divides m, n)
@@ -385,7 +386,7 @@ struct TileWork {
     // them is waited for): the caller requests the right-hand side there.
     template <class Mid>
     static __device__ __forceinline__ void load_direct(const TileArgs<T>& A, const Geo& G, Lds& S,
-                                                       Mid&& mid) {
+                                                       bool zero_in, Mid&& mid) {
         const Grid g = A.g;
         const int t = threadIdx.x;
         const int total = G.LX * G.LY;
@@ -409,7 +410,7 @@ struct TileWork {
                 for (int f = 0; f < NF; ++f) ev[j][f] = A.cuH[f][gq] - A.cvH[f][gq];
             }
         }
-        if (A.zero_in) {
+        if (zero_in) {
             mid();
             for (int q = t; q < total; q += NT) {
                 const int y = q / G.LX, x = q - y * G.LX;
@@ -801,7 +802,8 @@ struct TileWork {
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
-                                          const CycleState* stop, int tbx, int tby, int pslot) {
+                                          const CycleState* stop, int tbx, int tby, int pslot,
+                                          bool zero_in) {
     using W = TileWork<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>;
     __shared__ typename W::Lds S;
     if (stopped(stop)) return;
@@ -810,11 +812,11 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
     if constexpr (UP) {
         // the right-hand side is first used after the prolongation, which
         // covers its latency
-        W::load_direct(A, G, S, [] {});
+        W::load_direct(A, G, S, zero_in, [] {});
         __syncthreads();
         if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
-        W::load_direct(A, G, S, [&] { W::fetch_rhs(A, G, R); });
+        W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
         __syncthreads();
     }
     W::compute(op, A, G, S, R, pslot);
@@ -846,7 +848,7 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
     }
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, stop, tbx, tby, tl);
+    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, stop, tbx, tby, tl, A.zero_in);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)
@@ -866,15 +868,18 @@ struct BatchItem {
     int tile;             // linear tile index within that grid level
 };
 
-template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU>
+// `first` set: the members with zero_in start from u = 0.
+template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool EXACT>
 __global__ void __launch_bounds__(kTileThreads) k_tile_batched(const BatchTile<Op>* __restrict__ args,
                                                       const BatchItem* __restrict__ items,
-                                                      int nitems) {
+                                                      int nitems, int first) {
     const int b = xcd_item(blockIdx.x, nitems);
     const BatchItem it = items[b];
     const BatchTile<Op>& BA = args[it.arg];
     const int tby = it.tile / BA.ntx, tbx = it.tile - tby * BA.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU>(BA.op, BA.A, BA.stop, tbx, tby, BA.part_off + it.tile);
+    tile_body<Op, TX, TY, HMAX, UP, NEU, false, EXACT>(BA.op, BA.A, BA.stop, tbx, tby,
+                                                       BA.part_off + it.tile,
+                                                       first && BA.A.zero_in);
 }
 
 // ---------------------------------------------------------------------------
