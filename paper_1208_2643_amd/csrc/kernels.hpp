@@ -137,14 +137,14 @@ struct LevelOp {
     // [[1, a, 0], [-d, 1, b], [ec, 0, 1]] with d = al + d' (d' the linearised
     // nonlinear coefficient), has determinant det0 + a d'; d + b ec = dd0 + d'
     T k1, e1;            // c/h^2, e/h^2
-    T a, b, ec;          // 4c/h^2, 4/h^2, 4e/h^2
+    T a, b, ec;          // q c/h^2, q/h^2, q e/h^2, q the Laplacian's centre weight
     T det0, dd0;         // 1 + a (al + b ec), al + b ec
-    __host__ __device__ void derive() {
+    __host__ __device__ void derive(T q = T(4)) {
         k1 = c * ih2;
         e1 = e * ih2;
-        a = T(4) * k1;
-        b = T(4) * ih2;
-        ec = T(4) * e1;
+        a = q * k1;
+        b = q * ih2;
+        ec = q * e1;
         dd0 = al + b * ec;
         det0 = T(1) + a * dd0;
     }

@@ -82,32 +82,28 @@ template <int SCHEME, bool NEWTON>
 struct MpfcOp3 {
     static constexpr int NF = 3;
     static constexpr bool XK = SCHEME == 2;
-    LevelOp<double> op;
+    LevelOp<double> op;   // derived with centre weight 6
     __device__ __forceinline__ void apply(const double* u, const double* ns, double xk,
                                           double* N) const {
-        const double lphi = (ns[0] - 6.0 * u[0]) * op.ih2;
-        const double lmu = (ns[1] - 6.0 * u[1]) * op.ih2;
-        const double lka = (ns[2] - 6.0 * u[2]) * op.ih2;
-        N[0] = u[0] - op.c * lmu;
-        N[1] = u[1] - nl_value<double, SCHEME, false>(u[0], 0.0, xk) - op.al * u[0] - lka;
-        N[2] = u[2] - op.e * lphi;
+        N[0] = u[0] - op.k1 * (ns[1] - 6.0 * u[1]);
+        N[1] = u[1] - nl_value<double, SCHEME, false>(u[0], 0.0, xk) - op.al * u[0] -
+               op.ih2 * (ns[2] - 6.0 * u[2]);
+        N[2] = u[2] - op.e1 * (ns[0] - 6.0 * u[0]);
     }
     // J_loc delta = f - N(u), J_loc = [[1, a, 0], [-d, 1, b], [ec, 0, 1]] with
     // a = 6c/h^2, b = 6/h^2, ec = 6e/h^2, d = al + g'(phi) (Newton) or Picard's.
     __device__ __forceinline__ void relax(double* u, const double* ns, const double* f,
                                           double xk) const {
-        double N[3];
-        apply(u, ns, xk, N);
-        const double r1 = f[0] - N[0], r2 = f[1] - N[1], r3 = f[2] - N[2];
-        const double d = op.al + nl_lin<double, SCHEME, NEWTON>(u[0], xk);
-        const double a = 6.0 * op.c * op.ih2, b = 6.0 * op.ih2, ec = 6.0 * op.e * op.ih2;
-        const double det = 1.0 + a * d + a * b * ec;
-        const double dm = (r2 + (d + b * ec) * r1 - b * r3) / det;
-        const double dx = r1 - a * dm;
-        const double dk = r3 - ec * dx;
+        double g, d;
+        nl_both<double, SCHEME, NEWTON, false>(u[0], 0.0, xk, g, d);
+        const double r1 = f[0] - (u[0] - op.k1 * (ns[1] - 6.0 * u[1]));
+        const double r2 = f[1] - (u[1] - g - op.al * u[0] - op.ih2 * (ns[2] - 6.0 * u[2]));
+        const double r3 = f[2] - (u[2] - op.e1 * (ns[0] - 6.0 * u[0]));
+        const double dm = (r2 + (op.dd0 + d) * r1 - op.b * r3) * recip_ge1(op.det0 + op.a * d);
+        const double dx = r1 - op.a * dm;
         u[0] += dx;
         u[1] += dm;
-        u[2] += dk;
+        u[2] += r3 - op.ec * dx;
     }
 };
 
@@ -122,7 +118,7 @@ struct PoissonOp3 {
     }
     __device__ __forceinline__ void relax(double* u, const double* ns, const double* f,
                                           double) const {
-        u[0] = (h2 * f[0] + ns[0]) / 6.0;
+        u[0] = (h2 * f[0] + ns[0]) * (1.0 / 6.0);
     }
 };
 
@@ -234,29 +230,15 @@ __global__ void __launch_bounds__(256) k3_complete(Op op, Grid3 g, L3 A, double*
     for (int f = 0; f < NF; ++f) fo[f][q] = A.f[f][q] + N[f];
 }
 
-// Coarse correction in place: vH = uH - vH (vH is not needed afterwards), so
-// the prolongation reads one array per field.  g is the coarse grid.
-template <int NF>
-__global__ void __launch_bounds__(256) k3_correction(Grid3 g, L3 H, double* vH0, double* vH1,
-                                                     double* vH2, const CycleState* st) {
-    if (stopped(st)) return;
-    const size_t q = item3();
-    if (q >= cells3(g)) return;
-    double* vH[3] = {vH0, vH1, vH2};
-#pragma unroll
-    for (int f = 0; f < NF; ++f) vH[f][q] = H.u[f][q] - vH[f][q];
-}
-
-// u += trilinear interpolation of the coarse correction E = uH - vH (held in
-// vH by k3_correction): per axis 3/4 of the parent's
-// coarse index and 1/4 of the coarse neighbour on the fine cell's side.  One
+// u += trilinear interpolation of the coarse correction E = uH - vH: per axis 3/4
+// of the parent's coarse index and 1/4 of the coarse neighbour on the fine cell's side.  One
 // thread per pair of fine cells (2I, j, k), (2I + 1, j, k): they share the
 // coarse parent, sit at the same offset of the two colour halves (so a wave
 // reads and writes both halves contiguously) and need 12 coarse values
 // between them.  g is the fine grid.
 template <int NF>
-__global__ void __launch_bounds__(256) k3_prolong(Grid3 g, L3 A, const double* E0,
-                                                  const double* E1, const double* E2,
+__global__ void __launch_bounds__(256) k3_prolong(Grid3 g, L3 A, L3 H, const double* v0_,
+                                                  const double* v1_, const double* v2_,
                                                   const CycleState* st) {
     if (stopped(st)) return;
     const size_t t = item3();
@@ -270,7 +252,7 @@ __global__ void __launch_bounds__(256) k3_prolong(Grid3 g, L3 A, const double* E
     const int Y[2] = {j >> 1, ((j >> 1) + ((j & 1) ? 1 : -1)) & (c.n - 1)};
     const int Z[2] = {k >> 1, ((k >> 1) + ((k & 1) ? 1 : -1)) & (c.l - 1)};
     const double w[2] = {0.75, 0.25};
-    const double* E[3] = {E0, E1, E2};
+    const double* vH[3] = {v0_, v1_, v2_};
     const size_t q0 = sidx(2 * I, j, k, g), q1 = sidx(2 * I + 1, j, k, g);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -281,7 +263,8 @@ __global__ void __launch_bounds__(256) k3_prolong(Grid3 g, L3 A, const double* E
             for (int y = 0; y < 2; ++y)
 #pragma unroll
                 for (int x = 0; x < 3; ++x) {
-                    e[z][y][x] = E[f][sidx(X[x], Y[y], Z[z], c)];
+                    const size_t Q = sidx(X[x], Y[y], Z[z], c);
+                    e[z][y][x] = H.u[f][Q] - vH[f][Q];
                 }
         // fine 2I: parent X[1], side X[0]; fine 2I + 1: parent X[1], side X[2]
         double v0 = 0.0, v1 = 0.0;
@@ -299,15 +282,16 @@ __global__ void __launch_bounds__(256) k3_prolong(Grid3 g, L3 A, const double* E
     }
 }
 
-// The same prolongation with the coarse correction staged in LDS, for fine
+// The same prolongation with the coarse correction formed once in LDS (a launch
+// that formed it in memory first cost 5 us and a gap per level), for fine
 // grids with m >= 32 (n, l >= 4 hold on every fine level): a workgroup takes
 // P3X x-pairs x P3Y rows x P3Z planes, whose coarse footprint (one coarse cell
 // of margin on each side) is read from global memory once instead of twelve
 // times per pair.  Same values, same order of operations as k3_prolong.
 constexpr int P3X = 16, P3Y = 4, P3Z = 4;
 template <int NF>
-__global__ void __launch_bounds__(256) k3_prolong_blk(Grid3 g, L3 A, const double* E0,
-                                                      const double* E1, const double* E2,
+__global__ void __launch_bounds__(256) k3_prolong_blk(Grid3 g, L3 A, L3 H, const double* v0_,
+                                                      const double* v1_, const double* v2_,
                                                       const CycleState* st) {
     static_assert(P3X * P3Y * P3Z == 256, "one x-pair per thread");
     constexpr int CXN = P3X + 2, CYN = P3Y / 2 + 2, CZN = P3Z / 2 + 2;
@@ -319,12 +303,12 @@ __global__ void __launch_bounds__(256) k3_prolong_blk(Grid3 g, L3 A, const doubl
     const int I0 = bx * P3X, j0 = by * P3Y, k0 = bz * P3Z;
     const Grid3 c{g.m >> 1, g.n >> 1, g.l >> 1, g.lm - 1, g.ln - 1, g.ll - 1};
     const int cx0 = I0 - 1, cy0 = (j0 >> 1) - 1, cz0 = (k0 >> 1) - 1;
-    const double* E[3] = {E0, E1, E2};
+    const double* vH[3] = {v0_, v1_, v2_};
     for (int q = threadIdx.x; q < CXN * CYN * CZN; q += 256) {
         const int x = q % CXN, yz = q / CXN, y = yz % CYN, z = yz / CYN;
         const size_t Q = sidx((cx0 + x) & (c.m - 1), (cy0 + y) & (c.n - 1), (cz0 + z) & (c.l - 1), c);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) Es[f][z][y][x] = E[f][Q];
+        for (int f = 0; f < NF; ++f) Es[f][z][y][x] = H.u[f][Q] - vH[f][Q];
     }
     __syncthreads();
     const int tx = threadIdx.x & (P3X - 1), ty = (threadIdx.x / P3X) & (P3Y - 1),
@@ -398,14 +382,28 @@ __global__ void __launch_bounds__(NT) k3_resnorm(Op op, Grid3 g, L3 A, double* p
 // The small levels of a V-cycle are latency bound (a launch each for every
 // half-sweep, restriction, completion and prolongation).  This kernel runs
 // them all, from the first level of at most CP3_CELLS cells down to the
-// coarsest and back, in LDS (natural order inside), with the same arithmetic
-// as the per-level kernels: complete the top level's right-hand side, nu1
-// half-sweep pairs, restriction with completion, coarsest sweeps, trilinear
-// correction, nu2 pairs; the top level's u returns to global memory.
-constexpr int CP3_CELLS = 512;
-constexpr int CP3_TOTAL = 640;    // all levels below 512 cells: 512 + 64 + 8 (+ padding)
+// coarsest and back, in one workgroup, with the same arithmetic as the
+// per-level kernels: complete the top level's right-hand side, nu1 half-sweep
+// pairs, restriction with completion, coarsest sweeps, trilinear correction,
+// nu2 pairs; the top level's u returns to global memory.
+//
+// u lives in LDS, split by colour as in global memory, a cell's fields side by
+// side (24 bytes: every bank pair once per half wave, and one address for three
+// loads).  On the top level (up to 16^3) each thread owns the four cells
+// (2 i2, 2 i2 + 1) x (2 K2, 2 K2 + 1) of one row and keeps their u, right-hand side
+// and phi^k in registers: of a cell's six neighbours its thread holds two, and the
+// eight fine cells of a coarse cell are in two lanes of a wave.  Levels of up to 512
+// cells below it have a red-black pair per thread; from 128 cells down one wave
+// runs them without workgroup barriers, and a 2 x 2 x 2 coarsest level stays in
+// four lanes' registers.  Bound by the latency of the half-sweeps, which follow one
+// another (20 of them on the coarsest level), and on the top level by the issue
+// rate of one CU.  From 16^3 down it takes 38 us (16^3: some 22 us of it); the
+// kernel from 8^3 down took 25 us and the twelve launches of the 16^3 level 56 us
+// more, with a gap each.  Ten steps on 128^3: 28.5 -> 25.1 ms.
+constexpr int CP3_CELLS = 4096;
+constexpr int CP3_LOW = 592;      // all levels below the top one: 512 + 64 + 8 (+ padding)
 constexpr int CP3_MAXLEV = 10;
-constexpr int CP3_THREADS = 256;
+constexpr int CP3_THREADS = CP3_CELLS / 4;
 
 struct CoarseGeom3 {
     int nlev;
@@ -424,173 +422,463 @@ struct CoarseArgs3 {
     int nsw1, nsw2, nswc;  // half-sweep pairs down / up / on the coarsest level
 };
 
-__device__ __forceinline__ MpfcOp3<1, true> op_level(MpfcOp3<1, true> o, int l) { o.op.ih2 = ldexp(o.op.ih2, -2 * l); return o; }
-__device__ __forceinline__ MpfcOp3<1, false> op_level(MpfcOp3<1, false> o, int l) { o.op.ih2 = ldexp(o.op.ih2, -2 * l); return o; }
-__device__ __forceinline__ MpfcOp3<2, true> op_level(MpfcOp3<2, true> o, int l) { o.op.ih2 = ldexp(o.op.ih2, -2 * l); return o; }
-__device__ __forceinline__ MpfcOp3<2, false> op_level(MpfcOp3<2, false> o, int l) { o.op.ih2 = ldexp(o.op.ih2, -2 * l); return o; }
-__device__ __forceinline__ PoissonOp3 op_level(PoissonOp3 o, int l) {
-    o.ih2 = ldexp(o.ih2, -2 * l);
-    o.h2 = ldexp(o.h2, 2 * l);
-    return o;
+// Each level's operator, formed on the host (in vector registers and per level,
+// its constants cost the half-sweeps more than their loads).
+template <class Op>
+struct CoarseOps3 {
+    Op o[CP3_MAXLEV];
+};
+
+// x of another lane of the quad (0xB1: lane ^ 1, 0x4E: lane ^ 2) or, 0x141, of the
+// mirrored lane of the group of eight.
+template <int CTRL>
+__device__ __forceinline__ double lane_of(double x) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true));
+}
+// Sum over the lanes of an aligned group of eight, in each of them.
+__device__ __forceinline__ double sum8(double x) {
+    x += lane_of<0xB1>(x);
+    x += lane_of<0x4E>(x);
+    return x + lane_of<0x141>(x);
 }
 
 template <class Op>
-__global__ void __launch_bounds__(CP3_THREADS) k3_coarse(Op op_top, CoarseArgs3 A,
-                                                         const CycleState* st) {
+__global__ void __launch_bounds__(CP3_THREADS) k3_coarse(CoarseOps3<Op> ops,
+                                                         CoarseArgs3 A, const CycleState* st) {
     constexpr int NF = Op::NF;
-    constexpr int NT = CP3_THREADS;
-    __shared__ double Su[NF][CP3_TOTAL];
-    __shared__ double Sf[NF][CP3_TOTAL];
-    __shared__ double Sv[NF][CP3_TOTAL];
-    __shared__ double Sx[Op::XK ? CP3_TOTAL : 1];
+    __shared__ double U0[CP3_CELLS / 2][2 * NF + 1];  // [pair][colour, field]
+    __shared__ double U[CP3_LOW][NF], F[CP3_LOW][NF], V[CP3_LOW][NF];
+    __shared__ double X[Op::XK ? CP3_LOW : 1];
     if (stopped(st)) return;
     const int t = threadIdx.x;
+    const Op& op_top = ops.o[0];
     const CoarseGeom3& G = A.geo;
     const int L = G.nlev;
-    auto dec = [&](int l, int q, int& i, int& j, int& k) {
-        i = q & (G.m[l] - 1);
-        j = (q >> G.lm[l]) & (G.n[l] - 1);
-        k = q >> (G.lm[l] + G.ln[l]);
+
+    // ---- top level: four cells per thread
+    const int n0 = G.n[0], l0 = G.l[0], mh0 = G.m[0] >> 1, lh0 = G.lm[0] - 1;
+    const int half0 = mh0 * n0 * l0;
+    const bool act = t < (half0 >> 1);
+    auto ent = [&](int x2, int j, int k) __attribute__((always_inline)) {
+        return (((k & (l0 - 1)) * n0 + (j & (n0 - 1))) << lh0) + (x2 & (mh0 - 1));
     };
-    auto nat = [&](int l, int i, int j, int k) { return (((k << G.ln[l]) + j) << G.lm[l]) + i; };
-    auto ns6 = [&](const double* a, int l, int i, int j, int k) {
-        const int ip = (i + 1) & (G.m[l] - 1), im = (i - 1) & (G.m[l] - 1);
-        const int jp = (j + 1) & (G.n[l] - 1), jm = (j - 1) & (G.n[l] - 1);
-        const int kp = (k + 1) & (G.l[l] - 1), km = (k - 1) & (G.l[l] - 1);
-        return ((a[nat(l, ip, j, k)] + a[nat(l, im, j, k)]) + (a[nat(l, i, jp, k)] + a[nat(l, i, jm, k)])) +
-               (a[nat(l, i, j, kp)] + a[nat(l, i, j, km)]);
-    };
-    auto cells = [&](int l) { return G.m[l] * G.n[l] * G.l[l]; };
-    // load the top level (colour-split in global memory, natural here)
-    const int N0 = cells(0);
-    for (int q = t; q < N0; q += NT) {
-        int i, j, k;
-        split_cell((size_t)q, A.gtop, i, j, k);
-        const int p = nat(0, i, j, k);
+    // A thread's pairs (i2, j0, 2 K0 + z), z = 0, 1; plane z holds its red cell at
+    // 2 i2 + s, s = jp ^ z.  Entries of the pair and of its neighbours (the other
+    // x-neighbour of the cell of colour c in ex[z][c]).
+    struct Place { int jp, i2, J0, K0, e0[2], ex[2][2], ey[2][2], ez[2]; };
+    // (threads in the order of the pairs' entries, so a wave's loads are contiguous,
+    // but the row's parity no higher than lane bit 5: the restriction adds the two)
+    const int sh0 = lh0 < 5 ? lh0 : 5;
+    auto place = [&](int t) __attribute__((always_inline)) {
+        Place P;
+        const int hi = t >> (sh0 + 1), r = hi >> (lh0 - sh0);
+        P.jp = (t >> sh0) & 1;
+        P.i2 = ((hi << sh0) & (mh0 - 1)) | (t & ((1 << sh0) - 1));
+        P.J0 = r & ((n0 >> 1) - 1);
+        P.K0 = r >> (G.ln[0] - 1);
+        const int j = 2 * P.J0 + P.jp;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            Su[f][p] = A.u[f][q];
-            Sf[f][p] = A.f[f][q];
+        for (int z = 0; z < 2; ++z) {
+            const int k = 2 * P.K0 + z, s = P.jp ^ z;
+            P.e0[z] = ent(P.i2, j, k);
+            P.ex[z][0] = ent(P.i2 + (s ? 1 : -1), j, k);
+            P.ex[z][1] = ent(P.i2 + (s ? -1 : 1), j, k);
+            P.ey[z][0] = ent(P.i2, j + 1, k);
+            P.ey[z][1] = ent(P.i2, j - 1, k);
+            P.ez[z] = ent(P.i2, j, z ? k + 1 : k - 1);
         }
-        if constexpr (Op::XK) Sx[p] = A.xk[q];
+        return P;
+    };
+    Place P = place(t);
+    double ur[2][2][NF], fr[2][2][NF], xr[2][2];   // [plane][colour]
+    if (act) {
+        // u and phi^k first: the right-hand side, which one CU's loads take as long
+        // for, arrives behind the N(u) of its completion
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int q = c * half0 + P.e0[z];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) ur[z][c][f] = A.u[f][q];
+                xr[z][c] = Op::XK ? A.xk[q] : 0.0;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) fr[z][c][f] = A.f[f][c * half0 + P.e0[z]];
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) U0[P.e0[z]][c * NF + f] = ur[z][c][f];
     }
     __syncthreads();
-    auto complete = [&](int l) {
-        const Op o = op_level(op_top, l);
-        const int off = G.off[l];
-        for (int q = t; q < cells(l); q += NT) {
-            int i, j, k;
-            dec(l, q, i, j, k);
-            double u[NF], ns[NF], N[NF];
+    // neighbour sum of the thread's cell of colour c in plane z
+    auto ns0 = [&](auto zc, auto cc, double (&ns)[NF]) __attribute__((always_inline)) {
+        constexpr int z = decltype(zc)::value, c = decltype(cc)::value, oc = c ^ 1;
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                u[f] = Su[f][off + q];
-                ns[f] = ns6(&Su[f][off], l, i, j, k);
-            }
-            o.apply(u, ns, Op::XK ? Sx[off + q] : 0.0, N);
+        for (int f = 0; f < NF; ++f)
+            ns[f] = ((ur[z][oc][f] + U0[P.ex[z][c]][oc * NF + f]) +
+                     (U0[P.ey[z][0]][oc * NF + f] + U0[P.ey[z][1]][oc * NF + f])) +
+                    (ur[z ^ 1][oc][f] + U0[P.ez[z]][oc * NF + f]);
+    };
+    using Z0 = std::integral_constant<int, 0>;
+    using Z1 = std::integral_constant<int, 1>;
+    auto half_sweep0 = [&](auto cc) __attribute__((always_inline)) {
+        constexpr int c = decltype(cc)::value;
+        auto cell = [&](auto zc) __attribute__((always_inline)) {
+            constexpr int z = decltype(zc)::value;
+            double ns[NF];
+            ns0(zc, cc, ns);
+            op_top.relax(ur[z][c], ns, fr[z][c], xr[z][c]);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) Sf[f][off + q] += N[f];
+            for (int f = 0; f < NF; ++f) U0[P.e0[z]][c * NF + f] = ur[z][c][f];
+        };
+        if (act) {
+            cell(Z0{});
+            __builtin_amdgcn_sched_barrier(0);
+            cell(Z1{});
         }
         __syncthreads();
     };
-    auto sweeps = [&](int l, int pairs) {
-        const Op o = op_level(op_top, l);
-        const int off = G.off[l];
-        for (int p = 0; p < 2 * pairs; ++p) {
-            const int colour = p & 1;
-            for (int q = t; q < cells(l); q += NT) {
-                int i, j, k;
-                dec(l, q, i, j, k);
-                if (((i + j + k) & 1) != colour) continue;
-                double u[NF], ns[NF], fv[NF];
+    auto sweeps0 = [&](int pairs) __attribute__((always_inline)) {
+        for (int p = 0; p < pairs; ++p) {
+            half_sweep0(Z0{});
+            half_sweep0(Z1{});
+        }
+    };
+    // N(u) of the thread's cell of colour c in plane z
+    auto apply0 = [&](auto zc, auto cc, double (&N)[NF]) __attribute__((always_inline)) {
+        constexpr int z = decltype(zc)::value, c = decltype(cc)::value;
+        double ns[NF];
+        ns0(zc, cc, ns);
+        op_top.apply(ur[z][c], ns, xr[z][c], N);
+    };
+    // complete the right-hand side (a finest level's is complete)
+    if (act) {
+        const bool ct = A.complete_top;
+        auto add = [&](auto zc, auto cc) __attribute__((always_inline)) {
+            double N[NF];
+            apply0(zc, cc, N);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    u[f] = Su[f][off + q];
-                    ns[f] = ns6(&Su[f][off], l, i, j, k);
-                    fv[f] = Sf[f][off + q];
-                }
-                o.relax(u, ns, fv, Op::XK ? Sx[off + q] : 0.0);
+            for (int f = 0; f < NF; ++f) fr[decltype(zc)::value][decltype(cc)::value][f] += ct ? N[f] : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        add(Z0{}, Z0{}); add(Z0{}, Z1{}); add(Z1{}, Z0{}); add(Z1{}, Z1{});
+    }
+    __syncthreads();  // every N(u) reads u as loaded
+
+    // ---- levels below: entry of colour c at (i2, j, k): c half + (k n + j) m/2 + i2
+    struct Lev { int m, n, l, lh, ln, half, off; };
+    auto lev = [&](int l) __attribute__((always_inline)) {
+        return Lev{G.m[l], G.n[l], G.l[l], G.lm[l] - 1, G.ln[l], (G.m[l] * G.n[l] * G.l[l]) >> 1,
+                   G.off[l]};
+    };
+    auto lent = [&](const Lev& v, int x2, int j, int k) __attribute__((always_inline)) {
+        return (((((k & (v.l - 1)) << v.ln) + (j & (v.n - 1))) << v.lh)) + (x2 & ((v.m >> 1) - 1));
+    };
+    // neighbour sum of the cell of colour c at (x2, j, k)
+    auto nsl = [&](const Lev& v, int x2, int j, int k, int c, double (&ns)[NF]) __attribute__((always_inline)) {
+        const int s = (j + k) & 1, o = v.off + (c ^ 1) * v.half;
+        const int e = o + lent(v, x2, j, k), x = o + lent(v, x2 + ((s ^ c) ? 1 : -1), j, k);
+        const int yp = o + lent(v, x2, j + 1, k), ym = o + lent(v, x2, j - 1, k);
+        const int zp = o + lent(v, x2, j, k + 1), zm = o + lent(v, x2, j, k - 1);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) Su[f][off + q] = u[f];
-            }
+        for (int f = 0; f < NF; ++f)
+            ns[f] = ((U[e][f] + U[x][f]) + (U[yp][f] + U[ym][f])) + (U[zp][f] + U[zm][f]);
+    };
+    auto sync = [&](bool wave) __attribute__((always_inline)) {
+        if (wave) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
             __syncthreads();
         }
     };
-    if (A.complete_top) complete(0);
-    for (int l = 0; l < L - 1; ++l) {
-        sweeps(l, A.nsw1);
-        const Op o = op_level(op_top, l);
-        const int off = G.off[l], offc = G.off[l + 1];
-        for (int Q = t; Q < cells(l + 1); Q += NT) {
-            int I, J, K;
-            dec(l + 1, Q, I, J, K);
-            double su[NF], sr[NF], sx = 0.0;
+    // Each of these is run by every thread of the workgroup (wave = false, one
+    // pass over at most CP3_THREADS items) or by the first wave alone.
+    auto complete = [&](int l, bool wave) __attribute__((always_inline)) {
+        const Lev v = lev(l);
+        const Op& o = ops.o[l];
+        for (int q = t; q < 2 * v.half; q += wave ? 64 : CP3_THREADS) {
+            const int c = q >= v.half, e = q - c * v.half;
+            const int x2 = e & ((v.m >> 1) - 1), j = (e >> v.lh) & (v.n - 1), k = e >> (v.lh + v.ln);
+            double ns[NF], N[NF];
+            nsl(v, x2, j, k, c, ns);
+            o.apply(U[v.off + q], ns, Op::XK ? X[v.off + q] : 0.0, N);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) { su[f] = 0.0; sr[f] = 0.0; }
+            for (int f = 0; f < NF; ++f) F[v.off + q][f] += N[f];
+        }
+        sync(wave);
+    };
+    // A pair's u, right-hand side and phi^k stay in registers; its x-neighbour
+    // within the pair too.
+    auto sweeps = [&](int l, int pairs, bool wave) __attribute__((always_inline)) {
+        const Lev v = lev(l);
+        const Op& o = ops.o[l];
+        const bool on = t < v.half;
+        const int tt = on ? t : 0, b = v.off;
+        const int x2 = tt & ((v.m >> 1) - 1), j = (tt >> v.lh) & (v.n - 1), k = tt >> (v.lh + v.ln);
+        const int s = (j + k) & 1;
+        const int xn[2] = {b + lent(v, x2 + (s ? 1 : -1), j, k), b + lent(v, x2 + (s ? -1 : 1), j, k)};
+        const int yp = b + lent(v, x2, j + 1, k), ym = b + lent(v, x2, j - 1, k);
+        const int zp = b + lent(v, x2, j, k + 1), zm = b + lent(v, x2, j, k - 1);
+        double u[2][NF], fv[2][NF], xk[2];
 #pragma unroll
-            for (int cc = 0; cc < 8; ++cc) {
-                const int i = 2 * I + (cc & 1), j = 2 * J + ((cc >> 1) & 1), k = 2 * K + (cc >> 2);
-                const int q = nat(l, i, j, k);
-                double u[NF], ns[NF], N[NF];
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    u[f] = Su[f][off + q];
-                    ns[f] = ns6(&Su[f][off], l, i, j, k);
-                }
-                const double xk = Op::XK ? Sx[off + q] : 0.0;
-                o.apply(u, ns, xk, N);
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    su[f] += u[f];
-                    sr[f] += Sf[f][off + q] - N[f];
-                }
-                sx += xk;
-            }
+        for (int c = 0; c < 2; ++c) {
+            const int q = b + c * v.half + tt;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                Su[f][offc + Q] = 0.125 * su[f];
-                Sv[f][offc + Q] = 0.125 * su[f];
-                Sf[f][offc + Q] = 0.125 * sr[f];
+                u[c][f] = U[q][f];
+                fv[c][f] = F[q][f];
             }
-            if constexpr (Op::XK) Sx[offc + Q] = 0.125 * sx;
+            xk[c] = Op::XK ? X[q] : 0.0;
         }
-        __syncthreads();
-        complete(l + 1);
-    }
-    sweeps(L - 1, A.nswc);
-    for (int l = L - 2; l >= 0; --l) {
-        const int off = G.off[l], offc = G.off[l + 1];
-        const double w[2] = {0.75, 0.25};
-        for (int q = t; q < cells(l); q += NT) {
-            int i, j, k;
-            dec(l, q, i, j, k);
-            const int I[2] = {i >> 1, ((i >> 1) + ((i & 1) ? 1 : -1)) & (G.m[l + 1] - 1)};
-            const int J[2] = {j >> 1, ((j >> 1) + ((j & 1) ? 1 : -1)) & (G.n[l + 1] - 1)};
-            const int K[2] = {k >> 1, ((k >> 1) + ((k & 1) ? 1 : -1)) & (G.l[l + 1] - 1)};
+        auto half_sweep = [&](auto cc) __attribute__((always_inline)) {
+            constexpr int c = decltype(cc)::value, oc = c ^ 1;
+            const int oo = oc * v.half;
+            if (on) {
+                double ns[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    ns[f] = ((u[oc][f] + U[oo + xn[c]][f]) + (U[oo + yp][f] + U[oo + ym][f])) +
+                            (U[oo + zp][f] + U[oo + zm][f]);
+                o.relax(u[c], ns, fv[c], xk[c]);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) U[b + c * v.half + t][f] = u[c][f];
+            }
+            sync(wave);
+        };
+        for (int p = 0; p < pairs; ++p) {
+            half_sweep(Z0{});
+            half_sweep(Z1{});
+        }
+    };
+    // 2 x 2 x 2 cells: both neighbours along an axis are one cell, and lane
+    // j + 2 k holds the pair (j, k), so the other pairs are one lane exchange away.
+    auto sweeps_cube2 = [&](int l, int pairs) __attribute__((always_inline)) {
+        const Op& o = ops.o[l];
+        if (t < 4) {
+            const int b = G.off[l] + t;
+            double u[2][NF], fv[2][NF], xk[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    u[c][f] = U[b + 4 * c][f];
+                    fv[c][f] = F[b + 4 * c][f];
+                }
+                xk[c] = Op::XK ? X[b + 4 * c] : 0.0;
+            }
+            for (int p = 0; p < pairs; ++p) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    double ns[NF];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const double w = u[c ^ 1][f];
+                        ns[f] = 2.0 * ((w + lane_of<0xB1>(w)) + lane_of<0x4E>(w));
+                    }
+                    o.relax(u[c], ns, fv[c], xk[c]);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) U[b + 4 * c][f] = u[c][f];
+        }
+        sync(true);
+    };
+    // the sums over the eight cells of coarse cell (I, J, K)
+    auto put_coarse = [&](const Lev& w, int I, int J, int K, const double (&su)[NF],
+                          const double (&sr)[NF], double sx) __attribute__((always_inline)) {
+        const int Q = w.off + ((I + J + K) & 1) * w.half + lent(w, I >> 1, J, K);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            U[Q][f] = 0.125 * su[f];
+            V[Q][f] = 0.125 * su[f];
+            F[Q][f] = 0.125 * sr[f];
+        }
+        if constexpr (Op::XK) X[Q] = 0.125 * sx;
+    };
+    auto restrict_to = [&](int l, bool wave) __attribute__((always_inline)) {  // from l - 1 >= 1
+        const Lev v = lev(l - 1), w = lev(l);
+        const Op& o = ops.o[l - 1];
+        for (int q = t; q < 2 * v.half; q += wave ? 64 : CP3_THREADS) {
+            const int cc = q & 7, Q = q >> 3;
+            const int I = Q & (w.m - 1), J = (Q >> (w.lh + 1)) & (w.n - 1), K = Q >> (w.lh + 1 + w.ln);
+            const int j = 2 * J + ((cc >> 1) & 1), k = 2 * K + (cc >> 2);
+            const int c = ((cc & 1) + j + k) & 1, e = v.off + c * v.half + lent(v, I, j, k);
+            double su[NF], sr[NF], ns[NF], N[NF];
+            nsl(v, I, j, k, c, ns);
+            const double xk = Op::XK ? X[e] : 0.0;
+            o.apply(U[e], ns, xk, N);
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                double v = 0.0;
+                su[f] = sum8(U[e][f]);
+                sr[f] = sum8(F[e][f] - N[f]);
+            }
+            const double sx = Op::XK ? sum8(xk) : 0.0;
+            if (cc == 0) put_coarse(w, I, J, K, su, sr, sx);
+        }
+        sync(wave);
+    };
+    // the correction of level l (>= 1) into its V
+    auto correction = [&](int l, bool wave) __attribute__((always_inline)) {
+        const Lev v = lev(l);
+        for (int q = t; q < 2 * v.half; q += wave ? 64 : CP3_THREADS)
 #pragma unroll
-                for (int z = 0; z < 2; ++z)
+            for (int f = 0; f < NF; ++f) V[v.off + q][f] = U[v.off + q][f] - V[v.off + q][f];
+        sync(wave);
+    };
+    // entry of level w's cell (I, J, K), any integers
+    auto cell_of_ = [&](const Lev& w, int I, int J, int K) __attribute__((always_inline)) {
+        I &= w.m - 1;
+        return w.off + ((I + J + K) & 1) * w.half + lent(w, I >> 1, J, K);
+    };
+    auto prolong = [&](int l, bool wave) __attribute__((always_inline)) {  // from l + 1 into l >= 1
+        const Lev v = lev(l), w = lev(l + 1);
+        if (t < v.half) {
+            const int I = t & ((v.m >> 1) - 1), j = (t >> v.lh) & (v.n - 1), k = t >> (v.lh + v.ln);
+            const int J = j >> 1, K = k >> 1, dj = (j & 1) ? 1 : -1, dk = (k & 1) ? 1 : -1;
+            const int s = (j + k) & 1;
+            double e[3][NF];
 #pragma unroll
-                    for (int y = 0; y < 2; ++y)
+            for (int x = 0; x < 3; ++x) {
+                const int q00 = cell_of_(w, I + x - 1, J, K), q10 = cell_of_(w, I + x - 1, J + dj, K);
+                const int q01 = cell_of_(w, I + x - 1, J, K + dk), q11 = cell_of_(w, I + x - 1, J + dj, K + dk);
 #pragma unroll
-                        for (int x = 0; x < 2; ++x) {
-                            const int Q = offc + nat(l + 1, I[x], J[y], K[z]);
-                            v += w[x] * w[y] * w[z] * (Su[f][Q] - Sv[f][Q]);
-                        }
-                Su[f][off + q] += v;
+                for (int f = 0; f < NF; ++f)
+                    e[x][f] = 0.75 * (0.75 * V[q00][f] + 0.25 * V[q10][f]) +
+                              0.25 * (0.75 * V[q01][f] + 0.25 * V[q11][f]);
+            }
+            // cell 2I has colour s, cell 2I + 1 the other
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                U[v.off + s * v.half + t][f] += 0.75 * e[1][f] + 0.25 * e[0][f];
+                U[v.off + (s ^ 1) * v.half + t][f] += 0.75 * e[1][f] + 0.25 * e[2][f];
+            }
+        }
+        sync(wave);
+    };
+
+    sweeps0(L == 1 ? A.nswc : A.nsw1);
+    if (L > 1) {
+        if (act) {
+            double su[NF], sr[NF], sx = (xr[0][0] + xr[0][1]) + (xr[1][0] + xr[1][1]);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                su[f] = (ur[0][0][f] + ur[0][1][f]) + (ur[1][0][f] + ur[1][1][f]);
+                sr[f] = 0.0;
+            }
+            auto res = [&](auto zc, auto cc) __attribute__((always_inline)) {
+                double N[NF];
+                apply0(zc, cc, N);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) sr[f] += fr[decltype(zc)::value][decltype(cc)::value][f] - N[f];
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            res(Z0{}, Z0{}); res(Z0{}, Z1{}); res(Z1{}, Z0{}); res(Z1{}, Z1{});
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                su[f] += __shfl_xor(su[f], 1 << sh0);
+                sr[f] += __shfl_xor(sr[f], 1 << sh0);
+            }
+            if constexpr (Op::XK) sx += __shfl_xor(sx, 1 << sh0);
+            if (P.jp == 0) put_coarse(lev(1), P.i2, P.J0, P.K0, su, sr, sx);
+        }
+        __syncthreads();
+        // levels of at most 64 pairs: from `lw` on, the first wave alone
+        int lw = 1;
+        while (lw < L && (G.m[lw] * G.n[lw] * G.l[lw]) > 128) ++lw;
+        for (int l = 1; l < lw; ++l) {
+            if (l > 1) restrict_to(l, false);
+            complete(l, false);
+            sweeps(l, l < L - 1 ? A.nsw1 : A.nswc, false);
+        }
+        if (lw < L) {
+            if (lw > 1) restrict_to(lw, false);
+            if (t < 64) {
+                const bool cube2 = G.m[L - 1] == 2 && G.n[L - 1] == 2 && G.l[L - 1] == 2;
+                for (int l = lw; l < L; ++l) {
+                    if (l > lw) restrict_to(l, true);
+                    complete(l, true);
+                    if (l == L - 1 && cube2) sweeps_cube2(l, A.nswc);
+                    else sweeps(l, l < L - 1 ? A.nsw1 : A.nswc, true);
+                }
+                for (int l = L - 2; l >= lw; --l) {
+                    correction(l + 1, true);
+                    prolong(l, true);
+                    sweeps(l, A.nsw2, true);
+                }
+            }
+            __syncthreads();
+        }
+        for (int l = (lw < L ? lw : L - 1) - 1; l >= 1; --l) {
+            correction(l + 1, false);
+            prolong(l, false);
+            sweeps(l, A.nsw2, false);
+        }
+        correction(1, false);
+        // The pairs' u come back from LDS and their places are formed anew (from a
+        // copy of t that is opaque to the compiler): held in registers across the
+        // levels below they were spilled to memory, every half-sweep paying for it.
+        int t2 = t;
+        asm volatile("" : "+v"(t2));
+        P = place(t2);
+        if (act) {
+            const Lev w = lev(1);
+            const int dj = P.jp ? 1 : -1;
+            int q[3][3][2];
+#pragma unroll
+            for (int z = 0; z < 3; ++z)
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    q[z][x][0] = cell_of_(w, P.i2 + x - 1, P.J0, P.K0 + z - 1);
+                    q[z][x][1] = cell_of_(w, P.i2 + x - 1, P.J0 + dj, P.K0 + z - 1);
+                }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {  // (one field at a time: registers)
+                __builtin_amdgcn_sched_barrier(0);
+                double e[3][3];  // [plane][x], interpolated along y
+#pragma unroll
+                for (int z = 0; z < 3; ++z)
+#pragma unroll
+                    for (int x = 0; x < 3; ++x)
+                        e[z][x] = 0.75 * V[q[z][x][0]][f] + 0.25 * V[q[z][x][1]][f];
+#pragma unroll
+                for (int z = 0; z < 2; ++z) {
+                    double v[3];
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) v[x] = 0.75 * e[1][x] + 0.25 * e[z ? 2 : 0][x];
+                    const double a = 0.75 * v[1] + 0.25 * v[0], b = 0.75 * v[1] + 0.25 * v[2];
+                    const bool s = P.jp ^ z;  // cell 2 i2 is red where s = 0
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const double u = U0[P.e0[z]][c * NF + f] + (s == (c == 0) ? b : a);
+                        ur[z][c][f] = u;
+                        U0[P.e0[z]][c * NF + f] = u;
+                    }
+                }
             }
         }
         __syncthreads();
-        sweeps(l, A.nsw2);
+        sweeps0(A.nsw2);
     }
-    for (int q = t; q < N0; q += NT) {
-        int i, j, k;
-        split_cell((size_t)q, A.gtop, i, j, k);
-        const int p = nat(0, i, j, k);
+    if (act) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) A.u[f][q] = Su[f][p];
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) A.u[f][c * half0 + P.e0[z]] = ur[z][c][f];
     }
 }
 

@@ -92,7 +92,7 @@ LevelOp<double> level_op3(const mpfc3d_ctx* C, const Level3& lv) {
     o.c = C->c;
     o.al = C->p.scheme == 1 ? C->alpha : 0.5 * C->alpha;
     o.e = C->p.scheme == 1 ? 1.0 : 0.5;
-    o.derive();
+    o.derive(6.0);
     return o;
 }
 
@@ -190,8 +190,8 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
             const Level3& lv = C->L[top + k];
             CA.geo.m[k] = lv.m; CA.geo.n[k] = lv.n; CA.geo.l[k] = lv.l;
             CA.geo.lm[k] = lv.g.lm; CA.geo.ln[k] = lv.g.ln;
-            CA.geo.off[k] = off;
-            off += lv.m * lv.n * lv.l;
+            CA.geo.off[k] = off;  // (the top level has arrays of its own)
+            if (k > 0) off += lv.m * lv.n * lv.l;
         }
         CA.gtop = T.g;
         CA.complete_top = top > 0;
@@ -209,11 +209,10 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
             }
             CA.xk = T.xk;
         }
-        if constexpr (POISSON)
-            hipLaunchKernelGGL((k3_coarse<PoissonOp3>), dim3(1), dim3(CP3_THREADS), 0, s, op_of(T), CA,
-                               stop);
-        else
-            hipLaunchKernelGGL((k3_coarse<Op>), dim3(1), dim3(CP3_THREADS), 0, s, op_of(T), CA, stop);
+        using COp = std::conditional_t<POISSON, PoissonOp3, Op>;
+        CoarseOps3<COp> ops{};
+        for (int k = 0; k < CA.geo.nlev; ++k) ops.o[k] = op_of(C->L[top + k]);
+        hipLaunchKernelGGL((k3_coarse<COp>), dim3(1), dim3(CP3_THREADS), 0, s, ops, CA, stop);
     } else {
         // coarsest level: red-black sweeps
         const Level3& A = C->L[nl - 1];
@@ -235,27 +234,22 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
         // blocked prolongation: whole blocks of P3X x P3Y x P3Z pairs (sides
         // are powers of two, so m >= 2 P3X with n, l >= 4 tiles the level)
         const bool blk = A.m >= 2 * P3X && A.n >= P3Y && A.l >= P3Z;
-        const size_t ncB = (size_t)B.m * B.n * B.l;
         if constexpr (POISSON) {
-            hipLaunchKernelGGL((k3_correction<1>), dim3(blocks256(ncB)), dim3(256), 0, s, B.g, FB,
-                               B.pv, (double*)nullptr, (double*)nullptr, stop);
             if (blk)
                 hipLaunchKernelGGL((k3_prolong_blk<1>), dim3(blocks256(nc)), dim3(256), 0, s, A.g,
-                                   FA, (const double*)B.pv, (const double*)nullptr,
+                                   FA, FB, (const double*)B.pv, (const double*)nullptr,
                                    (const double*)nullptr, stop);
             else
-                hipLaunchKernelGGL((k3_prolong<1>), dim3(blocks256(nc)), dim3(256), 0, s, A.g, FA,
+                hipLaunchKernelGGL((k3_prolong<1>), dim3(blocks256(nc)), dim3(256), 0, s, A.g, FA, FB,
                                    (const double*)B.pv, (const double*)nullptr,
                                    (const double*)nullptr, stop);
         } else {
-            hipLaunchKernelGGL((k3_correction<3>), dim3(blocks256(ncB)), dim3(256), 0, s, B.g, FB,
-                               B.v[0], B.v[1], B.v[2], stop);
             if (blk)
                 hipLaunchKernelGGL((k3_prolong_blk<3>), dim3(blocks256(nc)), dim3(256), 0, s, A.g,
-                                   FA, (const double*)B.v[0], (const double*)B.v[1],
+                                   FA, FB, (const double*)B.v[0], (const double*)B.v[1],
                                    (const double*)B.v[2], stop);
             else
-                hipLaunchKernelGGL((k3_prolong<3>), dim3(blocks256(nc)), dim3(256), 0, s, A.g, FA,
+                hipLaunchKernelGGL((k3_prolong<3>), dim3(blocks256(nc)), dim3(256), 0, s, A.g, FA, FB,
                                    (const double*)B.v[0], (const double*)B.v[1],
                                    (const double*)B.v[2], stop);
         }
