@@ -154,12 +154,64 @@ __global__ void __launch_bounds__(256) k3_relax(Op op, Grid3 g, L3 A, int colour
     for (int f = 0; f < NF; ++f) A.u[f][q] = u[f];
 }
 
-// Residual r = f - N(u) at the eight fine cells of each coarse cell and the
-// 2x2x2 averages of u (into uH and vH), r (rH) and, if xkH is set, phi^k.
-// One thread per coarse cell, in natural coarse order: the two fine cells of a
-// coarse cell along x (one per colour) sit at the same offset of the two
-// halves, so consecutive threads read consecutive fine entries.  g is the fine
-// grid.
+// Residual r = f - N(u) at the eight cells of the 2x2x2 block (I, J, K) of g, in
+// turn to `cell(u, r, xk)`.  Of a cell's six neighbours three are in the block, so
+// a thread makes 32 loads of each field instead of 56, of both colours: the cells
+// (0, 0, 0) .. (1, 1, 1) have the colours of their parity, and the two cells of a
+// row sit at the same offset of the two halves, so consecutive threads read
+// consecutive entries.  (Restriction from 128^3: 32.0 -> 29.8 us, from 32^3 8.8 -> 7.2.)
+template <class Op, class Cell>
+__device__ __forceinline__ void block_residual3(const Op& op, const Grid3& g, const L3& A, int I,
+                                                int J, int K, Cell&& cell) {
+    constexpr int NF = Op::NF;
+    const size_t half = cells3(g) >> 1;
+    const int mh = g.m >> 1;
+    auto ent = [&](int x2, int j, int k) {
+        return ((((size_t)(k & (g.l - 1)) << g.ln) + (size_t)(j & (g.n - 1))) << (g.lm - 1)) +
+               (size_t)(x2 & (mh - 1));
+    };
+    double u[2][2][2][NF];  // [z][y][x]
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const size_t e = ent(I, 2 * J + y, 2 * K + z);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    u[z][y][x][f] = A.u[f][(((x + y + z) & 1) ? half : 0) + e];
+        }
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const int j = 2 * J + y, k = 2 * K + z;
+            const size_t e = ent(I, j, k), ey = ent(I, y ? j + 1 : j - 1, k),
+                         ez = ent(I, j, z ? k + 1 : k - 1);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const size_t ex = ent(x ? I + 1 : I - 1, j, k);
+                const size_t own = ((x + y + z) & 1) ? half : 0, oth = half - own;
+                double ns[NF], N[NF], r[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    const double* v = A.u[f] + oth;
+                    ns[f] = ((u[z][y][x ^ 1][f] + v[ex]) + (u[z][y ^ 1][x][f] + v[ey])) +
+                            (u[z ^ 1][y][x][f] + v[ez]);
+                }
+                const double xk = Op::XK ? A.xk[own + e] : 0.0;
+                op.apply(u[z][y][x], ns, xk, N);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) r[f] = A.f[f][own + e] - N[f];
+                cell(u[z][y][x], r, xk);
+            }
+        }
+}
+
+// Residual at the eight fine cells of each coarse cell and the 2x2x2 averages of
+// u (into uH and vH), r (rH) and, if xkH is set, phi^k.  One thread per coarse
+// cell, in natural coarse order.  g is the fine grid.
 template <class Op>
 __global__ void __launch_bounds__(256) k3_restrict(Op op, Grid3 g, L3 A, L3 H, double* vH0,
                                                    double* vH1, double* vH2, double* rH0,
@@ -177,25 +229,14 @@ __global__ void __launch_bounds__(256) k3_restrict(Op op, Grid3 g, L3 A, L3 H, d
     double su[NF], sr[NF], sxk = 0.0;
 #pragma unroll
     for (int f = 0; f < NF; ++f) { su[f] = 0.0; sr[f] = 0.0; }
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-        const int i = 2 * I + (cc & 1), j = 2 * J + ((cc >> 1) & 1), k = 2 * K + (cc >> 2);
-        const size_t q = sidx(i, j, k, g);
-        double u[NF], ns[NF], N[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            u[f] = A.u[f][q];
-            ns[f] = nsum6(A.u[f], i, j, k, g);
-        }
-        const double xk = Op::XK ? A.xk[q] : 0.0;
-        op.apply(u, ns, xk, N);
+    block_residual3(op, g, A, I, J, K, [&](const double* u, const double* r, double xk) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             su[f] += u[f];
-            sr[f] += A.f[f][q] - N[f];
+            sr[f] += r[f];
         }
         sxk += xk;
-    }
+    });
     double* vH[3] = {vH0, vH1, vH2};
     double* rH[3] = {rH0, rH1, rH2};
 #pragma unroll
@@ -345,34 +386,25 @@ __global__ void __launch_bounds__(256) k3_prolong_blk(Grid3 g, L3 A, L3 H, const
 }
 
 // Per-block sums of r^2 = (f - N(u))^2 over all fields (the stopping test;
-// k_norm_finalize / k_p_finalize turn them into the norm).
+// k_norm_finalize / k_p_finalize turn them into the norm): a 2x2x2 block per
+// thread, so that u of both colours is read by one XCD.  128^3: 22.8 us (5.2 TB/s of
+// the 56 bytes a cell must read), a cell per thread in 256 long ranges 32.4 us;
+// blocks in a loop over a range 47 us (the next block's loads wait for the sums).
 template <class Op, int NT>
 __global__ void __launch_bounds__(NT) k3_resnorm(Op op, Grid3 g, L3 A, double* part,
                                                  const CycleState* st) {
     if (stopped(st)) return;
     __shared__ double red[NT / 64];
     double acc = 0.0;
-    const size_t total = (size_t)g.m * g.n * g.l;
-    constexpr int NF = Op::NF;
-    // each workgroup sums one contiguous range (XCD-contiguous order)
-    const size_t chunk = ((total + gridDim.x - 1) / gridDim.x + NT - 1) / NT * NT;
-    const size_t b0 = (size_t)xcd_item(blockIdx.x, gridDim.x) * chunk;
-    const size_t b1 = b0 + chunk < total ? b0 + chunk : total;
-    for (size_t q = b0 + threadIdx.x; q < b1; q += NT) {
-        int i, j, k;
-        split_cell(q, g, i, j, k);
-        double u[NF], ns[NF], N[NF];
+    const size_t q = item3();
+    if (q < (cells3(g) >> 3)) {
+        const int I = (int)(q & (size_t)((g.m >> 1) - 1));
+        const int J = (int)((q >> (g.lm - 1)) & (size_t)((g.n >> 1) - 1));
+        const int K = (int)(q >> (g.lm + g.ln - 2));
+        block_residual3(op, g, A, I, J, K, [&](const double*, const double* r, double) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            u[f] = A.u[f][q];
-            ns[f] = nsum6(A.u[f], i, j, k, g);
-        }
-        op.apply(u, ns, Op::XK ? A.xk[q] : 0.0, N);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            const double r = A.f[f][q] - N[f];
-            acc += r * r;
-        }
+            for (int f = 0; f < Op::NF; ++f) acc += r[f] * r[f];
+        });
     }
     const double bs = block_sum<NT>(acc, red);
     if (threadIdx.x == 0) part[blockIdx.x] = bs;

@@ -33,6 +33,9 @@ unsigned red_blocks3(size_t total) {
     return (unsigned)(b < kRedBlocks3 ? b : kRedBlocks3);
 }
 
+// Residual norms: a 2x2x2 block of cells per thread.
+unsigned res_blocks3(size_t total) { return blocks256(total / 8); }
+
 constexpr int kPoissonCoarseSweeps3 = 10;
 
 int validate3(int m, int n, int l, const mpfc_params* p, const mpfc_opts* o) {
@@ -70,7 +73,6 @@ struct mpfc3d_ctx {
     double* phist = nullptr;
     double* acc = nullptr;
     double* part = nullptr;
-    int nparts = 0;
     void* arena = nullptr;
     CycleState* host_st = nullptr;
     double* host_buf = nullptr;
@@ -262,7 +264,7 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
     // finest residual norm and stopping test
     const Level3& F0 = C->L[0];
     const size_t total = (size_t)F0.m * F0.n * F0.l;
-    const unsigned nb = red_blocks3(total);
+    const unsigned nb = res_blocks3(total);
     const L3 FF = fields(F0, 0);
     if constexpr (POISSON) {
         hipLaunchKernelGGL((k3_resnorm<PoissonOp3, NT>), dim3(nb), dim3(NT), 0, s, op_of(F0), F0.g,
@@ -456,9 +458,10 @@ int mpfc3d_create(mpfc3d_ctx** out, int m, int n, int l, const mpfc_params* p,
         C->hist = take(o->max_cycles + 1 + 8);
         C->phist = take(kPoissonMax + 8);
         C->acc = take(64);
-        C->nparts = 4096;  // per-block partials (up to 8 values) of at most kRedBlocks3 blocks
-        static_assert(kRedBlocks3 <= 4096, "reduction partials exceed the buffer");
-        C->part = take((size_t)C->nparts * 8);
+        // per-block partials: up to 8 values of at most kRedBlocks3 blocks, or one of
+        // a residual norm's
+        const size_t N0 = (size_t)m * n * l;
+        C->part = take(std::max((size_t)kRedBlocks3 * 8, (size_t)res_blocks3(N0)));
         C->st = (CycleState*)take(16);
         C->pst = (CycleState*)take(16);
         return off;
@@ -518,7 +521,7 @@ int mpfc3d_step(mpfc3d_ctx* C, const double* phi_n, const double* phi_nm1, doubl
                            F0.u[0], F0.xk, F0.f[1], F0.u[2], F0.u[1]);
     // residual of the guess (history entry 0)
     {
-        const unsigned rb = red_blocks3(total);
+        const unsigned rb = res_blocks3(total);
         L3 FF{};
         for (int f = 0; f < 3; ++f) { FF.u[f] = F0.u[f]; FF.f[f] = F0.f[f]; }
         FF.xk = F0.xk;
