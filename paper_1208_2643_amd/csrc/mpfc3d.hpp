@@ -154,6 +154,54 @@ __global__ void __launch_bounds__(256) k3_relax(Op op, Grid3 g, L3 A, int colour
     for (int f = 0; f < NF; ++f) A.u[f][q] = u[f];
 }
 
+// The same with two neighbouring cells of the colour per thread, for m >= 4: every
+// load but the one x-neighbour outside is 16 bytes (rows and halves are even and
+// the arrays 256-byte aligned), so a wave makes half as many.  Bound by memory: a
+// half-sweep moves 52 bytes a cell.  128^3: 19.1 -> 17.0 us (6.4 TB/s), 64^3
+// 4.5 -> 3.7, 32^3 3.3 -> 2.9; the Poisson problem's on 128^3 7.6 -> 5.3.
+constexpr int RX_THREADS = 64;
+template <class Op>
+__global__ void __launch_bounds__(RX_THREADS) k3_relax2(Op op, Grid3 g, L3 A, int colour,
+                                                        const CycleState* st) {
+    if (stopped(st)) return;
+    const size_t half = cells3(g) >> 1;
+    const size_t t = 2 * item3();
+    if (t >= half) return;
+    const int mh = g.m >> 1;
+    const int x2 = (int)(t & (size_t)(mh - 1));
+    const size_t row = t >> (g.lm - 1);
+    const int j = (int)(row & (size_t)(g.n - 1)), k = (int)(row >> g.ln);
+    const bool odd = (j + k + colour) & 1;  // the cells' other x-neighbours: at x2 + 1, else x2 - 1
+    const size_t own = colour ? half : 0, oth = half - own;
+    auto ent = [&](int x, int jj, int kk) {
+        return oth + ((((size_t)(kk & (g.l - 1)) << g.ln) + (size_t)(jj & (g.n - 1))) << (g.lm - 1)) +
+               (size_t)(x & (mh - 1));
+    };
+    const size_t yp = ent(x2, j + 1, k), ym = ent(x2, j - 1, k), zp = ent(x2, j, k + 1),
+                 zm = ent(x2, j, k - 1), xe = ent(odd ? x2 + 2 : x2 - 1, j, k);
+    auto two = [](const double* p) { return *reinterpret_cast<const double2*>(p); };
+    constexpr int NF = Op::NF;
+    double u[2][NF], ns[2][NF], fv[2][NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const double* v = A.u[f];
+        const double2 a = two(v + own + t), b = two(v + oth + t), w = two(A.f[f] + own + t);
+        const double2 n = two(v + yp), s = two(v + ym), o = two(v + zp), i = two(v + zm);
+        const double e = v[xe];
+        u[0][f] = a.x; u[1][f] = a.y;
+        fv[0][f] = w.x; fv[1][f] = w.y;
+        ns[0][f] = (odd ? b.x + b.y : e + b.x) + (n.x + s.x) + (o.x + i.x);
+        ns[1][f] = (odd ? b.y + e : b.x + b.y) + (n.y + s.y) + (o.y + i.y);
+    }
+    double2 xk{0.0, 0.0};
+    if constexpr (Op::XK) xk = two(A.xk + own + t);
+    op.relax(u[0], ns[0], fv[0], xk.x);
+    op.relax(u[1], ns[1], fv[1], xk.y);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+        *reinterpret_cast<double2*>(A.u[f] + own + t) = double2{u[0][f], u[1][f]};
+}
+
 // Residual r = f - N(u) at the eight cells of the 2x2x2 block (I, J, K) of g, in
 // turn to `cell(u, r, xk)`.  Of a cell's six neighbours three are in the block, so
 // a thread makes 32 loads of each field instead of 56, of both colours: the cells

@@ -106,8 +106,12 @@ int relax3(mpfc3d_ctx* C, const Op& op, const Level3& lv, const L3& A, int colou
     const size_t half = (size_t)lv.m * lv.n * lv.l / 2;
     const bool timed = finest && C->prof;
     if (timed) HIP_TRY(hipEventRecord(C->ev[0], s));
-    hipLaunchKernelGGL((k3_relax<Op>), dim3(blocks256(half)), dim3(256), 0, s, op, lv.g, A, colour,
-                       stop);
+    if (lv.m >= 4)
+        hipLaunchKernelGGL((k3_relax2<Op>), dim3((unsigned)((half / 2 + RX_THREADS - 1) / RX_THREADS)),
+                           dim3(RX_THREADS), 0, s, op, lv.g, A, colour, stop);
+    else
+        hipLaunchKernelGGL((k3_relax<Op>), dim3(blocks256(half)), dim3(256), 0, s, op, lv.g, A,
+                           colour, stop);
     if (timed) {
         HIP_TRY(hipEventRecord(C->ev[1], s));
         HIP_TRY(hipEventSynchronize(C->ev[1]));

@@ -3,7 +3,8 @@ shape of its top level (cubic, thin in each axis, rows longer than a wave's lane
 a single level, coarsest levels that are not 2 x 2 x 2), as the finest level
 (complete right-hand side) and below one (completed in the kernel).  One cycle
 against the oracle, element by element, at the tolerance of the other one-cycle
-tests.
+tests.  And the half-sweeps of larger levels, whose threads take two neighbouring
+cells of a colour where a row has them.
 """
 import numpy as np
 import pytest
@@ -30,7 +31,8 @@ def relmax(a, b):
 @pytest.mark.parametrize("m,n,l", [
     (2, 2, 2), (4, 2, 2), (2, 8, 2), (2, 2, 1024), (4, 4, 4),      # one level, or two
     (16, 16, 16), (64, 8, 8), (8, 64, 8), (8, 8, 64), (128, 8, 4), (512, 4, 2), (4, 16, 64),
-    (32, 32, 32), (16, 32, 16), (256, 8, 8), (8, 512, 8), (32, 16, 8)])
+    (32, 32, 32), (16, 32, 16), (256, 8, 8), (8, 512, 8), (32, 16, 8),
+    (2, 64, 64), (4, 64, 64), (8, 64, 32)])                     # rows of one, two, four pairs
 def test_one_cycle(m, n, l, nu1, nu2):
     d = dict(eps=0.025, beta=0.9, M=1.0, h=0.5, dt=0.05, scheme=2)
     rng = np.random.default_rng(29)
