@@ -56,9 +56,9 @@ BATCH_FP32_VCYCLE_BYTES = 340.0
 # shape "TXxTY/HALO", valid only for the kernel sources they were measured on
 # (kernel_source_hash).
 MEASURED_TRAFFIC = {
-    "src": "a7c916ba31795d62",
-    "down": {"64x32/6": 113708059, "32x32/6": 110302851, "32x16/6": 109981065, "16x16/6": 109964685, "64x16/10": 110995883, "32x16/10": 110008707, "16x16/10": 110001541},
-    "up": {"64x32/6": 109757846, "32x32/6": 104919287, "32x16/6": 103134588, "16x16/6": 103130493, "64x16/10": 103905108, "32x16/10": 103176563, "16x16/10": 103166325},
+    "src": "c250577d457021a9",
+    "down": {"64x32/6": 113722936, "32x32/6": 110209594, "32x16/6": 109991456, "16x16/6": 109990496, "64x16/10": 110935630, "32x16/10": 110020122, "16x16/10": 110014139},
+    "up": {"64x32/6": 108732236, "32x32/6": 104558635, "32x16/6": 103145366, "16x16/6": 103142162, "64x16/10": 103831034, "32x16/10": 103173899, "16x16/10": 103165709},
 }
 
 

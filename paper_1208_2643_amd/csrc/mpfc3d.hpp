@@ -3,11 +3,12 @@
 // extension to three dimensions is straightforward).  Periodic m x n x l grids
 // with power-of-two sides, cell (i, j, k) at (k n + j) m + i, FP64.
 //
-// Kernels are plain global-memory passes, one thread per cell (or per cell of
-// one colour): a red-black half-sweep, the residual with the 2x2x2 restriction
-// of u, r and phi^k, the completion of a coarse right-hand side, the trilinear
-// prolongation and correction, and the residual norm.  Every pass is bound by
-// HBM bandwidth; each launch streams its level once.
+// Kernels are global-memory passes: a red-black half-sweep (two cells of a colour
+// per thread), the residual with the 2x2x2 restriction of u, r and phi^k, the
+// completion of a coarse right-hand side, the trilinear prolongation and
+// correction, and the residual norm (a 2x2x2 block per thread).  On the larger
+// levels every pass is bound by memory and streams its level once; the levels of at
+// most 4096 cells run in one workgroup.
 //
 // Storage inside the solver is split by colour: a level of N cells holds its
 // red cells ((i + j + k) even) in the first N/2 entries and its black cells in
@@ -479,7 +480,7 @@ __global__ void __launch_bounds__(NT) k3_resnorm(Op op, Grid3 g, L3 A, double* p
 // another (20 of them on the coarsest level), and on the top level by the issue
 // rate of one CU.  From 16^3 down it takes 38 us (16^3: some 22 us of it); the
 // kernel from 8^3 down took 25 us and the twelve launches of the 16^3 level 56 us
-// more, with a gap each.  Ten steps on 128^3: 28.5 -> 25.1 ms.
+// more, with a gap each.  Three steps on 128^3 (57 cycles): 28.5 -> 25.1 ms.
 constexpr int CP3_CELLS = 4096;
 constexpr int CP3_LOW = 592;      // all levels below the top one: 512 + 64 + 8 (+ padding)
 constexpr int CP3_MAXLEV = 10;
