@@ -894,9 +894,11 @@ int time_in_graph(hipStream_t& cap, hipStream_t s, int reps, Fn&& launch, float&
 }
 
 constexpr int kTuneReps = 8;
-// Cells of the largest general-grid level that tries 16 x 16 tiles: a down launch
-// takes 5.7 us against 6.2 with 32 x 16 tiles on 128 x 100, 8.1 against 6.6 on
-// 256 x 200.
+// Cells of the largest general-grid level that tries 16 x 16 tiles in place of
+// 64 x 32: a down launch takes 5.7 us against 6.2 with 32 x 16 tiles on 128 x 100,
+// 8.1 against 6.6 on 256 x 200, and 64 x 32 tiles leave such a level at most eight
+// workgroups.  (With all three tried there, a context took 22.6 -> 27.3 ms to create,
+// and its steps no less.)
 constexpr int kGenSmall = 16384;
 
 // For every level with tile launches and every launch kind, time each tile
@@ -928,7 +930,7 @@ int tune_one(mpfc_ctx* C, Level& lv, int kind, int H, Fn&& launch, Pre&& pre, bo
         }
         for (int k = 0; k < kNumShapes; ++k) {
             if (H > kShapes[k].hmax || (C->gen && !gen_shape(k))) continue;
-            if (C->gen && k == 3 && lv.m * lv.n > kGenSmall) continue;
+            if (C->gen && k == (lv.m * lv.n > kGenSmall ? 3 : 0)) continue;
             // the second round repeats only the shapes that may still win
             if (round > 0 && t[k] > 1.25f * best0) continue;
             lv.shape[kind] = k;
