@@ -37,6 +37,18 @@ __device__ __forceinline__ bool stopped(const CycleState* st) {
     return st != nullptr && st->done != 0;
 }
 
+// The same in a launch beside which the flag may rise: one thread's look decides
+// for the workgroup (each wave's own look may differ, and the rest of a workgroup
+// would go on over LDS that the waves which left have not filled).  Every thread of
+// the workgroup calls it; the writer stores the flag atomically.
+__device__ __forceinline__ bool block_stopped(const CycleState* st) {
+    __shared__ int done;
+    if (threadIdx.x == 0)
+        done = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return done != 0;
+}
+
 // ---------------------------------------------------------------------------
 // 1/x for x >= 1 (the determinant of the smoother's local system, 1 + a d +
 // a b e_c with a, b, e_c, d >= 0): the hardware reciprocal estimate refined by
@@ -325,7 +337,7 @@ __device__ __forceinline__ double parts_sum(const double* __restrict__ part, int
 // of its squares to part[b]; one block adds them in a fixed order, records
 // ||r|| = sqrt(h2 * sum) in hist[count] and sets the status: converged when
 // ||r|| <= tol, non-finite, diverged (growth by `diverge` over hist[0]) or the
-// cycle limit.  No atomics and no device-wide fences are involved, and the
+// cycle limit.  No atomic sums and no device-wide fences are involved, and the
 // norm is deterministic.  Bound by launch and memory latency, so the partial
 // sums and the cycle state are requested together, before the stop flag is
 // looked at: with 1024 threads and 16384 sums (the defect pass at 2048^2) 5.4 us
@@ -349,7 +361,9 @@ __device__ __forceinline__ void norm_finalize_body(const double* __restrict__ pa
         else if (k > 0 && nr > diverge * first) status = ST_DIVERGED;
         else if (k + 1 >= max_norms) status = ST_MAXCYC;
         st->status = status;
-        st->done = status != ST_RUNNING;
+        // (block_stopped may be looking)
+        __hip_atomic_store(&st->done, (int)(status != ST_RUNNING), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

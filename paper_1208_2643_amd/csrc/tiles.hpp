@@ -802,11 +802,9 @@ struct TileWork {
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
-                                          const CycleState* stop, int tbx, int tby, int pslot,
-                                          bool zero_in) {
+                                          int tbx, int tby, int pslot, bool zero_in) {
     using W = TileWork<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>;
     __shared__ typename W::Lds S;
-    if (stopped(stop)) return;
     const typename W::Geo G = W::geo(A, tbx, tby);
     typename W::Rhs R;
     if constexpr (UP) {
@@ -826,29 +824,34 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
 // (tx, ty divide m, n), and with a pending norm one more, the first, which runs
 // its stopping test.  The test used to be a launch of its own between the up
 // launch that wrote the sums and the next cycle's finest down launch: 4.4 us and
-// a launch gap of every cycle.  Beside the tiles it costs nothing: when it stops
-// the cycles, the tiles of this launch that did not see the flag yet have only
-// written what is rewritten before it is read again (the other copy of u, the
-// next level's arrays), and every launch behind this one returns at once.
+// a launch gap of every cycle.  Beside the tiles it costs nothing.  The flag may
+// rise while the tiles of this launch look at it, so each of their workgroups looks
+// once (block_stopped) and either returns whole or runs whole.  A tile that ran
+// beside the test that stops the cycles has written the other copy of u and the
+// next level's arrays, all rewritten before they are read again, and not what it
+// read; every launch behind this one returns at once.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
                                                        const CycleState* stop, PendingNorm P) {
     int b = blockIdx.x, nt = gridDim.x;
-    if constexpr (!UP) {
-        if (P.nparts) {
-            if (b == 0) {
-                norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
-                                                 P.max_norms, P.diverge);
-                return;
-            }
-            --b;
-            --nt;
+    bool halt;
+    if (!UP && P.nparts) {
+        if (b == 0) {
+            norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
+                                             P.max_norms, P.diverge);
+            return;
         }
+        --b;
+        --nt;
+        halt = block_stopped(stop);
+    } else {
+        halt = stopped(stop);
     }
+    if (halt) return;
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, stop, tbx, tby, tl, A.zero_in);
+    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, tbx, tby, tl, A.zero_in);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)
@@ -876,8 +879,9 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_batched(const BatchTile<O
     const int b = xcd_item(blockIdx.x, nitems);
     const BatchItem it = items[b];
     const BatchTile<Op>& BA = args[it.arg];
+    if (stopped(BA.stop)) return;
     const int tby = it.tile / BA.ntx, tbx = it.tile - tby * BA.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU, false, EXACT>(BA.op, BA.A, BA.stop, tbx, tby,
+    tile_body<Op, TX, TY, HMAX, UP, NEU, false, EXACT>(BA.op, BA.A, tbx, tby,
                                                        BA.part_off + it.tile,
                                                        first && BA.A.zero_in);
 }

@@ -1,0 +1,91 @@
+// Kernels of the V-cycle, one workgroup on the CPU (hip/hip_runtime.h here):
+//   tile <first wave>        a finest down tile whose stop flag rises while its waves start
+// It prints one line, checked by tests/test_workgroup_cpu.py.
+#include "kernels.hpp"
+#include "tiles.hpp"
+
+using namespace mpfc;
+
+static std::vector<unsigned> order_from(unsigned nt, unsigned wave) {
+    std::vector<unsigned> o(nt);
+    for (unsigned k = 0; k < nt; ++k) o[k] = (k + 64 * wave) % nt;
+    return o;
+}
+static std::vector<double> field(size_t n, unsigned seed, double amp) {
+    std::vector<double> f(n);
+    uint64_t s = seed * 0x9E3779B97F4A7C15ull + 1;
+    for (double& x : f) {
+        s = s * 6364136223846793005ull + 1442695040888963407ull;
+        x = amp * ((double)(s >> 11) / 9007199254740992.0 - 0.5);
+    }
+    return f;
+}
+static LevelOp<double> level(double h, double c, double al) {
+    LevelOp<double> op;
+    op.ih2 = 1.0 / (h * h);
+    op.c = c;
+    op.al = al;
+    op.e = 0.5;
+    op.derive();
+    return op;
+}
+using Op = MpfcOp<double, 2, true, false>;
+
+static int tile(unsigned wave) {
+    constexpr int M = 32, T = 16;
+    const size_t N = M * M;
+    std::vector<std::vector<double>> u, f;
+    for (int k = 0; k < 3; ++k) {
+        u.push_back(field(N, 1 + k, 1.0));
+        f.push_back(field(N, 4 + k, 1.0));
+    }
+    const std::vector<std::vector<double>> u0 = u;
+    std::vector<double> xk = field(N, 7, 1.0);
+    CycleState st{};
+    auto launch = [&](bool rise, std::vector<std::vector<double>>& w) {
+        w.assign(3 + 3 * 3 + 1, std::vector<double>(N, 1e300));
+        TileArgs<double> A{};
+        A.g = Grid{M, M, 5, 5, 0};
+        for (int k = 0; k < 3; ++k) {
+            A.uin[k] = u[k].data();
+            A.f[k] = f[k].data();
+            A.uout[k] = w[k].data();
+            A.uH[k] = w[3 + k].data();
+            A.vH[k] = w[6 + k].data();
+            A.rH[k] = w[9 + k].data();
+        }
+        A.xk = xk.data();
+        A.xkH = w[12].data();
+        A.nsweep = 4;
+        A.H = 6;
+        A.tx = A.ty = T;
+        A.ntx = M / T;
+        st = CycleState{};
+        PendingNorm P{};
+        P.nparts = 1;  // workgroup 0 is the stopping test's
+        emu::run(kTileThreads, dim3(2), dim3(1 + (M / T) * (M / T)),
+                 order_from(kTileThreads, wave), [&] {
+                     k_tile<Op, T, T, 6, false, false, false, true>(Op{level(0.8, 0.02, 0.4)}, A,
+                                                                    &st, P);
+                 },
+                 [&](unsigned k) { if (rise && k == 64) st.done = 1; });
+    };
+    std::vector<std::vector<double>> full, got;
+    launch(false, full);
+    launch(true, got);
+    bool none = true, untouched = u == u0;
+    for (auto& w : got)
+        for (double x : w) none = none && x == 1e300;
+    bool wrote = false;
+    for (double x : full[0]) wrote = wrote || x != 1e300;
+    printf("%s %s\n", !wrote ? "broken" : got == full ? "all" : none ? "none" : "part",
+           untouched ? "kept" : "overwritten");
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    auto num = [&](int k) { return k < argc ? atof(argv[k]) : 0.0; };
+    const char* what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "tile")) return tile((unsigned)num(2));
+    return 1;
+}

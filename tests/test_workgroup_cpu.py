@@ -1,0 +1,40 @@
+"""Kernels of the V-cycle run on the CPU, one workgroup with its work-items one
+after the other between barriers (tests/emulate): what must not depend on which
+work-item comes first.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+EMU = os.path.join(HERE, "emulate")
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1208_2643_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    cxx = shutil.which("amdclang++") or shutil.which("clang++", path="/opt/rocm/llvm/bin")
+    if cxx is None:
+        pytest.skip("clang++ not found")
+    exe = str(tmp_path_factory.mktemp("emulate") / "workgroup")
+    r = subprocess.run([cxx, "-x", "c++", "-std=c++17", "-O1", "-ffp-contract=off", "-w", "-I", EMU,
+                        "-I", CSRC, os.path.join(EMU, "workgroup.cpp"), "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def call(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return r.stdout.split()
+    return call
+
+
+@pytest.mark.parametrize("wave", range(8))
+def test_rising_stop_flag_leaves_no_tile_half_done(driver, wave):
+    """The stop flag may rise in the launch whose tiles look at it, here once the
+    first wave of a workgroup has looked: the workgroup runs whole or not at all,
+    and leaves the copy of u that it read."""
+    wrote, read = driver("tile", wave)
+    assert wrote in ("all", "none") and read == "kept"
