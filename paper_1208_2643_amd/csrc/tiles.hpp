@@ -1383,7 +1383,7 @@ struct CoarseWork {
             load_own(S, P, O);
             if (compl_f) complete(o, S, P, O);
         }
-        if (WG && compl_f) __syncthreads();  // every N(u) reads u as loaded
+        if (compl_f) sync<WG>();  // every N(u) reads u as loaded
         if (P.on) {
 #pragma unroll
             for (int c = 0; c < 2; ++c)

@@ -1,14 +1,15 @@
 // Kernels of the V-cycle, one workgroup on the CPU (hip/hip_runtime.h here):
 //   tile <first wave>        a finest down tile whose stop flag rises while its waves start
-// It prints one line, checked by tests/test_workgroup_cpu.py.
+//   coarse <m> <n> <bc>      the persistent levels with the work-items in two orders
+// Each prints one line, checked by tests/test_workgroup_cpu.py.
 #include "kernels.hpp"
 #include "tiles.hpp"
 
 using namespace mpfc;
 
-static std::vector<unsigned> order_from(unsigned nt, unsigned wave) {
+static std::vector<unsigned> order_from(unsigned nt, unsigned wave, bool back = false) {
     std::vector<unsigned> o(nt);
-    for (unsigned k = 0; k < nt; ++k) o[k] = (k + 64 * wave) % nt;
+    for (unsigned k = 0; k < nt; ++k) o[k] = back ? nt - 1 - k : (k + 64 * wave) % nt;
     return o;
 }
 static std::vector<double> field(size_t n, unsigned seed, double amp) {
@@ -83,9 +84,53 @@ static int tile(unsigned wave) {
     return 0;
 }
 
+template <int NC, bool NEU>
+static int coarse(int m, int n, int bc) {
+    const size_t N = (size_t)m * n;
+    using W = CoarseWork<Op, NC, NEU>;
+    static typename W::Lds S;
+    std::vector<double> xk = field(N, 7, 1.0);
+    std::vector<std::vector<double>> first;
+    double diff = 0.0, size = 0.0;
+    for (int back = 0; back < 2; ++back) {
+        std::vector<std::vector<double>> u, f;
+        for (int k = 0; k < 3; ++k) {
+            u.push_back(field(N, 1 + k, 1.0));
+            f.push_back(field(N, 4 + k, 1.0));
+        }
+        CoarseArgs<double> A{};
+        A.geo.bc = bc;
+        A.geo.m[0] = m;
+        A.geo.n[0] = n;
+        A.geo.lm[0] = __builtin_ctz(m);
+        for (int k = 0; k < 3; ++k) { A.u[k] = u[k].data(); A.rr[k] = f[k].data(); }
+        A.xk = xk.data();
+        A.h_top = 0.8;
+        A.nsw1 = A.nsw2 = 4;
+        A.complete_top = 1;
+        A.newton_maxit = 30;
+        A.newton_tol = 1e-15;
+        emu::run(CP_THREADS, dim3(0), dim3(1), order_from(CP_THREADS, 0, back),
+                 [&] { W::run(Op{level(0.8, 0.02, 0.4)}, A, S, nullptr); }, [](unsigned) {});
+        if (!back) first = u;
+        for (int k = 0; k < 3; ++k)
+            for (size_t q = 0; q < N; ++q) {
+                diff = fmax(diff, fabs(u[k][q] - first[k][q]));
+                size = fmax(size, fabs(u[k][q]));
+            }
+    }
+    printf("%.17g %.17g\n", diff, size);
+    return 0;
+}
+
 int main(int argc, char** argv) {
     auto num = [&](int k) { return k < argc ? atof(argv[k]) : 0.0; };
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "tile")) return tile((unsigned)num(2));
+    if (!strcmp(what, "coarse")) {
+        const int m = (int)num(2), n = (int)num(3), bc = (int)num(4);
+        if (m == n) return bc ? coarse<4, true>(m, n, bc) : coarse<4, false>(m, n, bc);
+        return bc ? coarse<8, true>(m, n, bc) : coarse<8, false>(m, n, bc);
+    }
     return 1;
 }

@@ -38,3 +38,14 @@ def test_rising_stop_flag_leaves_no_tile_half_done(driver, wave):
     and leaves the copy of u that it read."""
     wrote, read = driver("tile", wave)
     assert wrote in ("all", "none") and read == "kept"
+
+
+@pytest.mark.parametrize("m,n", [(2, 2), (4, 4), (8, 8), (16, 16), (32, 32), (4, 2), (8, 16),
+                                 (32, 16)])
+@pytest.mark.parametrize("bc", [0, 3])
+def test_persistent_levels_do_not_depend_on_the_order_of_the_lanes(driver, m, n, bc):
+    """A cycle over the levels of one workgroup, work-items first to last and last
+    to first: the same bits.  (Levels of up to 128 cells run in one wave, whose lanes
+    are ordered by fences only.)"""
+    diff, size = map(float, driver("coarse", m, n, bc))
+    assert diff == 0.0 and size > 0.0
