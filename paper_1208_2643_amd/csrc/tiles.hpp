@@ -918,6 +918,25 @@ struct CoarseArgs {
     T newton_tol;
 };
 
+// Whether Newton's method on the coarsest grid may stop after a step of at most
+// `step` in every cell's phi (xmax: the largest |phi| behind it).  In FP64 also when
+// the error left by the step is known to be below the tolerance, so that no further
+// step has to show it: divided by c times -Lap, the equation is the gradient of a
+// convex function whose second derivative is at least mu = min 1/(c lam) + e lam^2
+// over the grid's eigenvalues lam > 0 of -Lap, plus min(al + W), as g' >= 0.  The
+// residual left is at most |g''| step^2 / 2 per cell with |g''| taken over the step,
+// hence the error at most sqrt(NC) / mu times that, NC <= 8.  (A bare test of step^2
+// against the tolerance left up to 2.3e-14 where c is large, al zero and phi small.)
+template <class Op, typename T>
+__device__ __forceinline__ bool newton_done(T step, T xmax, T xkmax, T mu, T tol) {
+    const T xs = T(1) + xmax;
+    if (step <= tol * xs) return true;
+    if (sizeof(T) != 8) return false;
+    const T top = xmax + step, g2 = Op::XK ? T(1.5) * top + T(0.5) * xkmax : T(6) * top;
+    const T s2 = step * step;
+    return s2 <= tol * xs && T(1.5) * g2 * s2 <= tol * xs * mu;
+}
+
 // Coarsest grid, MPFC: eliminate kappa and mu (kappa = f3 + e Lap phi,
 // mu = f2 + g(phi) + al phi + Lap kappa) and solve the remaining equation
 //   phi - c Lap(g(phi) + al phi + e Lap^2 phi) = f1 + c Lap(f2 + Lap f3)
@@ -991,6 +1010,13 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
         pbv[a] = Op::PB ? pb[a] : T(0);
         alv[a] = Op::PW ? al + pw[a] : al;  // pinning: W added to the phi coefficient
     }
+    T xkmax = T(0), almin = alv[0];
+#pragma unroll
+    for (int a = 0; a < NC; ++a) {
+        xkmax = fmax(xkmax, fabs(xkv[a]));
+        almin = fmin(almin, alv[a]);
+    }
+    const T lmu = almin + T(1) / (T(8) * c * op.op.ih2);  // lam <= 8/h^2
     for (int it = 0; it < maxit; ++it) {
         // residual R = x - c Lap(g(x) + al x + e Lap^2 x) - rhs
         T w[NC], d[NC], R[NC], J[NC][NC + 1];
@@ -1048,10 +1074,7 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
             smax = fmax(smax, fabs(t1[a]));
             xmax = fmax(xmax, fabs(x[a]));
         }
-        // Newton's method converges quadratically: in FP64 a step below the root of
-        // the tolerance leaves an error below the tolerance
-        const T xs = T(1) + xmax;
-        if (smax <= tol * xs || (sizeof(T) == 8 && smax * smax <= tol * xs * xs)) break;
+        if (newton_done<Op>(smax, xmax, xkmax, lmu, tol)) break;
     }
     // recover kappa and mu
     lap(x, t1);
@@ -1130,6 +1153,13 @@ __device__ __forceinline__ void coarse_solve_walsh(const Op& op, typename Op::re
 #pragma unroll
         for (int k = 0; k < NC; ++k) s[k] = icl[k] + e * lam[k] * lam[k];
     }
+    T xkmax = T(0), smin = s[1], almin = Op::PW ? al + pw[0] : al;
+#pragma unroll
+    for (int a = 0; a < NC; ++a) {
+        xkmax = Op::XK ? fmax(xkmax, fabs(xk[a])) : T(0);
+        smin = a ? fmin(smin, s[a]) : smin;
+        if constexpr (Op::PW) almin = fmin(almin, al + pw[a]);
+    }
     z[0] = rho[0];
     for (int it = 0; it < maxit; ++it) {
         walsh<NC>(z, x, T(1));
@@ -1176,9 +1206,8 @@ __device__ __forceinline__ void coarse_solve_walsh(const Op& op, typename Op::re
             smax += fabs(b[k]);
             xmax += fabs(z[k]);
         }
-        // quadratic convergence: as in coarse_solve_mpfc
-        const T xs = T(1) + xmax;
-        if (smax <= tol * xs || (sizeof(T) == 8 && smax * smax <= tol * xs * xs)) break;
+        // (smax and xmax: sums over the modes, no cell's value is larger)
+        if (newton_done<Op>(smax, xmax, xkmax, smin + almin, tol)) break;
     }
     // kappa = f3 + e Lap phi, mu = f2 + g(phi) + al phi + Lap kappa
     walsh<NC>(z, u[0], T(1));

@@ -1,6 +1,8 @@
 // Kernels of the V-cycle, one workgroup on the CPU (hip/hip_runtime.h here):
 //   tile <first wave>        a finest down tile whose stop flag rises while its waves start
 //   coarse <m> <n> <bc>      the persistent levels with the work-items in two orders
+//   newton <h> <c> <al> <size> <pivot> <seed>   the coarsest grid's solve against one
+//                            that takes every step
 // Each prints one line, checked by tests/test_workgroup_cpu.py.
 #include "kernels.hpp"
 #include "tiles.hpp"
@@ -123,6 +125,40 @@ static int coarse(int m, int n, int bc) {
     return 0;
 }
 
+// `pivot`: the elimination with pivoting, else the sign patterns.
+static int newton(double h, double c, double al, double amp, int pivot, unsigned seed) {
+    constexpr int NC = 4;
+    double f[3][NC], xk[NC], none[NC] = {};
+    std::vector<double> a[3];
+    for (int k = 0; k < 3; ++k) {
+        a[k] = field(NC, seed + k, amp);
+        const std::vector<double> b = field(NC, seed + 4 + k, amp);
+        for (int q = 0; q < NC; ++q) f[k][q] = b[q];
+    }
+    const std::vector<double> x = field(NC, seed + 7, amp);
+    for (int q = 0; q < NC; ++q) xk[q] = x[q];
+    const Op op{level(h, c, al)};
+    auto solve = [&](int maxit, double tol) {
+        double u[3][NC];
+        for (int k = 0; k < 3; ++k)
+            for (int q = 0; q < NC; ++q) u[k][q] = a[k][q];
+        if (pivot) coarse_solve_mpfc<Op, NC>(op, u, f, xk, none, none, 2, 1, 2, 0, maxit, tol);
+        else coarse_solve_walsh<Op, NC>(op, u, f, xk, none, none, 2, 2, 0, maxit, tol);
+        return std::vector<double>(u[0], u[0] + NC);
+    };
+    auto apart = [](const std::vector<double>& p, const std::vector<double>& q) {
+        double d = 0.0;
+        for (int k = 0; k < NC; ++k) d = fmax(d, fabs(p[k] - q[k]));
+        return d;
+    };
+    const std::vector<double> got = solve(30, 1e-15), late = solve(100, 0.0);
+    double noise = 0.0, size = 1.0;   // what the solve's own rounding moves, step after step
+    for (int k = 80; k < 100; ++k) noise = fmax(noise, apart(solve(k, 0.0), late));
+    for (double v : late) size = fmax(size, fabs(v));
+    printf("%.17g %.17g %.17g\n", apart(got, late), noise, size);
+    return 0;
+}
+
 int main(int argc, char** argv) {
     auto num = [&](int k) { return k < argc ? atof(argv[k]) : 0.0; };
     const char* what = argc > 1 ? argv[1] : "";
@@ -132,5 +168,7 @@ int main(int argc, char** argv) {
         if (m == n) return bc ? coarse<4, true>(m, n, bc) : coarse<4, false>(m, n, bc);
         return bc ? coarse<8, true>(m, n, bc) : coarse<8, false>(m, n, bc);
     }
+    if (!strcmp(what, "newton"))
+        return newton(num(2), num(3), num(4), num(5), (int)num(6), (unsigned)num(7));
     return 1;
 }

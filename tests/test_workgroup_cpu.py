@@ -49,3 +49,16 @@ def test_persistent_levels_do_not_depend_on_the_order_of_the_lanes(driver, m, n,
     are ordered by fences only.)"""
     diff, size = map(float, driver("coarse", m, n, bc))
     assert diff == 0.0 and size > 0.0
+
+
+@pytest.mark.parametrize("pivot", [0, 1])
+@pytest.mark.parametrize("h,c,al,amp,seed", [
+    (45.2, 3.03e6, 0.0, 2.25e-6, 20), (13.8, 5.32e8, 0.0, 5.40e-5, 773),
+    (21.5, 7.39e6, 0.0, 1.99e-5, 146), (0.8, 0.02, 0.4, 1.0, 1)])
+def test_coarsest_newton_stops_within_its_tolerance(driver, pivot, h, c, al, amp, seed):
+    """Large dt (c), alpha = 0 and a small phi: a step's square says little about the
+    error it leaves.  Against the same solve with every step taken: the tolerance,
+    1e-15 of 1 + |phi|, beside what rounding moves that solve by from step to step
+    (1e-14 where the elimination with pivoting is ill conditioned)."""
+    err, noise, size = map(float, driver("newton", h, c, al, amp, pivot, seed))
+    assert err <= 1e-15 * (1.0 + size) + noise
