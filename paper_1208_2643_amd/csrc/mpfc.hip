@@ -1664,12 +1664,12 @@ static int create_ctx(mpfc_ctx** out, int m, int n, const mpfc_params* p, const 
             }
         }
         C->G = take(nG);
-        C->rb_count = 32 + (size_t)o->max_cycles + 1;
+        C->rb_count = kReadbackHead + (size_t)o->max_cycles + 1;
         C->rb = take(C->rb_count + 8);
         C->st = (CycleState*)C->rb;
         C->pst = (CycleState*)(C->rb + 8);
         C->acc = C->rb + 16;
-        C->hist = C->rb + 32;
+        C->hist = C->rb + kReadbackHead;
         C->io = (StepIO*)take(8);
         C->phist = take(64);
         // one partial sum per finest tile (general grids: tiles down to 2 x 2),
@@ -1864,7 +1864,7 @@ int mpfc_step(mpfc_ctx* C, const double* phi_n, const double* phi_nm1, double* p
         info->energy_pseudo = en[1];
         info->energy_mod = en[2];
         info->mass = en[3];
-        const double* hb = C->host_buf + 32;
+        const double* hb = C->host_buf + kReadbackHead;
         info->residual = hb[fin.count - 1];
         if (info->residual_history)
             std::memcpy(info->residual_history, hb, sizeof(double) * fin.count);

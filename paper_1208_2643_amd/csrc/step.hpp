@@ -240,11 +240,19 @@ __device__ __forceinline__ void complete_kappa_cell(const Grid& g, double ih2, d
     ka[q] = kappa_value(S3[q], e, nsum(phi, i, j, g), phi[q], ih2);
 }
 
-// The first `count` doubles of the readback block into pinned host memory (one
-// workgroup; visible to the host when the stream has been waited for).
+// The readback block into pinned host memory (one workgroup; visible to the host
+// when the stream has been waited for): its first `count` doubles, of the residual
+// history behind the first kReadbackHead only the norms recorded so far.  (The
+// history has an entry per allowed cycle, up to 100 001.)
+constexpr int kReadbackHead = 32;
 __global__ void __launch_bounds__(256) k_readback(const double* __restrict__ rb, int count,
                                                   double* host) {
-    for (int k = threadIdx.x; k < count; k += 256) host[k] = rb[k];
+    const int t = threadIdx.x;
+    const double v = rb[min(t, count - 1)];   // in flight with the cycle state
+    const int norms = reinterpret_cast<const CycleState*>(rb)->count;
+    const int used = min(count, kReadbackHead + norms);
+    if (t < used) host[t] = v;
+    for (int k = t + 256; k < used; k += 256) host[k] = rb[k];
 }
 
 __global__ void k_set_io(StepIO* io, const double* phi_n, const double* phi_nm1, double* psi,

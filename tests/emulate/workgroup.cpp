@@ -1,11 +1,13 @@
-// Kernels of the V-cycle, one workgroup on the CPU (hip/hip_runtime.h here):
+// Kernels of a step, one workgroup on the CPU (hip/hip_runtime.h here):
 //   tile <first wave>        a finest down tile whose stop flag rises while its waves start
 //   coarse <m> <n> <bc>      the persistent levels with the work-items in two orders
 //   newton <h> <c> <al> <size> <pivot> <seed>   the coarsest grid's solve against one
 //                            that takes every step
+//   readback <norms> <max>   what the step's readback writes after that many norms
 // Each prints one line, checked by tests/test_workgroup_cpu.py.
 #include "kernels.hpp"
 #include "tiles.hpp"
+#include "step.hpp"
 
 using namespace mpfc;
 
@@ -159,6 +161,25 @@ static int newton(double h, double c, double al, double amp, int pivot, unsigned
     return 0;
 }
 
+static int readback(int norms, int most) {
+    const int fixed = 32, count = fixed + most + 1;
+    std::vector<double> rb = field(count, 3, 1.0), host(count, 1e300);
+    CycleState st{};
+    st.count = norms;
+    memcpy(rb.data(), &st, sizeof st);
+    emu::run(256, dim3(0), dim3(1), order_from(256, 0),
+             [&] { k_readback(rb.data(), count, host.data()); }, [](unsigned) {});
+    int written = 0, wrong = 0;
+    for (int k = 0; k < count; ++k) {
+        if (host[k] == 1e300) continue;
+        ++written;
+        wrong += memcmp(&host[k], &rb[k], sizeof(double)) != 0;
+    }
+    for (int k = 0; k < fixed + norms; ++k) wrong += host[k] == 1e300;
+    printf("%d %d\n", written, wrong);
+    return 0;
+}
+
 int main(int argc, char** argv) {
     auto num = [&](int k) { return k < argc ? atof(argv[k]) : 0.0; };
     const char* what = argc > 1 ? argv[1] : "";
@@ -170,5 +191,6 @@ int main(int argc, char** argv) {
     }
     if (!strcmp(what, "newton"))
         return newton(num(2), num(3), num(4), num(5), (int)num(6), (unsigned)num(7));
+    if (!strcmp(what, "readback")) return readback((int)num(2), (int)num(3));
     return 1;
 }

@@ -1,4 +1,4 @@
-"""Kernels of the V-cycle run on the CPU, one workgroup with its work-items one
+"""Kernels of a step run on the CPU, one workgroup with its work-items one
 after the other between barriers (tests/emulate): what must not depend on which
 work-item comes first.
 """
@@ -62,3 +62,11 @@ def test_coarsest_newton_stops_within_its_tolerance(driver, pivot, h, c, al, amp
     (1e-14 where the elimination with pivoting is ill conditioned)."""
     err, noise, size = map(float, driver("newton", h, c, al, amp, pivot, seed))
     assert err <= 1e-15 * (1.0 + size) + noise
+
+
+@pytest.mark.parametrize("norms,most", [(1, 1), (3, 100), (224, 300), (225, 100000), (101, 100)])
+def test_readback_takes_the_recorded_norms_only(driver, norms, most):
+    """Of a history with room for every allowed cycle the host gets the norms that the
+    step recorded, behind the 32 doubles of state and sums."""
+    written, wrong = map(int, driver("readback", norms, most))
+    assert written == 32 + norms and wrong == 0
