@@ -929,12 +929,10 @@ struct CoarseArgs {
 // against the tolerance left up to 2.3e-14 where c is large, al zero and phi small.)
 template <class Op, typename T>
 __device__ __forceinline__ bool newton_done(T step, T xmax, T xkmax, T mu, T tol) {
-    const T xs = T(1) + xmax;
-    if (step <= tol * xs) return true;
-    if (sizeof(T) != 8) return false;
-    const T top = xmax + step, g2 = Op::XK ? T(1.5) * top + T(0.5) * xkmax : T(6) * top;
-    const T s2 = step * step;
-    return s2 <= tol * xs && T(1.5) * g2 * s2 <= tol * xs * mu;
+    const T lim = tol * (T(1) + xmax), s2 = step * step, top = xmax + step;
+    const T g2 = Op::XK ? T(1.5) * top + T(0.5) * xkmax : T(6) * top;
+    // (without branches: one thread waits for each)
+    return (step <= lim) | ((sizeof(T) == 8) & (s2 <= lim) & (T(1.5) * g2 * s2 <= lim * mu));
 }
 
 // Coarsest grid, MPFC: eliminate kappa and mu (kappa = f3 + e Lap phi,
