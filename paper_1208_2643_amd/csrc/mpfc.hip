@@ -958,9 +958,9 @@ int autotune(mpfc_ctx* C) {
     if (forced && forced[0]) {
         const int k = std::atoi(forced);
         if (k < 0 || k >= kNumShapes) return fail(MPFC_EINVAL, "MPFC_TILE_SHAPE out of range");
-        if (C->gen && k != 0 && k != 2)
+        if (C->gen && !gen_shape(k))
             return fail(MPFC_EINVAL, "MPFC_TILE_SHAPE: grids with a side that is not a power of two "
-                                     "take shape 0 or 2");
+                                     "take shape 0, 2 or 3");
         for (auto& lv : C->L)
             for (int kind = 0; kind < SH_KINDS; ++kind) lv.shape[kind] = k;
         return MPFC_OK;

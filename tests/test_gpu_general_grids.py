@@ -277,3 +277,35 @@ def test_axis_exchange_general(m, n, bc):
     for key in ("energy_F", "energy_mod", "mass"):
         a, b = getattr(ia, key), getattr(ib, key)
         assert abs(a - b) <= 1e-10 * max(1.0, abs(a)), key
+
+
+# the 16 x 16 tiles of the small levels, on every level: several tiles, levels whose
+# even divisors leave 4 x 4 and 2 x 2 tiles (76 x 92 -> 38 x 46), one tile larger than
+# the level (12 x 4)
+@pytest.mark.parametrize("m,n,kw", [
+    (192, 160, {}), (192, 160, dict(scheme=1, newton=False)),
+    (200, 120, dict(bc=L.MPFC_BC_NEUMANN_X | L.MPFC_BC_NEUMANN_Y)),
+    (200, 120, dict(nu=(1, 0), pin=True)), (160, 96, dict(nu=(0, 1), bc=L.MPFC_BC_NEUMANN_Y)),
+    (76, 92, {}), (76, 92, dict(bc=L.MPFC_BC_NEUMANN_X, pin=True, nu=(1, 1))), (12, 4, {})])
+def test_small_tiles_match_oracle(m, n, kw, monkeypatch):
+    monkeypatch.setenv("MPFC_TILE_SHAPE", "3")
+    got, ref, info, hist = one_cycle(m, n, seed=90, **kw)
+    for a, b in zip(got, ref):
+        assert relmax(a, b) <= 1e-12
+    np.testing.assert_allclose(info.history, hist, rtol=1e-9)
+
+
+@pytest.mark.parametrize("bc", [0, L.MPFC_BC_NEUMANN_X | L.MPFC_BC_NEUMANN_Y])
+@pytest.mark.parametrize("m,n", [(96, 80), (76, 92)])
+def test_small_tiles_energies_match_oracle(m, n, bc, monkeypatch):
+    """The Poisson cycles of the -1 norm on the same tiles, from a cold start."""
+    monkeypatch.setenv("MPFC_TILE_SHAPE", "3")
+    po, pg = both(bc)
+    phi = I.crystallites(m, n, pg.h, radius_cells=10, seed=91)
+    prev = phi + 0.01 * I.noise(m, n, mean=0.0, amp=1.0, seed=92)
+    psi = 0.05 * I.noise(m, n, mean=0.0, amp=1.0, seed=93)
+    st = api.Stepper(m, n, pg, coarse_sweeps=K)
+    e = st.energies(dev(phi), dev(prev), dev(psi))
+    ref = O.energies(po, phi, prev, psi)
+    np.testing.assert_allclose(e, ref, rtol=1e-10)
+    st.close()
