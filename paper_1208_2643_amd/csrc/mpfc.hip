@@ -894,12 +894,24 @@ int time_in_graph(hipStream_t& cap, hipStream_t s, int reps, Fn&& launch, float&
 }
 
 constexpr int kTuneReps = 8;
-// Cells of the largest general-grid level that tries 16 x 16 tiles in place of
-// 64 x 32: a down launch takes 5.7 us against 6.2 with 32 x 16 tiles on 128 x 100,
-// 8.1 against 6.6 on 256 x 200, and 64 x 32 tiles leave such a level at most eight
-// workgroups.  (With all three tried there, a context took 22.6 -> 27.3 ms to create,
-// and its steps no less.)
-constexpr int kGenSmall = 16384;
+// The tile shapes that a level of a general grid tries.  Up to kGenSmall cells
+// 16 x 16 in place of 64 x 32: ten grids of 64 x 60 to 24 x 640 take 0.71 to 0.95
+// of the time of 64 x 32 tiles with them (a down launch on 128 x 100 5.7 us against
+// 6.2 with 32 x 16), on 256 x 200 a down launch takes 8.1 against 6.6.  All three
+// where the sides' even divisors leave 16 x 16 fewer than kGenTile cells and
+// 64 x 32 at least four times as many: 4 x 4 against 46 x 4 on 92 x 92 takes 288 us a
+// step against 251, 360 against 301 on 124 x 116, but 229 against 241 on 76 x 92.
+// (All three on every small level: a context of 512 x 400 took 22.6 -> 27.3 ms to
+// create, and its steps no less.)
+constexpr int kGenSmall = 16384, kGenTile = 64;
+bool gen_tries(const Level& lv, int k) {
+    if (k == 2 || !gen_shape(k)) return k == 2;
+    if (lv.m * lv.n > kGenSmall) return k == 0;
+    int tx, ty, wx, wy;
+    tile_dims(lv, 3, tx, ty);
+    tile_dims(lv, 0, wx, wy);
+    return k == 3 || (tx * ty < kGenTile && 4 * tx * ty <= wx * wy);
+}
 
 // For every level with tile launches and every launch kind, time each tile
 // shape whose halo allowance fits and keep the fastest (first within 5 %).
@@ -929,8 +941,7 @@ int tune_one(mpfc_ctx* C, Level& lv, int kind, int H, Fn&& launch, Pre&& pre, bo
             t_pre = ms < t_pre ? ms : t_pre;
         }
         for (int k = 0; k < kNumShapes; ++k) {
-            if (H > kShapes[k].hmax || (C->gen && !gen_shape(k))) continue;
-            if (C->gen && k == (lv.m * lv.n > kGenSmall ? 3 : 0)) continue;
+            if (H > kShapes[k].hmax || (C->gen && !gen_tries(lv, k))) continue;
             // the second round repeats only the shapes that may still win
             if (round > 0 && t[k] > 1.25f * best0) continue;
             lv.shape[kind] = k;

@@ -309,3 +309,12 @@ def test_small_tiles_energies_match_oracle(m, n, bc, monkeypatch):
     ref = O.energies(po, phi, prev, psi)
     np.testing.assert_allclose(e, ref, rtol=1e-10)
     st.close()
+
+
+@pytest.mark.parametrize("m,n", [(92, 92), (124, 116), (44, 44), (148, 108)])
+def test_sides_with_few_divisors_match_oracle(m, n):
+    """4 times a prime: small levels that may take any of the three general shapes."""
+    got, ref, info, hist = one_cycle(m, n, seed=95)
+    for a, b in zip(got, ref):
+        assert relmax(a, b) <= 1e-12
+    np.testing.assert_allclose(info.history, hist, rtol=1e-9)
