@@ -435,25 +435,48 @@ __global__ void __launch_bounds__(256) k3_prolong_blk(Grid3 g, L3 A, L3 H, const
 }
 
 // Per-block sums of r^2 = (f - N(u))^2 over all fields (the stopping test;
-// k_norm_finalize / k_p_finalize turn them into the norm): a 2x2x2 block per
+// k_norm_finalize / k_p_finalize turn them into the norm).  BLOCK: a 2x2x2 block per
 // thread, so that u of both colours is read by one XCD.  128^3: 22.8 us (5.2 TB/s of
 // the 56 bytes a cell must read), a cell per thread in 256 long ranges 32.4 us;
 // blocks in a loop over a range 47 us (the next block's loads wait for the sums).
-template <class Op, int NT>
+// Else a cell per thread: on at most RES_CELLS cells blocks leave fewer than 64
+// workgroups, each a chain of eight residuals (32^3: 5.7 us against 3.6 with cells,
+// 64 x 64 x 32 6.3 against 4.4; the Poisson problem's 3.8 against 3.0 and 3.9 against
+// 3.3.  On 64^3 blocks take 7.0 and 4.0, cells in 256 ranges 6.9 and 5.1).
+constexpr size_t RES_CELLS = 131072;
+template <class Op, int NT, bool BLOCK>
 __global__ void __launch_bounds__(NT) k3_resnorm(Op op, Grid3 g, L3 A, double* part,
                                                  const CycleState* st) {
     if (stopped(st)) return;
     __shared__ double red[NT / 64];
+    constexpr int NF = Op::NF;
     double acc = 0.0;
     const size_t q = item3();
-    if (q < (cells3(g) >> 3)) {
-        const int I = (int)(q & (size_t)((g.m >> 1) - 1));
-        const int J = (int)((q >> (g.lm - 1)) & (size_t)((g.n >> 1) - 1));
-        const int K = (int)(q >> (g.lm + g.ln - 2));
-        block_residual3(op, g, A, I, J, K, [&](const double*, const double* r, double) {
+    if constexpr (BLOCK) {
+        if (q < (cells3(g) >> 3)) {
+            const int I = (int)(q & (size_t)((g.m >> 1) - 1));
+            const int J = (int)((q >> (g.lm - 1)) & (size_t)((g.n >> 1) - 1));
+            const int K = (int)(q >> (g.lm + g.ln - 2));
+            block_residual3(op, g, A, I, J, K, [&](const double*, const double* r, double) {
 #pragma unroll
-            for (int f = 0; f < Op::NF; ++f) acc += r[f] * r[f];
-        });
+                for (int f = 0; f < NF; ++f) acc += r[f] * r[f];
+            });
+        }
+    } else if (q < cells3(g)) {
+        int i, j, k;
+        split_cell(q, g, i, j, k);
+        double u[NF], ns[NF], N[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            u[f] = A.u[f][q];
+            ns[f] = nsum6(A.u[f], i, j, k, g);
+        }
+        op.apply(u, ns, Op::XK ? A.xk[q] : 0.0, N);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const double r = A.f[f][q] - N[f];
+            acc += r * r;
+        }
     }
     const double bs = block_sum<NT>(acc, red);
     if (threadIdx.x == 0) part[blockIdx.x] = bs;

@@ -33,8 +33,23 @@ unsigned red_blocks3(size_t total) {
     return (unsigned)(b < kRedBlocks3 ? b : kRedBlocks3);
 }
 
-// Residual norms: a 2x2x2 block of cells per thread.
-unsigned res_blocks3(size_t total) { return blocks256(total / 8); }
+// Residual norms: a cell or a 2x2x2 block of cells per thread (k3_resnorm).
+unsigned res_blocks3(size_t total) { return blocks256(total <= RES_CELLS ? total : total / 8); }
+
+// Launch the residual norm of a level; returns the number of its partial sums.
+template <class Op>
+int resnorm3(const Op& op, const Level3& lv, const L3& A, double* part, const CycleState* stop,
+             hipStream_t s) {
+    const size_t total = (size_t)lv.m * lv.n * lv.l;
+    const unsigned nb = res_blocks3(total);
+    if (total <= RES_CELLS)
+        hipLaunchKernelGGL((k3_resnorm<Op, NT, false>), dim3(nb), dim3(NT), 0, s, op, lv.g, A, part,
+                           stop);
+    else
+        hipLaunchKernelGGL((k3_resnorm<Op, NT, true>), dim3(nb), dim3(NT), 0, s, op, lv.g, A, part,
+                           stop);
+    return (int)nb;
+}
 
 constexpr int kPoissonCoarseSweeps3 = 10;
 
@@ -267,20 +282,13 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
     }
     // finest residual norm and stopping test
     const Level3& F0 = C->L[0];
-    const size_t total = (size_t)F0.m * F0.n * F0.l;
-    const unsigned nb = res_blocks3(total);
-    const L3 FF = fields(F0, 0);
-    if constexpr (POISSON) {
-        hipLaunchKernelGGL((k3_resnorm<PoissonOp3, NT>), dim3(nb), dim3(NT), 0, s, op_of(F0), F0.g,
-                           FF, C->part, stop);
-        hipLaunchKernelGGL((k_p_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, (int)nb, C->pst,
+    const int nb = resnorm3(op_of(F0), F0, fields(F0, 0), C->part, stop, s);
+    if constexpr (POISSON)
+        hipLaunchKernelGGL((k_p_finalize<NT>), dim3(1), dim3(NT), 0, s, C->part, nb, C->pst,
                            C->phist, C->acc + 10, kPoissonRel, kPoissonStall, kPoissonMax);
-    } else {
-        hipLaunchKernelGGL((k3_resnorm<Op, NT>), dim3(nb), dim3(NT), 0, s, op_of(F0), F0.g, FF,
-                           C->part, stop);
-        launch_norm_finalize(PendingNorm{C->part, (int)nb, C->st, C->hist, F0.h * F0.h * F0.h,
+    else
+        launch_norm_finalize(PendingNorm{C->part, nb, C->st, C->hist, F0.h * F0.h * F0.h,
                                          C->o.tol, C->o.diverge, C->o.max_cycles + 1}, s);
-    }
     HIP_TRY(hipGetLastError());
     return MPFC_OK;
 }
@@ -525,19 +533,15 @@ int mpfc3d_step(mpfc3d_ctx* C, const double* phi_n, const double* phi_nm1, doubl
                            F0.u[0], F0.xk, F0.f[1], F0.u[2], F0.u[1]);
     // residual of the guess (history entry 0)
     {
-        const unsigned rb = res_blocks3(total);
         L3 FF{};
         for (int f = 0; f < 3; ++f) { FF.u[f] = F0.u[f]; FF.f[f] = F0.f[f]; }
         FF.xk = F0.xk;
         const bool nw = C->o.linearization == MPFC_NEWTON;
-        if (C->p.scheme == 1) {
-            if (nw) hipLaunchKernelGGL((k3_resnorm<MpfcOp3<1, true>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<1, true>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
-            else hipLaunchKernelGGL((k3_resnorm<MpfcOp3<1, false>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<1, false>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
-        } else {
-            if (nw) hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, true>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, true>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
-            else hipLaunchKernelGGL((k3_resnorm<MpfcOp3<2, false>, NT>), dim3(rb), dim3(NT), 0, s, MpfcOp3<2, false>{lo}, F0.g, FF, C->part, (const CycleState*)nullptr);
-        }
-        launch_norm_finalize(PendingNorm{C->part, (int)rb, C->st, C->hist, F0.h * F0.h * F0.h,
+        auto norm = [&](const auto& op) { return resnorm3(op, F0, FF, C->part, nullptr, s); };
+        const int rb = C->p.scheme == 1
+                           ? (nw ? norm(MpfcOp3<1, true>{lo}) : norm(MpfcOp3<1, false>{lo}))
+                           : (nw ? norm(MpfcOp3<2, true>{lo}) : norm(MpfcOp3<2, false>{lo}));
+        launch_norm_finalize(PendingNorm{C->part, rb, C->st, C->hist, F0.h * F0.h * F0.h,
                                          C->o.tol, C->o.diverge, C->o.max_cycles + 1}, s);
     }
     HIP_TRY(hipGetLastError());

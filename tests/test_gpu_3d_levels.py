@@ -49,3 +49,24 @@ def test_one_cycle(m, n, l, nu1, nu2):
     u, _, _ = O.fas_solve3(po, u0, S, phik=phi0, nu1=nu1, nu2=nu2, tol=1e-30, max_cycles=1,
                            coarse_sweeps=K)
     assert relmax(got, u[0]) <= 1e-12
+
+
+@pytest.mark.parametrize("scheme", [1, 2])
+@pytest.mark.parametrize("m,n,l", [
+    (2, 2, 2), (32, 32, 32), (64, 64, 32), (2, 256, 256),       # a cell per thread
+    (128, 64, 32), (2, 512, 256), (64, 64, 64)])                # a block per thread
+def test_residual_norms(m, n, l, scheme):
+    """The norms of the guess and of two cycles, on both sides of the size from which
+    a thread takes a block of cells."""
+    d = dict(eps=0.025, beta=0.9, M=1.0, h=0.5, dt=0.05, scheme=scheme)
+    rng = np.random.default_rng(31)
+    phi0 = 0.1 + 0.1 * (rng.random((l, n, m)) - 0.5)
+    st = api.Stepper3(m, n, l, api.Params(**d), tol=1e-30, max_cycles=2, coarse_sweeps=K, energy=0)
+    x = torch.from_numpy(phi0).to(DEV)
+    _, info = st.step(x, x, torch.zeros_like(x), allow_fail=True)
+    st.close()
+    po = O.Params(**d)
+    S = O.source3(po, phi0, phi0, np.zeros_like(phi0))
+    u0 = O.complete_guess3(po, phi0.copy(), S, phi0)
+    _, hist, _ = O.fas_solve3(po, u0, S, phik=phi0, tol=1e-30, max_cycles=2, coarse_sweeps=K)
+    np.testing.assert_allclose(info.history, hist, rtol=1e-9)
