@@ -255,31 +255,6 @@ __device__ __forceinline__ void residual_at(const Fields<T>& F, const LevelOp<T>
     r3 = F.f3[q] - (z - op.e * lphi);
 }
 
-// Nonlinear collective Gauss-Seidel update of one cell (App. B): the 3x3
-// system J_loc * delta = r, J_loc = [[1, a, 0], [-d, 1, b], [ec, 0, 1]],
-// a = 4c/h^2, b = 4/h^2, ec = 4e/h^2, d = al + linearised nonlinear
-// coefficient, solved by elimination (equivalent to Cramer's rule; one
-// division).
-template <typename T, int SCHEME, bool NEWTON, bool DEFECT>
-__device__ __forceinline__ void relax_at(const Fields<T>& F, const LevelOp<T>& op, const Grid& g,
-                                         int i, int j) {
-    T r1, r2, r3;
-    residual_at<T, SCHEME, DEFECT>(F, op, g, i, j, r1, r2, r3);
-    const size_t q = at(i, j, g);
-    const T x = F.phi[q];
-    const T xk = (SCHEME == 2) ? F.phik[q] : T(0);
-    const T pb = DEFECT ? F.base[q] : T(0);
-    const T d = op.al + (F.pin ? F.pin[q] : T(0)) + nl_lin<T, SCHEME, NEWTON>(pb + x, xk);
-    const T a = T(4) * op.c * op.ih2, b = T(4) * op.ih2, ec = T(4) * op.e * op.ih2;
-    const T det = T(1) + a * d + a * b * ec;
-    const T dm = (r2 + (d + b * ec) * r1 - b * r3) * recip_ge1(det);
-    const T dx = r1 - a * dm;
-    const T dk = r3 - ec * dx;
-    F.phi[q] = x + op.w * dx;
-    F.mu[q] += op.w * dm;
-    F.ka[q] += op.w * dk;
-}
-
 // r = f - N(u) on every cell (operator-level entry point).
 template <typename T, int SCHEME, bool DEFECT>
 __global__ void __launch_bounds__(256) k_residual_field(Fields<T> F, LevelOp<T> op, Grid g, T* r0,

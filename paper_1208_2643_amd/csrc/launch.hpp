@@ -12,9 +12,8 @@ namespace mpfc {
 
 // Tile shapes (interior TX x TY, largest halo HMAX) instantiated for the
 // tiled levels.  Shapes 0-3 serve halos up to 6 (nu <= 2), shapes 4-6 up to
-// 10.  Grids with a side that is not a power of two take shapes 0, 2 and 3 (the
-// last in place of the first on their small levels: 5.7 us against 6.2 a down
-// launch on 128 x 100).
+// 10.  Grids with a side that is not a power of two take shapes 0, 2 and 3 (their
+// tuner tries 0 or 3 by a level's size and divisors: gen_tries).
 struct TileShape { int tx, ty, hmax; };
 constexpr TileShape kShapes[] = {{64, 32, 6},  {32, 32, 6},  {32, 16, 6}, {16, 16, 6},
                                  {64, 16, 10}, {32, 16, 10}, {16, 16, 10}};

@@ -263,17 +263,8 @@ void tile_dims(const Level& lv, int shape, int& tx, int& ty) {
 }
 
 CoarseGeom coarse_geom(const mpfc_ctx* C) {
-    CoarseGeom G{};
-    G.bc = C->p.bc;
-    G.nlev = (int)C->L.size() - C->Lp;
-    int off = 0;
-    for (int k = 0; k < G.nlev; ++k) {
-        const Level& lv = C->L[C->Lp + k];
-        G.m[k] = lv.m; G.n[k] = lv.n; G.lm[k] = lv.g.lm;
-        G.off[k] = off;
-        off += lv.m * lv.n;
-    }
-    return G;
+    const Level& top = C->L[C->Lp];
+    return CoarseGeom{C->p.bc, top.m, top.n, top.g.lm};
 }
 
 void prof_mark(mpfc_ctx* C, int which, hipStream_t s) {
@@ -348,7 +339,6 @@ CoarseArgs<double> coarse_args64(const mpfc_ctx* C) {
     }
     A.xk = top.xk;
     A.pin = C->pinned ? top.pin : nullptr;
-    A.h_top = top.h;
     A.nsw1 = 2 * C->o.nu1;
     A.nsw2 = 2 * C->o.nu2;
     A.complete_top = C->Lp > 0;
@@ -431,7 +421,6 @@ CoarseArgs<float> coarse_args32(const mpfc_ctx* C) {
     }
     A.xk = FT.xk;
     A.pb = FT.pb;
-    A.h_top = (float)top.h;
     A.nsw1 = 2 * C->o.nu1;
     A.nsw2 = 2 * C->o.nu2;
     if (C->Lp > 0 && C->o.inner_nu_coarse)  // every level here is below the finest
@@ -658,7 +647,6 @@ void vcycle_poisson(mpfc_ctx* C, hipStream_t s, int only = -1, int only_up = 0) 
         A.geo = coarse_geom(C);
         A.u[0] = top.w[0];
         A.rr[0] = Lp > 0 ? top.prr : top.pf;
-        A.h_top = top.h;
         A.nsw1 = 4;
         A.nsw2 = 4;
         A.complete_top = Lp > 0;

@@ -518,7 +518,6 @@ struct CoarseGeom3 {
 
 struct CoarseArgs3 {
     CoarseGeom3 geo;
-    Grid3 gtop;            // top level (its global arrays are colour-split)
     double* u[3];          // top level u (in/out)
     const double* f[3];    // top level R r (complete_top = 1) or complete right-hand side
     const double* xk;      // top level phi^k (scheme 2)

@@ -24,9 +24,9 @@ struct Level3 {
 
 Grid3 make_grid3(int m, int n, int l) { return Grid3{m, n, l, ilog2(m), ilog2(n), ilog2(l)}; }
 unsigned blocks256(size_t cells) { return (unsigned)((cells + 255) / 256); }
-// Reductions in three dimensions: each workgroup sums one contiguous range,
-// whose z-neighbour planes stay in L2 better with 256 long ranges than with
-// the 2-D count (measured: the 128^3 residual norm 30 us vs 36 us).
+// Sums over the caller's fields in three dimensions (energies, Poisson right-hand
+// side): each workgroup takes one contiguous range, so that the z-neighbour planes
+// stay in its L2, and at most 256 of them leave few partial sums.
 constexpr unsigned kRedBlocks3 = 256;
 unsigned red_blocks3(size_t total) {
     const size_t b = (total + NT - 1) / NT;
@@ -214,7 +214,6 @@ int vcycle3(mpfc3d_ctx* C, hipStream_t s) {
             CA.geo.off[k] = off;  // (the top level has arrays of its own)
             if (k > 0) off += lv.m * lv.n * lv.l;
         }
-        CA.gtop = T.g;
         CA.complete_top = top > 0;
         CA.nsw1 = nu1;
         CA.nsw2 = nu2;

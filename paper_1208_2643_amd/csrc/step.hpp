@@ -39,8 +39,9 @@ __global__ void __launch_bounds__(NT) k_resnorm(Fields<double> F, LevelOp<double
 // of one cell (the neighbour rule of wrapx / wrapy) is formed once into LDS, so
 // each cell's value is loaded from memory once instead of by its five stencils.
 // The tile's sum of r^2 goes into part[pslot], summed by the stopping test.  The
-// correction e is cleared by the next outer iteration, not here (other
-// workgroups still read it for their ring).
+// correction e is left as it is (other workgroups still read it for their ring):
+// the next outer iteration's first launch starts from zero without reading it
+// (zero_in), or clears it on grids without tiled levels.
 constexpr int DT_X = 32, DT_Y = 8;
 template <int SCHEME>
 __device__ __forceinline__ void defect_tile(const Fields<double>& F, const LevelOp<double>& op,

@@ -70,7 +70,9 @@ struct MpfcOp {
         }
         residual_lap(u, ns, lap, r);
     }
-    // Collective update of the cells: J_loc delta = f - N(u) (see relax_at).
+    // Collective update of the cells: J_loc delta = f - N(u) (App. B), the
+    // 3x3 system J_loc = [[1, a, 0], [-d, 1, b], [ec, 0, 1]], a = 4c/h^2, b = 4/h^2,
+    // ec = 4e/h^2, d = al + linearised nonlinear coefficient, by elimination.
     // What does not depend on the neighbours comes first (their LDS reads are
     // in flight meanwhile).
     template <int K>
@@ -892,14 +894,12 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_batched(const BatchTile<O
 // solved directly.
 constexpr int CP_CELLS = 1024;  // largest level handled here (32 x 32)
 constexpr int CP_TOTAL = 1368;  // cells of all its levels (1024 + 256 + 64 + 16 + 4, padded)
-constexpr int CP_MAXLEV = 12;
 constexpr int CP_THREADS = CP_CELLS / 2;  // one thread per red-black pair of the largest level
 
+// The top level of the persistent launches (or the coarsest, coarsest launches).
 struct CoarseGeom {
     int bc;               // boundary conditions (BC_NEUMANN_X | BC_NEUMANN_Y bits)
-    int nlev;             // levels in this kernel (top first)
-    int m[CP_MAXLEV], n[CP_MAXLEV], lm[CP_MAXLEV];
-    int off[CP_MAXLEV];   // cell offset of each level in the LDS arrays
+    int m, n, lm;         // sides, log2 m
 };
 
 template <typename T>
@@ -910,7 +910,6 @@ struct CoarseArgs {
     const T* xk;          // phi^k on the top level (global)
     const T* pb;          // base phi on the top level (global)
     const T* pin;         // pinning weight on the top level (global; Op::PW)
-    T h_top;              // spacing of the top level
     int nsw1, nsw2;       // half-sweeps down / up
     int complete_top;     // 1: rr holds R r (add N(u)); 0: rr is already the full f
     const double* G;      // Poisson: Green's matrix of the coarsest grid
@@ -1325,7 +1324,7 @@ struct CoarseWork {
         else
             return __int_as_float(swap1(__float_as_int(x)));
     }
-    // level l has spacing 2^l h_top: scale 1/h^2 (and h^2) by exact powers of two
+    // level l has 2^l times the top level's spacing: scale 1/h^2 (and h^2) by exact powers of two
     static __device__ __forceinline__ Op opl(const Op& top, int l) {
         Op o = top;
         if constexpr (NF == 3) { o.op.ih2 = ldexp(top.op.ih2, -2 * l); o.op.derive(); }
@@ -1574,7 +1573,7 @@ struct CoarseWork {
 
     static __device__ __forceinline__ void run(const Op& top, const CoarseArgs<T>& A, Lds& S,
                                                const CycleState* stop) {
-        Lev L = {A.geo.m[0], A.geo.n[0], A.geo.lm[0], 0, 0};
+        Lev L = {A.geo.m, A.geo.n, A.geo.lm, 0, 0};
         const int bc = A.geo.bc;
         const Pos P = pos(L, bc);
         const size_t g0 = ((size_t)(2 * P.by + P.dy) << L.lm) + 2 * P.bx;  // the west cell
@@ -1670,7 +1669,7 @@ __global__ void __launch_bounds__(CG_THREADS) k_coarsest_sweeps(Op op,
     __shared__ T Su[NF][CG_CELLS];
     if (stopped(stop)) return;
     const int t = threadIdx.x;
-    const int m = A.geo.m[0], n = A.geo.n[0], N = m * n, mh = m >> 1;
+    const int m = A.geo.m, n = A.geo.n, N = m * n, mh = m >> 1;
     const bool nbx = NEU && (A.geo.bc & BC_NEUMANN_X), nby = NEU && (A.geo.bc & BC_NEUMANN_Y);
     for (int q = t; q < N; q += CG_THREADS) {
 #pragma unroll
@@ -1773,7 +1772,7 @@ __global__ void __launch_bounds__(CG_THREADS) k_coarsest_poisson(PoissonOp<T> op
     __shared__ double mean_v;
     if (stopped(stop)) return;
     const int t = threadIdx.x;
-    const int m = A.geo.m[0], n = A.geo.n[0], N = m * n;
+    const int m = A.geo.m, n = A.geo.n, N = m * n;
     const bool nbx = A.geo.bc & BC_NEUMANN_X, nby = A.geo.bc & BC_NEUMANN_Y;
     const double* Vx = A.G;
     const double* Vy = Vx + (size_t)m * m;

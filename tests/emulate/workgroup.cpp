@@ -103,13 +103,9 @@ static int coarse(int m, int n, int bc) {
             f.push_back(field(N, 4 + k, 1.0));
         }
         CoarseArgs<double> A{};
-        A.geo.bc = bc;
-        A.geo.m[0] = m;
-        A.geo.n[0] = n;
-        A.geo.lm[0] = __builtin_ctz(m);
+        A.geo = CoarseGeom{bc, m, n, __builtin_ctz(m)};
         for (int k = 0; k < 3; ++k) { A.u[k] = u[k].data(); A.rr[k] = f[k].data(); }
         A.xk = xk.data();
-        A.h_top = 0.8;
         A.nsw1 = A.nsw2 = 4;
         A.complete_top = 1;
         A.newton_maxit = 30;
