@@ -37,16 +37,11 @@ __device__ __forceinline__ bool stopped(const CycleState* st) {
     return st != nullptr && st->done != 0;
 }
 
-// The same in a launch beside which the flag may rise: one thread's look decides
-// for the workgroup (each wave's own look may differ, and the rest of a workgroup
-// would go on over LDS that the waves which left have not filled).  Every thread of
-// the workgroup calls it; the writer stores the flag atomically.
-__device__ __forceinline__ bool block_stopped(const CycleState* st) {
-    __shared__ int done;
-    if (threadIdx.x == 0)
-        done = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    return done != 0;
+// The same in a launch beside which the flag may rise: a wave's own look, which
+// another wave's may contradict (the writer stores the flag atomically too).
+__device__ __forceinline__ bool stopped_now(const CycleState* st) {
+    return __builtin_amdgcn_readfirstlane(
+               __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -336,7 +331,7 @@ __device__ __forceinline__ void norm_finalize_body(const double* __restrict__ pa
         else if (k > 0 && nr > diverge * first) status = ST_DIVERGED;
         else if (k + 1 >= max_norms) status = ST_MAXCYC;
         st->status = status;
-        // (block_stopped may be looking)
+        // (stopped_now may be looking)
         __hip_atomic_store(&st->done, (int)(status != ST_RUNNING), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -240,6 +240,7 @@ struct TileWork {
         T U[NF][2][LYM][LXP];
         T E[UP ? NF : 1][UP ? CYM : 1][UP ? CXM : 1];  // up: uH - vH
         double red[NT / 64];
+        int saw[NT / 64];  // the waves' looks at a stop flag that may rise
     };
     // Extents of the tile (tbx, tby) of a launch.
     struct Geo {
@@ -801,10 +802,14 @@ struct TileWork {
 
 // Body of one tile launch: the tile into LDS, its right-hand side into
 // registers, then the computation.
+// `vote` (down): the stop flag may rise beside this launch and `saw` is the wave's
+// look at it.  A wave that saw it up loads nothing; behind the barrier the looks of
+// all waves decide for the workgroup, which returns if any saw it.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
-                                          int tbx, int tby, int pslot, bool zero_in) {
+                                          int tbx, int tby, int pslot, bool zero_in,
+                                          bool vote = false, bool saw = false) {
     using W = TileWork<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>;
     __shared__ typename W::Lds S;
     const typename W::Geo G = W::geo(A, tbx, tby);
@@ -816,8 +821,15 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
         __syncthreads();
         if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
-        W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
+        if (!saw) W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
+        if (vote && (threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
         __syncthreads();
+        if (vote) {
+            int any = 0;
+#pragma unroll
+            for (int w = 0; w < W::NT / 64; ++w) any |= S.saw[w];
+            if (any) return;
+        }
     }
     W::compute(op, A, G, S, R, pslot);
 }
@@ -827,18 +839,20 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
 // its stopping test.  The test used to be a launch of its own between the up
 // launch that wrote the sums and the next cycle's finest down launch: 4.4 us and
 // a launch gap of every cycle.  Beside the tiles it costs nothing.  The flag may
-// rise while the tiles of this launch look at it, so each of their workgroups looks
-// once (block_stopped) and either returns whole or runs whole.  A tile that ran
-// beside the test that stops the cycles has written the other copy of u and the
-// next level's arrays, all rewritten before they are read again, and not what it
-// read; every launch behind this one returns at once.
+// rise while the waves of this launch look at it, so a workgroup's waves decide
+// together (tile_body): it returns whole or runs whole.  A tile that ran beside the
+// test that stops the cycles has written the other copy of u and the next level's
+// arrays, all rewritten before they are read again, and not what it read; every
+// launch behind this one returns at once.  (One thread's look for its workgroup,
+// with a barrier ahead of the loads, cost 4 to 5 us of the 113 us on 2048^2.)
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
                                                        const CycleState* stop, PendingNorm P) {
     int b = blockIdx.x, nt = gridDim.x;
-    bool halt;
-    if (!UP && P.nparts) {
+    const bool vote = !UP && P.nparts;
+    bool saw = false;
+    if (vote) {
         if (b == 0) {
             norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
                                              P.max_norms, P.diverge);
@@ -846,14 +860,13 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
         }
         --b;
         --nt;
-        halt = block_stopped(stop);
-    } else {
-        halt = stopped(stop);
+        saw = stopped_now(stop);
+    } else if (stopped(stop)) {
+        return;
     }
-    if (halt) return;
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, tbx, tby, tl, A.zero_in);
+    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, tbx, tby, tl, A.zero_in, vote, saw);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)

@@ -133,6 +133,7 @@ inline void __syncthreads() { emu::yield(emu::AT_WORKGROUP); }
     emu::exchange<ctrl>(x)
 #define __builtin_amdgcn_rcp(x) (1.0 / (x))
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
+#define __builtin_amdgcn_readfirstlane(x) (x)  // used on uniform values
 #define __hip_atomic_load(p, order, scope) (*(p))
 #define __hip_atomic_store(p, v, order, scope) ((void)(*(p) = (v)))
 #define __HIP_MEMORY_SCOPE_AGENT 4
