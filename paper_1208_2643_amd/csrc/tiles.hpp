@@ -930,22 +930,45 @@ struct CoarseArgs {
     T newton_tol;
 };
 
-// Whether Newton's method on the coarsest grid may stop after a step of at most
-// `step` in every cell's phi (xmax: the largest |phi| behind it).  In FP64 also when
-// the error left by the step is known to be below the tolerance, so that no further
-// step has to show it: divided by c times -Lap, the equation is the gradient of a
-// convex function whose second derivative is at least mu = min 1/(c lam) + e lam^2
-// over the grid's eigenvalues lam > 0 of -Lap, plus min(al + W), as g' >= 0.  The
-// residual left is at most |g''| step^2 / 2 per cell with |g''| taken over the step,
-// hence the error at most sqrt(NC) / mu times that, NC <= 8.  (A bare test of step^2
-// against the tolerance left up to 2.3e-14 where c is large, al zero and phi small.)
+// When Newton's method on the coarsest grid may stop: after a step of at most `tol`
+// (1 + |phi|) in every cell's phi, and in FP64 also once the error left by the step
+// is known to be below that, so that no further step has to show it.  Divided by c
+// times -Lap, the equation is the gradient of a convex function whose second
+// derivative is at least mu = 1/(8 c/h^2) + min(al + W): 1/(c lam) for the largest
+// eigenvalue lam <= 8/h^2 of -Lap, and g' >= 0.  A step s leaves a residual of at
+// most |g''| s^2 / 2 per cell, |g''| <= 6 (1 + |phi|), in the second-order scheme 3/2
+// (1 + |phi|) + |phi^k| / 2, hence an error of at most sqrt(NC) / 2 |g''| s^2 / mu, and
+// NC <= 8.  (A bare test of s^2 against the tolerance left up to 2.3e-14 where c is
+// large, al zero and phi small.)
 template <class Op, typename T>
-__device__ __forceinline__ bool newton_done(T step, T xmax, T xkmax, T mu, T tol) {
-    const T lim = tol * (T(1) + xmax), s2 = step * step, top = xmax + step;
-    const T g2 = Op::XK ? T(1.5) * top + T(0.5) * xkmax : T(6) * top;
+struct NewtonStop {
+    T tol, w, v;   // the error bound holds where w s^2 <= v
+    template <int NC>
+    __device__ __forceinline__ NewtonStop(const Op& op, const T (&xk)[NC], const T (&pw)[NC],
+                                          T tol_) : tol(tol_) {
+        T g = T(9), al = op.op.al;
+        if constexpr (Op::XK) {
+            T xm = fabs(xk[0]);
+#pragma unroll
+            for (int a = 1; a < NC; ++a) xm = fmax(xm, fabs(xk[a]));
+            g = T(2.25) + T(0.75) * xm;
+        }
+        if constexpr (Op::PW) {
+            T wm = pw[0];
+#pragma unroll
+            for (int a = 1; a < NC; ++a) wm = fmin(wm, pw[a]);
+            al += wm;
+        }
+        const T q = T(8) * op.op.k1;
+        w = g * q;
+        v = tol * (T(1) + q * al);
+    }
     // (without branches: one thread waits for each)
-    return (step <= lim) | ((sizeof(T) == 8) & (s2 <= lim) & (T(1.5) * g2 * s2 <= lim * mu));
-}
+    __device__ __forceinline__ bool operator()(T step, T xmax) const {
+        const T lim = tol + tol * xmax, s2 = step * step;
+        return (step <= lim) | ((sizeof(T) == 8) & (s2 <= lim) & (w * s2 <= v));
+    }
+};
 
 // Coarsest grid, MPFC: eliminate kappa and mu (kappa = f3 + e Lap phi,
 // mu = f2 + g(phi) + al phi + Lap kappa) and solve the remaining equation
@@ -1020,13 +1043,7 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
         pbv[a] = Op::PB ? pb[a] : T(0);
         alv[a] = Op::PW ? al + pw[a] : al;  // pinning: W added to the phi coefficient
     }
-    T xkmax = T(0), almin = alv[0];
-#pragma unroll
-    for (int a = 0; a < NC; ++a) {
-        xkmax = fmax(xkmax, fabs(xkv[a]));
-        almin = fmin(almin, alv[a]);
-    }
-    const T lmu = almin + T(1) / (T(8) * c * op.op.ih2);  // lam <= 8/h^2
+    const NewtonStop<Op, T> done(op, xkv, pw, tol);
     for (int it = 0; it < maxit; ++it) {
         // residual R = x - c Lap(g(x) + al x + e Lap^2 x) - rhs
         T w[NC], d[NC], R[NC], J[NC][NC + 1];
@@ -1084,7 +1101,7 @@ __device__ __forceinline__ void coarse_solve_mpfc(const Op& op, typename Op::rea
             smax = fmax(smax, fabs(t1[a]));
             xmax = fmax(xmax, fabs(x[a]));
         }
-        if (newton_done<Op>(smax, xmax, xkmax, lmu, tol)) break;
+        if (done(smax, xmax)) break;
     }
     // recover kappa and mu
     lap(x, t1);
@@ -1163,13 +1180,7 @@ __device__ __forceinline__ void coarse_solve_walsh(const Op& op, typename Op::re
 #pragma unroll
         for (int k = 0; k < NC; ++k) s[k] = icl[k] + e * lam[k] * lam[k];
     }
-    T xkmax = T(0), smin = s[1], almin = Op::PW ? al + pw[0] : al;
-#pragma unroll
-    for (int a = 0; a < NC; ++a) {
-        xkmax = Op::XK ? fmax(xkmax, fabs(xk[a])) : T(0);
-        smin = a ? fmin(smin, s[a]) : smin;
-        if constexpr (Op::PW) almin = fmin(almin, al + pw[a]);
-    }
+    const NewtonStop<Op, T> done(op, xk, pw, tol);
     z[0] = rho[0];
     for (int it = 0; it < maxit; ++it) {
         walsh<NC>(z, x, T(1));
@@ -1217,7 +1228,7 @@ __device__ __forceinline__ void coarse_solve_walsh(const Op& op, typename Op::re
             xmax += fabs(z[k]);
         }
         // (smax and xmax: sums over the modes, no cell's value is larger)
-        if (newton_done<Op>(smax, xmax, xkmax, smin + almin, tol)) break;
+        if (done(smax, xmax)) break;
     }
     // kappa = f3 + e Lap phi, mu = f2 + g(phi) + al phi + Lap kappa
     walsh<NC>(z, u[0], T(1));
