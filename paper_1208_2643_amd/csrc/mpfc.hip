@@ -886,19 +886,20 @@ constexpr int kTuneReps = 8;
 // 16 x 16 in place of 64 x 32: ten grids of 64 x 60 to 24 x 640 take 0.71 to 0.95
 // of the time of 64 x 32 tiles with them (a down launch on 128 x 100 5.7 us against
 // 6.2 with 32 x 16), on 256 x 200 a down launch takes 8.1 against 6.6.  All three
-// where the sides' even divisors leave 16 x 16 fewer than kGenTile cells and
-// 64 x 32 at least four times as many: 4 x 4 against 46 x 4 on 92 x 92 takes 288 us a
-// step against 251, 360 against 301 on 124 x 116, but 229 against 241 on 76 x 92.
-// (All three on every small level: a context of 512 x 400 took 22.6 -> 27.3 ms to
-// create, and its steps no less.)
-constexpr int kGenSmall = 16384, kGenTile = 64;
+// where the sides' even divisors leave 16 x 16 more tiles than the 512 workgroups that
+// are resident at a time, and 64 x 32 tiles at least four times as large: 529 of 4 x 4
+// against 46 of 46 x 4 on 92 x 92 take 288 us a step against 251, 899 against 58 on
+// 124 x 116 360 against 301, but 437 against 46 on 76 x 92 229 against 241.  (All
+// three on every small level: a context of 512 x 400 took 22.6 -> 27.3 ms to create,
+// and its steps no less.)
+constexpr int kGenSmall = 16384, kGenResident = 512;
 bool gen_tries(const Level& lv, int k) {
     if (k == 2 || !gen_shape(k)) return k == 2;
     if (lv.m * lv.n > kGenSmall) return k == 0;
     int tx, ty, wx, wy;
     tile_dims(lv, 3, tx, ty);
     tile_dims(lv, 0, wx, wy);
-    return k == 3 || (tx * ty < kGenTile && 4 * tx * ty <= wx * wy);
+    return k == 3 || (lv.m * lv.n > kGenResident * tx * ty && 4 * tx * ty <= wx * wy);
 }
 
 // For every level with tile launches and every launch kind, time each tile
