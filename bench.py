@@ -56,9 +56,9 @@ BATCH_FP32_VCYCLE_BYTES = 340.0
 # shape "TXxTY/HALO", valid only for the kernel sources they were measured on
 # (kernel_source_hash).
 MEASURED_TRAFFIC = {
-    "src": "c250577d457021a9",
-    "down": {"64x32/6": 113722936, "32x32/6": 110209594, "32x16/6": 109991456, "16x16/6": 109990496, "64x16/10": 110935630, "32x16/10": 110020122, "16x16/10": 110014139},
-    "up": {"64x32/6": 108732236, "32x32/6": 104558635, "32x16/6": 103145366, "16x16/6": 103142162, "64x16/10": 103831034, "32x16/10": 103173899, "16x16/10": 103165709},
+    "src": "85752f9bdccf7a58",
+    "down": {"64x32/6": 113701137, "32x32/6": 110229663, "32x16/6": 109998657, "16x16/6": 109981405, "64x16/10": 110849146, "32x16/10": 110025236, "16x16/10": 110017227},
+    "up": {"64x32/6": 108423176, "32x32/6": 104957702, "32x16/6": 103132969, "16x16/6": 103132947, "64x16/10": 103926514, "32x16/10": 103166682, "16x16/10": 103165709},
 }
 
 

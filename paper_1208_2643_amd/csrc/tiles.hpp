@@ -843,8 +843,8 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
 // together (tile_body): it returns whole or runs whole.  A tile that ran beside the
 // test that stops the cycles has written the other copy of u and the next level's
 // arrays, all rewritten before they are read again, and not what it read; every
-// launch behind this one returns at once.  (One thread's look for its workgroup,
-// with a barrier ahead of the loads, cost 4 to 5 us of the 113 us on 2048^2.)
+// launch behind this one returns at once.  (2048^2: 122.9 us without the vote, 123.1
+// with it, 125.9 with one thread's look and a barrier of its own ahead of the loads.)
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
