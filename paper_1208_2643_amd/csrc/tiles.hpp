@@ -239,8 +239,10 @@ struct TileWork {
     struct Lds {
         T U[NF][2][LYM][LXP];
         T E[UP ? NF : 1][UP ? CYM : 1][UP ? CXM : 1];  // up: uH - vH
-        double red[NT / 64];
-        int saw[NT / 64];  // the waves' looks at a stop flag that may rise
+        union {
+            double red[NT / 64];
+            int saw[NT / 64];  // the waves' looks at a stop flag that may rise
+        };
     };
     // Extents of the tile (tbx, tby) of a launch.
     struct Geo {
@@ -894,8 +896,8 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_batched(const BatchTile<O
     const int b = xcd_item(blockIdx.x, nitems);
     const BatchItem it = items[b];
     const BatchTile<Op>& BA = args[it.arg];
-    if (stopped(BA.stop)) return;
     const int tby = it.tile / BA.ntx, tbx = it.tile - tby * BA.ntx;
+    if (stopped(BA.stop)) return;  // (behind the record's loads: its pointer is one of them)
     tile_body<Op, TX, TY, HMAX, UP, NEU, false, EXACT>(BA.op, BA.A, tbx, tby,
                                                        BA.part_off + it.tile,
                                                        first && BA.A.zero_in);
