@@ -22,33 +22,47 @@ bool general_index(const Grid& g) { return g.lm < 0 || g.ln < 0; }
 // precision: 10.3 -> 10.04 ms.  (Shapes 5 and 6 would repeat 2 and 3.)
 constexpr int kHaloSmall = 4;
 
+// One tile launch, with one more workgroup for a pending norm.
+template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN, bool EXACT>
+void tile_launch(const Op& op, TileArgs<typename Op::real>& A, const CycleState* stop,
+                 hipStream_t s, const PendingNorm& P) {
+    A.ntx = A.g.m / A.tx;
+    const dim3 grid(A.ntx * (A.g.n / A.ty) + (P.nparts ? 1 : 0)), blk(kTileThreads);
+    constexpr bool norms = !UP && Op::NF == 3;
+    constexpr bool f64 = std::is_same<typename Op::real, double>::value;
+    if constexpr (norms && !f64) {
+        if (P.nparts) {
+            hipLaunchKernelGGL((k_tile<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, true>), grid, blk, 0,
+                               s, op, A, stop, P);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_tile<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, norms && f64>), grid, blk, 0,
+                       s, op, A, stop, P);
+}
+
 template <class Op, bool UP, bool NEU, int K>
 void tile_k(const Op& op, TileArgs<typename Op::real> A, const CycleState* stop, hipStream_t s,
             bool gen, const PendingNorm& P) {
     constexpr TileShape S = kShapes[K];
-    A.ntx = A.g.m / A.tx;
-    const dim3 grid(A.ntx * (A.g.n / A.ty) + (P.nparts ? 1 : 0)), blk(kTileThreads);
     if constexpr (std::is_same<typename Op::real, double>::value && gen_shape(K)) {
         if (gen) {
-            hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU, true>), grid, blk, 0, s, op,
-                               A, stop, P);
+            tile_launch<Op, S.tx, S.ty, S.hmax, UP, NEU, true, false>(op, A, stop, s, P);
             return;
         }
     }
     // the shape's own tile and halo (the larger levels): compile-time extents
     if (MPFC_TILE_EXACT && A.tx == S.tx && A.ty == S.ty && A.H == S.hmax) {
-        hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU, false, true>), grid, blk, 0, s,
-                           op, A, stop, P);
+        tile_launch<Op, S.tx, S.ty, S.hmax, UP, NEU, false, true>(op, A, stop, s, P);
         return;
     }
     if constexpr (K <= 4) {
         if (MPFC_TILE_EXACT && A.tx == S.tx && A.ty == S.ty && A.H == kHaloSmall) {
-            hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, kHaloSmall, UP, NEU, false, true>), grid, blk,
-                               0, s, op, A, stop, P);
+            tile_launch<Op, S.tx, S.ty, kHaloSmall, UP, NEU, false, true>(op, A, stop, s, P);
             return;
         }
     }
-    hipLaunchKernelGGL((k_tile<Op, S.tx, S.ty, S.hmax, UP, NEU>), grid, blk, 0, s, op, A, stop, P);
+    tile_launch<Op, S.tx, S.ty, S.hmax, UP, NEU, false, false>(op, A, stop, s, P);
 }
 
 template <class Op, bool UP, bool NEU>

@@ -804,11 +804,11 @@ struct TileWork {
 
 // Body of one tile launch: the tile into LDS, its right-hand side into
 // registers, then the computation.
-// `vote` (down): the stop flag may rise beside this launch and `saw` is the wave's
-// look at it.  A wave that saw it up loads nothing; behind the barrier the looks of
-// all waves decide for the workgroup, which returns if any saw it.
+// `vote` (VOTE, down): the stop flag may rise beside this launch and `saw` is the
+// wave's look at it.  A wave that saw it up loads nothing; behind the barrier the looks
+// of all waves decide for the workgroup, which returns if any saw it.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
-          bool EXACT = false>
+          bool EXACT = false, bool VOTE = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
                                           int tbx, int tby, int pslot, bool zero_in,
                                           bool vote = false, bool saw = false) {
@@ -823,10 +823,10 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
         __syncthreads();
         if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
-        if (!saw) W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
-        if (vote && (threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
+        if (!VOTE || !saw) W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
+        if (VOTE && vote && (threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
         __syncthreads();
-        if (vote) {
+        if (VOTE && vote) {
             int any = 0;
 #pragma unroll
             for (int w = 0; w < W::NT / 64; ++w) any |= S.saw[w];
@@ -847,12 +847,15 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
 // arrays, all rewritten before they are read again, and not what it read; every
 // launch behind this one returns at once.  (2048^2: 122.9 us without the vote, 123.1
 // with it, 125.9 with one thread's look and a barrier of its own ahead of the loads.)
-template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
-          bool EXACT = false>
+// VOTE: the kernel can run a pending norm's test (P.nparts).  FP64 down launches all
+// can: the finest level and the ones below share their code.  FP32 ones have it only
+// where there is a test: not taken, it cost a 16 x 16 launch 0.15 to 0.3 of its 5.6 to
+// 11.1 us (arguments that were read ahead of the barrier are read behind it).
+template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN, bool EXACT, bool VOTE>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
                                                        const CycleState* stop, PendingNorm P) {
     int b = blockIdx.x, nt = gridDim.x;
-    const bool vote = !UP && P.nparts;
+    const bool vote = VOTE && P.nparts;
     bool saw = false;
     if (vote) {
         if (b == 0) {
@@ -868,7 +871,8 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
     }
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
-    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>(op, A, tbx, tby, tl, A.zero_in, vote, saw);
+    tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, VOTE>(op, A, tbx, tby, tl, A.zero_in, vote,
+                                                           saw);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)

@@ -70,7 +70,7 @@ static int tile(unsigned wave) {
         P.nparts = 1;  // workgroup 0 is the stopping test's
         emu::run(kTileThreads, dim3(2), dim3(1 + (M / T) * (M / T)),
                  order_from(kTileThreads, wave), [&] {
-                     k_tile<Op, T, T, 6, false, false, false, true>(Op{level(0.8, 0.02, 0.4)}, A,
+                     k_tile<Op, T, T, 6, false, false, false, true, true>(Op{level(0.8, 0.02, 0.4)}, A,
                                                                     &st, P);
                  },
                  [&](unsigned k) { if (rise && k == 64) st.done = 1; });
