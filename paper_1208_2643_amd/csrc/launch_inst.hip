@@ -22,7 +22,11 @@ bool general_index(const Grid& g) { return g.lm < 0 || g.ln < 0; }
 // precision: 10.3 -> 10.04 ms.  (Shapes 5 and 6 would repeat 2 and 3.)
 constexpr int kHaloSmall = 4;
 
-// One tile launch, with one more workgroup for a pending norm.
+// One tile launch, with one more workgroup for a pending norm.  Two kernels, with the
+// vote and without, where a launch without a norm feels it (k_tile): in FP32, and with
+// the FP64 tiles of the small levels (6.84 -> 6.98 us on 64^2 with 16 x 16).  Larger
+// FP64 tiles have one: the finest level shares its code with the levels below (two
+// cost the 512^2 and 1024^2 steps 1.5 % in instruction cache misses).
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN, bool EXACT>
 void tile_launch(const Op& op, TileArgs<typename Op::real>& A, const CycleState* stop,
                  hipStream_t s, const PendingNorm& P) {
@@ -30,14 +34,15 @@ void tile_launch(const Op& op, TileArgs<typename Op::real>& A, const CycleState*
     const dim3 grid(A.ntx * (A.g.n / A.ty) + (P.nparts ? 1 : 0)), blk(kTileThreads);
     constexpr bool norms = !UP && Op::NF == 3;
     constexpr bool f64 = std::is_same<typename Op::real, double>::value;
-    if constexpr (norms && !f64) {
+    constexpr bool two = norms && (!f64 || (!GEN && TX * TY <= 512 && HMAX <= 6));
+    if constexpr (two) {
         if (P.nparts) {
             hipLaunchKernelGGL((k_tile<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, true>), grid, blk, 0,
                                s, op, A, stop, P);
             return;
         }
     }
-    hipLaunchKernelGGL((k_tile<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, norms && f64>), grid, blk, 0,
+    hipLaunchKernelGGL((k_tile<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, norms && !two>), grid, blk, 0,
                        s, op, A, stop, P);
 }
 

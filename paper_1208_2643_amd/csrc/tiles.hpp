@@ -204,6 +204,10 @@ __device__ __forceinline__ int xcd_item(int b, int nt) {
 #endif
 // Threads of a tile workgroup.
 constexpr int kTileThreads = MPFC_TILE_THREADS;
+// Workgroups of the larger tiles resident at a time (two per CU).  A launch of no more
+// has all of them started before the test beside it can end: no wave waits for its
+// look ahead of its loads there.
+constexpr int kResidentTiles = 512;
 static_assert(kTileThreads == kNormThreads, "a tile launch runs a pending stopping test");
 
 // One tile of a tiled level, in phases:
@@ -804,14 +808,15 @@ struct TileWork {
 
 // Body of one tile launch: the tile into LDS, its right-hand side into
 // registers, then the computation.
-// `vote` (VOTE, down): the stop flag may rise beside this launch and `saw` is the
-// wave's look at it.  A wave that saw it up loads nothing; behind the barrier the looks
-// of all waves decide for the workgroup, which returns if any saw it.
+// `vote` (VOTE, down): the stop flag may rise beside this launch and `look` is the
+// wave's look at it.  Behind the barrier the looks of all waves decide for the
+// workgroup, which returns if any saw it up; with `early` such a wave loads nothing.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false, bool VOTE = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
                                           int tbx, int tby, int pslot, bool zero_in,
-                                          bool vote = false, bool saw = false) {
+                                          bool vote = false, int look = 0,
+                                          bool early = false) {
     using W = TileWork<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>;
     __shared__ typename W::Lds S;
     const typename W::Geo G = W::geo(A, tbx, tby);
@@ -823,8 +828,12 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
         __syncthreads();
         if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
-        if (!VOTE || !saw) W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
-        if (VOTE && vote && (threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
+        if (!VOTE || !early || !__builtin_amdgcn_readfirstlane(look))
+            W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
+        if (VOTE && vote) {
+            const int saw = __builtin_amdgcn_readfirstlane(look);
+            if ((threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
+        }
         __syncthreads();
         if (VOTE && vote) {
             int any = 0;
@@ -847,16 +856,16 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
 // arrays, all rewritten before they are read again, and not what it read; every
 // launch behind this one returns at once.  (2048^2: 122.9 us without the vote, 123.1
 // with it, 125.9 with one thread's look and a barrier of its own ahead of the loads.)
-// VOTE: the kernel can run a pending norm's test (P.nparts).  FP64 down launches all
-// can: the finest level and the ones below share their code.  FP32 ones have it only
-// where there is a test: not taken, it cost a 16 x 16 launch 0.15 to 0.3 of its 5.6 to
-// 11.1 us (arguments that were read ahead of the barrier are read behind it).
+// VOTE: the kernel can run a pending norm's test (P.nparts).  Not taken, the vote cost
+// a 16 x 16 launch 0.15 to 0.3 of its 5.6 to 11.1 us (behind a possible return the
+// arguments are read after the barrier, not ahead of it), so most have a kernel
+// without it (tile_launch).
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN, bool EXACT, bool VOTE>
 __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename Op::real> A,
                                                        const CycleState* stop, PendingNorm P) {
     int b = blockIdx.x, nt = gridDim.x;
     const bool vote = VOTE && P.nparts;
-    bool saw = false;
+    int look = 0;
     if (vote) {
         if (b == 0) {
             norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
@@ -865,14 +874,14 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
         }
         --b;
         --nt;
-        saw = stopped_now(stop);
+        look = look_now(stop);
     } else if (stopped(stop)) {
         return;
     }
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
     tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, VOTE>(op, A, tbx, tby, tl, A.zero_in, vote,
-                                                           saw);
+                                                           look, vote && nt > kResidentTiles);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)
