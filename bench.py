@@ -56,9 +56,9 @@ BATCH_FP32_VCYCLE_BYTES = 340.0
 # shape "TXxTY/HALO", valid only for the kernel sources they were measured on
 # (kernel_source_hash).
 MEASURED_TRAFFIC = {
-    "src": "85752f9bdccf7a58",
-    "down": {"64x32/6": 113701137, "32x32/6": 110229663, "32x16/6": 109998657, "16x16/6": 109981405, "64x16/10": 110849146, "32x16/10": 110025236, "16x16/10": 110017227},
-    "up": {"64x32/6": 108423176, "32x32/6": 104957702, "32x16/6": 103132969, "16x16/6": 103132947, "64x16/10": 103926514, "32x16/10": 103166682, "16x16/10": 103165709},
+    "src": "bdd27fb906a089b0",
+    "down": {"64x32/6": 113703056, "32x32/6": 110299832, "32x16/6": 109960942, "16x16/6": 109959852, "64x16/10": 110860482, "32x16/10": 110023188, "16x16/10": 110025337},
+    "up": {"64x32/6": 109758134, "32x32/6": 103708600, "32x16/6": 103145329, "16x16/6": 103129879, "64x16/10": 103862431, "32x16/10": 103163661, "16x16/10": 103162638},
 }
 
 
