@@ -39,8 +39,9 @@ __device__ __forceinline__ bool stopped(const CycleState* st) {
 
 // The flag in a launch beside which it may rise: a wave's own look, which another
 // wave's may contradict (the writer stores the flag atomically too).
-__device__ __forceinline__ int look_now(const CycleState* st) {
-    return __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ bool stopped_now(const CycleState* st) {
+    return __builtin_amdgcn_readfirstlane(
+               __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -330,7 +331,7 @@ __device__ __forceinline__ void norm_finalize_body(const double* __restrict__ pa
         else if (k > 0 && nr > diverge * first) status = ST_DIVERGED;
         else if (k + 1 >= max_norms) status = ST_MAXCYC;
         st->status = status;
-        // (look_now may be looking)
+        // (stopped_now may be looking)
         __hip_atomic_store(&st->done, (int)(status != ST_RUNNING), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }

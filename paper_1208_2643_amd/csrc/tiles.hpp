@@ -204,10 +204,6 @@ __device__ __forceinline__ int xcd_item(int b, int nt) {
 #endif
 // Threads of a tile workgroup.
 constexpr int kTileThreads = MPFC_TILE_THREADS;
-// Workgroups of the larger tiles resident at a time (two per CU).  A launch of no more
-// has all of them started before the test beside it can end: no wave waits for its
-// look ahead of its loads there.
-constexpr int kResidentTiles = 512;
 static_assert(kTileThreads == kNormThreads, "a tile launch runs a pending stopping test");
 
 // One tile of a tiled level, in phases:
@@ -808,15 +804,14 @@ struct TileWork {
 
 // Body of one tile launch: the tile into LDS, its right-hand side into
 // registers, then the computation.
-// `vote` (VOTE, down): the stop flag may rise beside this launch and `look` is the
-// wave's look at it.  Behind the barrier the looks of all waves decide for the
-// workgroup, which returns if any saw it up; with `early` such a wave loads nothing.
+// `vote` (VOTE, down): the stop flag may rise beside this launch and `saw` is the
+// wave's look at it.  A wave that saw it up loads nothing; behind the barrier the looks
+// of all waves decide for the workgroup, which returns if any saw it.
 template <class Op, int TX, int TY, int HMAX, bool UP, bool NEU, bool GEN = false,
           bool EXACT = false, bool VOTE = false>
 __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename Op::real>& A,
                                           int tbx, int tby, int pslot, bool zero_in,
-                                          bool vote = false, int look = 0,
-                                          bool early = false) {
+                                          bool vote = false, bool saw = false) {
     using W = TileWork<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT>;
     __shared__ typename W::Lds S;
     const typename W::Geo G = W::geo(A, tbx, tby);
@@ -828,12 +823,8 @@ __device__ __forceinline__ void tile_body(const Op& op, const TileArgs<typename 
         __syncthreads();
         if (A.nsweep || A.norm) W::fetch_rhs(A, G, R);  // else only the correction is added
     } else {
-        if (!VOTE || !early || !__builtin_amdgcn_readfirstlane(look))
-            W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
-        if (VOTE && vote) {
-            const int saw = __builtin_amdgcn_readfirstlane(look);
-            if ((threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
-        }
+        if (!VOTE || !saw) W::load_direct(A, G, S, zero_in, [&] { W::fetch_rhs(A, G, R); });
+        if (VOTE && vote && (threadIdx.x & 63) == 0) S.saw[threadIdx.x >> 6] = saw;
         __syncthreads();
         if (VOTE && vote) {
             int any = 0;
@@ -865,7 +856,7 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
                                                        const CycleState* stop, PendingNorm P) {
     int b = blockIdx.x, nt = gridDim.x;
     const bool vote = VOTE && P.nparts;
-    int look = 0;
+    bool saw = false;
     if (vote) {
         if (b == 0) {
             norm_finalize_body<kTileThreads>(P.part, P.nparts, P.st, P.hist, P.h2, P.tol,
@@ -874,14 +865,14 @@ __global__ void __launch_bounds__(kTileThreads) k_tile(Op op, TileArgs<typename 
         }
         --b;
         --nt;
-        look = look_now(stop);
+        saw = stopped_now(stop);
     } else if (stopped(stop)) {
         return;
     }
     const int tl = xcd_item(b, nt);
     const int tby = tl / A.ntx, tbx = tl - tby * A.ntx;
     tile_body<Op, TX, TY, HMAX, UP, NEU, GEN, EXACT, VOTE>(op, A, tbx, tby, tl, A.zero_in, vote,
-                                                           look, vote && nt > kResidentTiles);
+                                                           saw);
 }
 
 // Batched launch: one level of many independent grids.  Each (grid, level)
