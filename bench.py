@@ -56,9 +56,9 @@ BATCH_FP32_VCYCLE_BYTES = 340.0
 # shape "TXxTY/HALO", valid only for the kernel sources they were measured on
 # (kernel_source_hash).
 MEASURED_TRAFFIC = {
-    "src": "bdd27fb906a089b0",
-    "down": {"64x32/6": 113703056, "32x32/6": 110299832, "32x16/6": 109960942, "16x16/6": 109959852, "64x16/10": 110860482, "32x16/10": 110023188, "16x16/10": 110025337},
-    "up": {"64x32/6": 109758134, "32x32/6": 103708600, "32x16/6": 103145329, "16x16/6": 103129879, "64x16/10": 103862431, "32x16/10": 103163661, "16x16/10": 103162638},
+    "src": "531a23e160029f14",
+    "down": {"64x32/6": 113722745, "32x32/6": 110265993, "32x16/6": 109957695, "16x16/6": 109971537, "64x16/10": 110842259, "32x16/10": 110025236, "16x16/10": 110018738},
+    "up": {"64x32/6": 108717913, "32x32/6": 104654803, "32x16/6": 103133606, "16x16/6": 103133054, "64x16/10": 104060799, "32x16/10": 103165733, "16x16/10": 103165850},
 }
 
 
